@@ -11,8 +11,9 @@
 //    work-items into LDS, instead of once per work-item;
 //  * for Ls = 8 and 16 the fifth-dimension neighbours psi(s -+ 1) are taken
 //    from the neighbouring lanes with DPP moves instead of memory loads.
-// The generic kernel (other Ls, and the hop-class split used by the coarse
-// build) loads links and fifth-dimension neighbours directly.
+// The site kernel keeps both in LDS for any lattice and Ls; the generic kernel
+// (Ls < 4, and the hop-class split used by the coarse build) loads links and
+// fifth-dimension neighbours directly.
 //
 // Field loads and stores go through buffer descriptors: the per-lane part of an
 // address is one 32-bit byte offset per neighbouring site, the component offset
@@ -512,6 +513,57 @@ __device__ __forceinline__ void st_pair_s_nt(float4 v, __amdgpu_buffer_rsrc_t r,
     }
 }
 
+// Writes a pair of output slices (a1 first: the pair lands reversed) of a
+// work-item at byte offset oo, with the epilogue of store_out.
+template <int NY, bool H16>
+__device__ __forceinline__ void store_pair(const FieldRefs& f, uint32_t oo, const Epi<float>& ep,
+                                           const float2 (&a0)[12], const float2 (&a1)[12]) {
+    typedef float T;
+    if constexpr (NY == 0) {
+#pragma unroll
+        for (int c = 0; c < 12; ++c) {
+            const C2<T> lo = (c < 6) ? a1[c] : cneg<T>(a1[c]);
+            const C2<T> hi = (c < 6) ? a0[c] : cneg<T>(a0[c]);
+            st_pair_s_nt<H16>(make_float4(lo.x, lo.y, hi.x, hi.y), f.out, oo, (uint32_t)c * f.cstride);
+        }
+    } else {
+        // every epilogue load is issued before the first combination: left to
+        // itself the compiler loads one component's fields, stores it and only
+        // then loads the next, twelve dependent round trips at the end of the
+        // workgroup.  The hop temporaries are dead here, so the NY x 12 loaded
+        // pairs fit the register budget (in two halves of 6 components for
+        // four FP32 fields).
+        constexpr int CH = (!H16 && NY >= 4) ? 6 : 12;
+        __amdgpu_buffer_rsrc_t yr[NY];
+#pragma unroll
+        for (int i = 0; i < NY; ++i) yr[i] = make_rsrc(ep.y[i], 12u * f.cstride);
+#pragma unroll
+        for (int c0 = 0; c0 < 12; c0 += CH) {
+            float4 yv[NY][CH];
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int c = 0; c < CH; ++c)
+#pragma unroll
+                for (int i = 0; i < NY; ++i) yv[i][c] = ld_pair_s<H16>(yr[i], oo, (uint32_t)(c0 + c) * f.cstride);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int c = 0; c < CH; ++c) {
+                const int cc = c0 + c;
+                C2<T> lo = (cc < 6) ? a1[cc] : cneg<T>(a1[cc]);
+                C2<T> hi = (cc < 6) ? a0[cc] : cneg<T>(a0[cc]);
+                lo = cscale<T>(ep.beta, lo);
+                hi = cscale<T>(ep.beta, hi);
+#pragma unroll
+                for (int i = 0; i < NY; ++i) {
+                    axpy<T>(ep.g[i], mk<T>(yv[i][c].x, yv[i][c].y), lo);
+                    axpy<T>(ep.g[i], mk<T>(yv[i][c].z, yv[i][c].w), hi);
+                }
+                st_pair_s_nt<H16>(make_float4(lo.x, lo.y, hi.x, hi.y), f.out, oo, (uint32_t)cc * f.cstride);
+            }
+        }
+    }
+}
+
 template <int NY, bool H16>
 __global__ void __launch_bounds__(PAR2_WG) __attribute__((amdgpu_waves_per_eu(2))) dslash_par2_kernel(FineGeom g, TileGeom tg, const float2* U,
                                                                const float2* in, float2* out, Epi<float> ep) {
@@ -633,49 +685,171 @@ __global__ void __launch_bounds__(PAR2_WG) __attribute__((amdgpu_waves_per_eu(2)
     // slice s0 goes to Ls-1-s0, slice s0+1 to Ls-2-s0: one pair at Ls-2-s0,
     // lower spins negated (H = gamma5 R5 D)
     const uint32_t oo = (uint32_t)(st.site * LS + (LS - 2 - s0)) * CB;
-    if constexpr (NY == 0) {
+    store_pair<NY, H16>(f, oo, ep, a0, a1);
+}
+
+// Parity-tile kernel at Ls = 8 (even extents, FP32 and FP64).  The tile scheme
+// above, work-item (p, kk) with W adjacent slices (FP32: a pair, every field
+// access 16 bytes; FP64: one).  At 16^3 x 32 x 8 it takes 81 us in FP32 and 134 us
+// in FP64, against 101 and 166 us for the tile kernel that gathers all eight
+// hops: the gathers' data return bounds both, and this halves them.  Three
+// things keep the loads of a workgroup in flight together: the 72 link entries
+// of a site are split evenly over its work-items and loaded in one batch (a
+// strided loop over the nine entries of a matrix waits for each round), the
+// links, the own spinor and the first partners are all requested before the
+// first LDS store, and no load is guarded (a guarded load ends in a wait at the
+// branch's join).
+template <typename T, int W> struct SliceWord;
+template <typename T> struct SliceWord<T, 1> {
+    typedef C2<T> type;
+    static __device__ __forceinline__ type ld(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
+        return Buf<T>::ld(r, voff, soff);
+    }
+    static __device__ __forceinline__ C2<T> slice(type w, int) { return w; }
+};
+template <> struct SliceWord<float, 2> {
+    typedef float4 type;
+    static __device__ __forceinline__ type ld(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
+        return ld_pair(r, voff, soff);
+    }
+    static __device__ __forceinline__ C2<float> slice(type w, int i) {
+        return i == 0 ? mk<float>(w.x, w.y) : mk<float>(w.z, w.w);
+    }
+};
+
+template <typename T, int W, int LS, int NY>
+__global__ void __launch_bounds__(16 * LS / W) __attribute__((amdgpu_waves_per_eu(2)))
+dslash_ptile_kernel(FineGeom g, TileGeom tg, const C2<T>* U, const C2<T>* in, C2<T>* out, Epi<T> ep) {
+    typedef SliceWord<T, W> Wd;
+    typedef typename Wd::type Word;
+    constexpr uint32_t CB = sizeof(C2<T>);
+    constexpr int NK = LS / W;
+    __shared__ Word spin[12 * 16 * NK];    // [c][pattern][kk]
+    __shared__ C2<T> lds[16 * 8 * LPAD];   // [pattern][matrix][entry]
+    const int p = (int)threadIdx.x / NK, kk = (int)threadIdx.x % NK;
+    const int s0 = W * kk;
+    const Site tt = traverse(tg.t, logical_block(blockIdx.x, gridDim.x));
+    Site st;
+#pragma unroll
+    for (int mu = 0; mu < 4; ++mu) st.x[mu] = 2 * tt.x[mu] + ((p >> mu) & 1);
+    st.site = ((st.x[3] * g.L[2] + st.x[2]) * g.L[1] + st.x[1]) * g.L[0] + st.x[0];
+    const Nbrs<T> n = neighbours<T>(g, st);
+    FieldRefs f;
+    f.cstride = (uint32_t)g.N5 * CB;
+    f.in = make_rsrc(in, 12u * f.cstride);
+    f.out = make_rsrc(out, 12u * f.cstride);
+    f.U = make_rsrc(U, (uint32_t)g.V4 * 36u * CB);
+    // matrix 2 mu is the hop of direction mu inside the tile, 2 mu + 1 the one
+    // leaving it (backward matrices conjugate-transposed)
+    constexpr int LB = 72 / NK;
+    static_assert(LB * NK == 72, "a site's link entries split evenly");
+    C2<T> lk[LB];
+#pragma unroll
+    for (int i = 0; i < LB; ++i) {
+        const int id = kk + i * NK, d = id / 9, mu = d & 3;
+        const int src = d < 4 ? st.site : (mu == 0 ? n.b[0] : mu == 1 ? n.b[1] : mu == 2 ? n.b[2] : n.b[3]);
+        lk[i] = Buf<T>::ld(f.U, (uint32_t)(src * 36 + mu * 9 + id - 9 * d) * CB, 0u);
+    }
+    Word own[12];
+    const uint32_t o0 = (uint32_t)(st.site * LS + s0) * CB;
+#pragma unroll
+    for (int c = 0; c < 12; ++c) own[c] = Wd::ld(f.in, o0, (uint32_t)c * f.cstride);
+    // out-of-tile partners: FP32 pairs two directions ahead, else one
+    constexpr int AHEAD = (W == 2) ? 2 : 1;
+#define HDCR_PT_GATHER(MU)                                                                                    \
+    {                                                                                                         \
+        const uint32_t noff = (uint32_t)((((p >> MU) & 1) ? n.f[MU] : n.b[MU]) * LS + s0) * CB;              \
+        _Pragma("unroll") for (int c = 0; c < 12; ++c) nx[MU % AHEAD][c] = Wd::ld(f.in, noff, (uint32_t)c * f.cstride); \
+    }
+    Word nx[AHEAD][12];
+    HDCR_PT_GATHER(0)
+    if constexpr (AHEAD == 2) HDCR_PT_GATHER(1)
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < LB; ++i) {
+        const int id = kk + i * NK, d = id / 9, e = id - 9 * d, mu = d & 3;
+        const int up = (p >> mu) & 1, r = e / 3;
+        if (d < 4)
+            lds[(p * 8 + 2 * mu + up) * LPAD + e] = lk[i];
+        else
+            lds[(p * 8 + 2 * mu + 1 - up) * LPAD + 3 * (e - 3 * r) + r] = mk<T>(lk[i].x, -lk[i].y);
+    }
+#pragma unroll
+    for (int c = 0; c < 12; ++c) spin[(c * 16 + p) * NK + kk] = own[c];
+    __syncthreads();
+    const C2<T>* lnk = lds + p * 8 * LPAD;
+    C2<T> v[W][12];
+#pragma unroll
+    for (int c = 0; c < 12; ++c)
+#pragma unroll
+        for (int i = 0; i < W; ++i) v[i][c] = Wd::slice(own[c], i);
+
+    // diagonal and fifth-dimension terms: upper spins take slice s - 1, lower
+    // spins slice s + 1 (wall coefficient mf at s = 0 and s = Ls - 1), from the
+    // staged tile
+    C2<T> a[W][12];
+    {
+        const T diag = (T)g.diag, mf = (T)g.mf;
+        const T cm = (s0 == 0) ? mf : (T)-1;
+        const T cp = (s0 + W == LS) ? mf : (T)-1;
+        const int kd = (kk + NK - 1) % NK, ku = (kk + 1) % NK;
+        const C2<T>* sp = reinterpret_cast<const C2<T>*>(spin);
 #pragma unroll
         for (int c = 0; c < 12; ++c) {
-            const C2<T> lo = (c < 6) ? a1[c] : cneg<T>(a1[c]);
-            const C2<T> hi = (c < 6) ? a0[c] : cneg<T>(a0[c]);
-            st_pair_s_nt<H16>(make_float4(lo.x, lo.y, hi.x, hi.y), f.out, oo, (uint32_t)c * f.cstride);
-        }
-    } else {
-        // every epilogue load is issued before the first combination: left to
-        // itself the compiler loads one component's fields, stores it and only
-        // then loads the next, twelve dependent round trips at the end of the
-        // workgroup.  The hop temporaries are dead here, so the NY x 12 loaded
-        // pairs fit the register budget (in two halves of 6 components for
-        // four FP32 fields).
-        constexpr int CH = (!H16 && NY >= 4) ? 6 : 12;
-        __amdgpu_buffer_rsrc_t yr[NY];
-#pragma unroll
-        for (int i = 0; i < NY; ++i) yr[i] = make_rsrc(ep.y[i], 12u * f.cstride);
-#pragma unroll
-        for (int c0 = 0; c0 < 12; c0 += CH) {
-            float4 yv[NY][CH];
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int c = 0; c < CH; ++c)
-#pragma unroll
-                for (int i = 0; i < NY; ++i) yv[i][c] = ld_pair_s<H16>(yr[i], oo, (uint32_t)(c0 + c) * f.cstride);
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int c = 0; c < CH; ++c) {
-                const int cc = c0 + c;
-                C2<T> lo = (cc < 6) ? a1[cc] : cneg<T>(a1[cc]);
-                C2<T> hi = (cc < 6) ? a0[cc] : cneg<T>(a0[cc]);
-                lo = cscale<T>(ep.beta, lo);
-                hi = cscale<T>(ep.beta, hi);
-#pragma unroll
-                for (int i = 0; i < NY; ++i) {
-                    axpy<T>(ep.g[i], mk<T>(yv[i][c].x, yv[i][c].y), lo);
-                    axpy<T>(ep.g[i], mk<T>(yv[i][c].z, yv[i][c].w), hi);
-                }
-                st_pair_s_nt<H16>(make_float4(lo.x, lo.y, hi.x, hi.y), f.out, oo, (uint32_t)cc * f.cstride);
+            if (c < 6) {
+                const C2<T> w = sp[((c * 16 + p) * NK + kd) * W + W - 1];
+                a[0][c] = mk<T>(fma(diag, v[0][c].x, cm * w.x), fma(diag, v[0][c].y, cm * w.y));
+                if constexpr (W == 2)
+                    a[1][c] = mk<T>(fma(diag, v[1][c].x, -v[0][c].x), fma(diag, v[1][c].y, -v[0][c].y));
+            } else {
+                const C2<T> w = sp[((c * 16 + p) * NK + ku) * W];
+                if constexpr (W == 2)
+                    a[0][c] = mk<T>(fma(diag, v[0][c].x, -v[1][c].x), fma(diag, v[0][c].y, -v[1][c].y));
+                a[W - 1][c] = mk<T>(fma(diag, v[W - 1][c].x, cp * w.x), fma(diag, v[W - 1][c].y, cp * w.y));
             }
         }
     }
+#define HDCR_PT_HOPS(MU)                                                                                      \
+    {                                                                                                         \
+        const bool up = (p >> MU) & 1;                                                                        \
+        const T sg_in = up ? (T)-1 : (T)1;                                                                    \
+        const int q = p ^ (1 << MU);                                                                         \
+        C2<T> m[9];                                                                                           \
+        _Pragma("unroll") for (int e = 0; e < 9; ++e) m[e] = lnk[(2 * MU) * LPAD + e];                        \
+        _Pragma("unroll") for (int c = 0; c < 12; ++c) {                                                      \
+            const Word w = spin[(c * 16 + q) * NK + kk];                                                      \
+            _Pragma("unroll") for (int i = 0; i < W; ++i) v[i][c] = Wd::slice(w, i);                          \
+        }                                                                                                     \
+        _Pragma("unroll") for (int i = 0; i < W; ++i)                                                         \
+            hop_core_rt<T, MU>(v[i], m, sg_in, up ? n.cb[MU] : n.cf[MU], a[i]);                               \
+        _Pragma("unroll") for (int e = 0; e < 9; ++e) m[e] = lnk[(2 * MU + 1) * LPAD + e];                    \
+        _Pragma("unroll") for (int c = 0; c < 12; ++c)                                                        \
+            _Pragma("unroll") for (int i = 0; i < W; ++i) v[i][c] = Wd::slice(nx[MU % AHEAD][c], i);          \
+        _Pragma("unroll") for (int i = 0; i < W; ++i)                                                         \
+            hop_core_rt<T, MU>(v[i], m, -sg_in, up ? n.cf[MU] : n.cb[MU], a[i]);                              \
+    }
+#define HDCR_PT_NEXT(MU)                                                                                      \
+    if constexpr (MU + AHEAD < 4) {                                                                           \
+        __builtin_amdgcn_sched_barrier(0);                                                                    \
+        HDCR_PT_GATHER((MU + AHEAD) % 4)                                                                      \
+        __builtin_amdgcn_sched_barrier(0);                                                                    \
+    }
+    HDCR_PT_HOPS(0)
+    HDCR_PT_NEXT(0)
+    HDCR_PT_HOPS(1)
+    HDCR_PT_NEXT(1)
+    HDCR_PT_HOPS(2)
+    HDCR_PT_NEXT(2)
+    HDCR_PT_HOPS(3)
+#undef HDCR_PT_NEXT
+#undef HDCR_PT_HOPS
+#undef HDCR_PT_GATHER
+    // slice s goes to Ls-1-s (a pair to the pair at Ls-2-s0, reversed)
+    const uint32_t oo = (uint32_t)(st.site * LS + (LS - W - s0)) * CB;
+    if constexpr (W == 2)
+        store_pair<NY, false>(f, oo, ep, a[0], a[1]);
+    else
+        store_out<T, NY, true, (sizeof(T) == 8)>(f, oo, ep, a[0]);
 }
 
 // FP16-storage kernel with four fifth-dimension slices per work-item (Ls = 16,
@@ -859,6 +1033,117 @@ dslash_quad_h16_kernel(FineGeom g, TileGeom tg, const float2* U, const uint4_t* 
     }
 }
 
+// Site kernel: any extents, any Ls up to 256 W.  A workgroup holds whole 4d
+// sites, work-item (j, kk) the site j of the workgroup and W adjacent slices.
+// The 72 link entries of a site are loaded once, split over its work-items, and
+// staged in LDS with the workgroup's own spinors (the fifth-dimension
+// neighbours); all eight hops gather from the field.
+struct SiteSplit {
+    int NK;     // work-items per site (Ls / W)
+    int sites;  // sites per workgroup
+};
+template <typename T, int W, int NY>
+__global__ void __launch_bounds__(256) dslash_site_kernel(FineGeom g, SiteSplit ss, const C2<T>* U, const C2<T>* in,
+                                                          C2<T>* out, Epi<T> ep) {
+    typedef SliceWord<T, W> Wd;
+    typedef typename Wd::type Word;
+    constexpr uint32_t CB = sizeof(C2<T>);
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    const int Ls = g.Ls, NK = ss.NK, row = ss.sites * NK;
+    Word* spin = reinterpret_cast<Word*>(smem_raw);          // [c][j][kk]
+    C2<T>* lds = reinterpret_cast<C2<T>*>(spin + 12 * row);  // [j][matrix][entry]
+    // Work-items past the last site repeat another's loads and LDS stores (same
+    // values, same places) and store nothing: a guarded load would end in a wait
+    // at the branch's join.
+    const int t = (int)threadIdx.x / NK, kk = (int)threadIdx.x - t * NK;
+    const int j = min(t, ss.sites - 1);
+    const int lsite = logical_block(blockIdx.x, gridDim.x) * ss.sites + j;
+    const bool active = t < ss.sites && lsite < g.V4;
+    const Site st = traverse(g, min(lsite, g.V4 - 1));
+    const Nbrs<T> n = neighbours<T>(g, st);
+    FieldRefs f;
+    f.cstride = (uint32_t)g.N5 * CB;
+    f.in = make_rsrc(in, 12u * f.cstride);
+    f.out = make_rsrc(out, 12u * f.cstride);
+    f.U = make_rsrc(U, (uint32_t)g.V4 * 36u * CB);
+    constexpr int LB = (W == 2) ? 18 : 9;
+    for (int i0 = 0; i0 * NK < 72; i0 += LB) {
+        C2<T> lk[LB];
+#pragma unroll
+        for (int i = 0; i < LB; ++i) {
+            const int id = min(kk + (i0 + i) * NK, 71), d = id / 9, e = id - 9 * d, mu = d & 3;
+            const int src = d < 4 ? st.site : (mu == 0 ? n.b[0] : mu == 1 ? n.b[1] : mu == 2 ? n.b[2] : n.b[3]);
+            lk[i] = Buf<T>::ld(f.U, (uint32_t)(src * 36 + mu * 9 + e) * CB, 0u);
+        }
+#pragma unroll
+        for (int i = 0; i < LB; ++i) {
+            const int id = min(kk + (i0 + i) * NK, 71), d = id / 9;
+            lds[(j * 8 + d) * LPAD + id - 9 * d] = lk[i];
+        }
+    }
+    const int s0 = W * kk;
+    const uint32_t o0 = (uint32_t)(st.site * Ls + s0) * CB;
+    C2<T> v[W][12];
+#pragma unroll
+    for (int c = 0; c < 12; ++c) {
+        const Word q = Wd::ld(f.in, o0, (uint32_t)c * f.cstride);
+        spin[c * row + j * NK + kk] = q;
+#pragma unroll
+        for (int i = 0; i < W; ++i) v[i][c] = Wd::slice(q, i);
+    }
+    __syncthreads();
+    if (!active) return;
+    const C2<T>* lnk = lds + j * 8 * LPAD;
+    C2<T> a[W][12];
+    {
+        const T diag = (T)g.diag, mf = (T)g.mf;
+        const T cm = (s0 == 0) ? mf : (T)-1;
+        const T cp = (s0 + W == Ls) ? mf : (T)-1;
+        const int kd = (kk == 0) ? NK - 1 : kk - 1, ku = (kk == NK - 1) ? 0 : kk + 1;
+        const C2<T>* sp = reinterpret_cast<const C2<T>*>(spin);
+#pragma unroll
+        for (int c = 0; c < 12; ++c) {
+            if (c < 6) {
+                const C2<T> w = sp[(c * row + j * NK + kd) * W + W - 1];
+                a[0][c] = mk<T>(fma(diag, v[0][c].x, cm * w.x), fma(diag, v[0][c].y, cm * w.y));
+                if constexpr (W == 2)
+                    a[1][c] = mk<T>(fma(diag, v[1][c].x, -v[0][c].x), fma(diag, v[1][c].y, -v[0][c].y));
+            } else {
+                const C2<T> w = sp[(c * row + j * NK + ku) * W];
+                if constexpr (W == 2)
+                    a[0][c] = mk<T>(fma(diag, v[0][c].x, -v[1][c].x), fma(diag, v[0][c].y, -v[1][c].y));
+                a[W - 1][c] = mk<T>(fma(diag, v[W - 1][c].x, cp * w.x), fma(diag, v[W - 1][c].y, cp * w.y));
+            }
+        }
+    }
+#define HDCR_SITE_HOP(MU, FWD)                                                                                \
+    {                                                                                                         \
+        const uint32_t noff = (uint32_t)((FWD ? n.f[MU] : n.b[MU]) * Ls + s0) * CB;                           \
+        C2<T> u[9];                                                                                           \
+        _Pragma("unroll") for (int e = 0; e < 9; ++e) u[e] = lnk[(FWD ? MU : 4 + MU) * LPAD + e];             \
+        _Pragma("unroll") for (int c = 0; c < 12; ++c) {                                                      \
+            const Word q = Wd::ld(f.in, noff, (uint32_t)c * f.cstride);                                       \
+            _Pragma("unroll") for (int i = 0; i < W; ++i) v[i][c] = Wd::slice(q, i);                          \
+        }                                                                                                     \
+        _Pragma("unroll") for (int i = 0; i < W; ++i)                                                         \
+            hop_core<T, MU, FWD>(v[i], u, FWD ? n.cf[MU] : n.cb[MU], a[i]);                                   \
+    }
+    HDCR_SITE_HOP(0, true)
+    HDCR_SITE_HOP(0, false)
+    HDCR_SITE_HOP(1, true)
+    HDCR_SITE_HOP(1, false)
+    HDCR_SITE_HOP(2, true)
+    HDCR_SITE_HOP(2, false)
+    HDCR_SITE_HOP(3, true)
+    HDCR_SITE_HOP(3, false)
+#undef HDCR_SITE_HOP
+    const uint32_t oo = (uint32_t)(st.site * Ls + (Ls - W - s0)) * CB;
+    if constexpr (W == 2)
+        store_pair<NY, false>(f, oo, ep, a[0], a[1]);
+    else
+        store_out<T, NY, true, (sizeof(T) == 8)>(f, oo, ep, a[0]);
+}
+
 // Generic kernel: any Ls, links and fifth-dimension neighbours loaded
 // directly.
 template <typename T, int NY>
@@ -1007,10 +1292,6 @@ bool launch_tile_ls(const FineGeom& g, const C2<T>* U, const C2<T>* in, C2<T>* o
     }
 }
 
-// tile kernel for Ls = 8, 16, 32, 64 with non-temporal output stores (the
-// output is not re-read by this launch; streaming it keeps the L2 for the
-// neighbour re-reads); generic kernel otherwise.  Tuning switch: variant 1
-// uses cached stores for the plain apply, variant 2 the generic kernel.
 // the lattice of 2^4 tiles for the parity-tile kernel (traversal order chosen
 // as for a lattice of those extents)
 TileGeom tile_geom(const FineGeom& g) {
@@ -1052,26 +1333,83 @@ template <typename K> int lds_pad(const FineGeom& g, K kernel) {
     return want;
 }
 
-bool par_ok(const FineGeom& g) {
-    return g.Ls == 16 && g.L[0] % 2 == 0 && g.L[1] % 2 == 0 && g.L[2] % 2 == 0 && g.L[3] % 2 == 0;
+bool even_extents(const FineGeom& g) {
+    return g.L[0] % 2 == 0 && g.L[1] % 2 == 0 && g.L[2] % 2 == 0 && g.L[3] % 2 == 0;
+}
+bool par_ok(const FineGeom& g) { return g.Ls == 16 && even_extents(g); }
+
+// Work split of the site kernel, or false where it does not apply: below four
+// slices a work-item would stage 18 or more link entries by itself, and above
+// 256 work-items a site does not fit the workgroup.  The LDS cap leaves room for
+// two workgroups per compute unit.
+template <typename T, int W> bool site_split(const FineGeom& g, SiteSplit& ss, int& lds) {
+    const int per = (12 * g.Ls + 8 * LPAD) * (int)sizeof(C2<T>);  // LDS bytes per site
+    ss.NK = g.Ls / W;
+    if (g.Ls < 4 || ss.NK > WG) return false;
+    ss.sites = WG / ss.NK;
+    if (ss.sites * per > LDS_PER_CU / 2) ss.sites = LDS_PER_CU / 2 / per;
+    lds = ss.sites * per;
+    return ss.sites > 0;
+}
+template <typename T, int W, int NY>
+bool launch_site(const FineGeom& g, const C2<T>* U, const C2<T>* in, C2<T>* out, const Epi<T>& ep, hipStream_t s) {
+    SiteSplit ss;
+    int lds;
+    if (!site_split<T, W>(g, ss, lds)) return false;
+    hipLaunchKernelGGL((dslash_site_kernel<T, W, NY>), dim3((g.V4 + ss.sites - 1) / ss.sites), dim3(ss.sites * ss.NK), lds,
+                       s, g, ss, U, in, out, ep);
+    return true;
+}
+
+// FP32 fields with even Ls take the site kernel's 16-byte slice pairs from this
+// many 5d sites on; below it the second work-item per pair is worth more: 16^3 x
+// 32 x 12 (1.6M sites) takes 119 us in pairs and 139 us in single slices, 12^4 x
+// 20 (0.4M) 40 and 36 us, 15^4 x 24 (1.2M) 104 and 102 us.
+constexpr int SITE_PAIRS = 1 << 20;
+
+// The library's choice (tune.dslash_variant 0).  Even extents with Ls = 16 or 8:
+// the parity-tile kernels, whose tiles fill whole wavefronts there (at other Ls
+// they do not, and were no faster than the site kernel: 141 against 119 us at 16^3
+// x 32 x 12 in FP32, 234 against 237 us in FP64).  Odd extents with Ls = 16 in FP32:
+// the tile kernel (31.7 against 32.4 us at 11 x 12 x 13 x 14).  Otherwise the site
+// kernel: against the generic one it takes 119 instead of 205 us (FP32) and 237
+// instead of 340 us (FP64) at 16^3 x 32 x 12.
+template <typename T, int NY>
+bool launch_default(const FineGeom& g, const C2<T>* U, const C2<T>* in, C2<T>* out, const Epi<T>& ep, hipStream_t s) {
+    constexpr int W = sizeof(T) == 4 ? 2 : 1;
+    if (even_extents(g) && g.Ls == 16) {
+        const TileGeom tg = tile_geom(g);
+        if constexpr (sizeof(T) == 4) {
+            const int pad = lds_pad(g, dslash_par2_kernel<NY, false>);
+            hipLaunchKernelGGL((dslash_par2_kernel<NY, false>), dim3(tg.t.V4), dim3(PAR2_WG), pad, s, g, tg, U, in, out,
+                               ep);
+        } else {
+            const int pad = lds_pad(g, dslash_par_kernel<T, NY>);
+            hipLaunchKernelGGL((dslash_par_kernel<T, NY>), dim3(tg.t.V4), dim3(WG), pad, s, g, tg, U, in, out, ep);
+        }
+        return true;
+    }
+    if (even_extents(g) && g.Ls == 8) {
+        const TileGeom tg = tile_geom(g);
+        const int pad = lds_pad(g, dslash_ptile_kernel<T, W, 8, NY>);
+        hipLaunchKernelGGL((dslash_ptile_kernel<T, W, 8, NY>), dim3(tg.t.V4), dim3(16 * 8 / W), pad, s, g, tg, U, in, out,
+                           ep);
+        return true;
+    }
+    if (sizeof(T) == 4 && g.Ls == 16) return false;
+    if constexpr (W == 2) {
+        if (g.Ls % 2 == 0 && (g.N5 >= SITE_PAIRS || g.Ls > WG)) return launch_site<T, 2, NY>(g, U, in, out, ep, s);
+    }
+    return launch_site<T, 1, NY>(g, U, in, out, ep, s);
 }
 
 template <typename T, int NY>
 void launch_ny(const FineGeom& g, const C2<T>* U, const C2<T>* in, C2<T>* out, const Epi<T>& ep, hipStream_t s) {
-    // parity-tile kernels at Ls = 16 with even extents: FP32 with paired slices
-    // by default (variant 4: one slice per work-item), FP64 with one slice per
-    // work-item (variants 0 and 4); variants 1 to 3 select the tile and generic
-    // kernels
-    if ((g.variant == 0 || g.variant == 4) && par_ok(g)) {
+    // variant 4: the parity-tile kernel with one slice per work-item; variants 1 to
+    // 3 select the tile and generic kernels
+    if (g.variant == 0 && launch_default<T, NY>(g, U, in, out, ep, s)) return;
+    if (g.variant == 4 && par_ok(g)) {
         const TileGeom tg = tile_geom(g);
-        if constexpr (sizeof(T) == 4) {
-            if (g.variant == 0) {
-                const int pad = lds_pad(g, dslash_par2_kernel<NY, false>);
-                hipLaunchKernelGGL((dslash_par2_kernel<NY, false>), dim3(tg.t.V4), dim3(PAR2_WG), pad, s, g, tg, U,
-                                   in, out, ep);
-                return;
-            }
-        }
         const int pad = lds_pad(g, dslash_par_kernel<T, NY>);
         hipLaunchKernelGGL((dslash_par_kernel<T, NY>), dim3(tg.t.V4), dim3(WG), pad, s, g, tg, U, in, out, ep);
         return;

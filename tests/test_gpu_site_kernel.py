@@ -1,0 +1,73 @@
+"""The fine apply's kernels for fifth dimensions other than 16: the site kernel (links and own spinors
+of whole 4d sites in LDS; slice pairs in FP32 on large lattices) and the parity-tile kernel at Ls = 8,
+against the oracle, and their fused epilogues against the same smoother on the generic kernel."""
+import numpy as np
+import pytest
+
+import hdcr_inputs as hi
+import oracle
+import paper_1611_06944_amd as hd
+from tests.gpu_util import log, max_rel_elem, rel_err, to_dev, to_host, torch_dev
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [
+    ((2, 2, 2, 2), 8),      # one tile, extent-2 directions
+    ((4, 6, 2, 4), 8),      # parity tiles, ragged over the XCDs
+    ((3, 5, 2, 3), 8),      # odd extents at Ls = 8: site kernel, ragged last workgroup
+    ((2, 3, 2, 5), 4),      # smallest Ls of the site kernel, workgroups capped by LDS
+    ((4, 2, 2, 4), 7),      # odd Ls, work-items past the last whole site
+    ((1, 3, 2, 2), 12),     # extent 1
+    ((4, 4, 2, 2), 12),
+    ((3, 2, 2, 3), 24),
+    ((2, 2, 1, 1), 130),    # one site per workgroup, idle lanes
+    ((1, 1, 2, 1), 258),    # FP32 pairs by length, FP64 on the generic kernel
+]
+
+
+@pytest.mark.parametrize("L,Ls", SHAPES)
+@pytest.mark.parametrize("prec,tol", [("c128", 1e-10), ("c64", 1e-5)])
+def test_apply_any_ls(L, Ls, prec, tol):
+    torch = torch_dev()
+    log(f"site kernel L={L} Ls={Ls} {prec}")
+    p = oracle.Params(L, Ls, M5=1.8, mf=0.07, bc=(1, -1, 1, -1), b=1.3)
+    lat = hd.Lattice(L, Ls, M5=p.M5, mf=p.mf, bc=p.bc, b=1.3)
+    U = hi.gauge_field(L, seed=1)
+    psi = hi.gaussian_fermion(L, Ls, seed=0)
+    ref = oracle.apply_h(U, psi, p)
+    dt = torch.complex128 if prec == "c128" else torch.complex64
+    out = hd.apply_fine(lat, to_dev(hd.pack_gauge(U), dt), to_dev(hd.pack_fermion(psi), dt))
+    got = hd.unpack_fermion(to_host(out), L, Ls)
+    assert max_rel_elem(got, ref) <= tol and rel_err(got, ref) <= tol
+
+
+@pytest.mark.parametrize("L,Ls", [((4, 4, 2, 6), 8), ((3, 4, 2, 3), 12), ((2, 3, 3, 2), 5)])
+@pytest.mark.parametrize("prec,tol", [("c128", 1e-12), ("c64", 2e-5)])
+def test_epilogues_match_generic_kernel(L, Ls, prec, tol):
+    """An order-5 smoother runs one to three epilogue fields; FP32 rounding (2^-24 per operation, about
+    10^2 operations deep, the polynomial's growth below 2) stays under 2e-5."""
+    torch = torch_dev()
+    log(f"epilogues L={L} Ls={Ls} {prec}")
+    lat = hd.Lattice(L, Ls, mf=0.05)
+    dt = torch.complex128 if prec == "c128" else torch.complex64
+    U = to_dev(hd.pack_gauge(hi.gauge_field(L, seed=4)), dt)
+    x = to_dev(hd.pack_fermion(hi.gaussian_fermion(L, Ls, seed=3)), dt)
+    got = hd.smooth(lat, U, x, order=5, lo=0.5, hi=64.0)
+    ref = hd.smooth(lat.with_tune(dslash_variant=2), U, x, order=5, lo=0.5, hi=64.0)
+    assert float((got - ref).abs().max()) <= tol * float(ref.abs().max())
+
+
+def test_slice_pairs_match_single_slices():
+    """16 x 16 x 16 x 24 x 12 is above the size from which FP32 takes slice pairs."""
+    torch = torch_dev()
+    L, Ls = (16, 16, 16, 24), 12
+    log("slice pairs")
+    lat = hd.Lattice(L, Ls, mf=0.05)
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(5)
+    U = to_dev(hd.pack_gauge(hi.gauge_field(L, seed=4)), torch.complex64)
+    x = torch.randn((12, lat.V4, Ls), dtype=torch.complex64, device="cuda:0", generator=g)
+    got = hd.apply_fine(lat, U, x)
+    ref = hd.apply_fine(lat.with_tune(dslash_variant=2), U, x)
+    assert float((got - ref).abs().max()) <= 1e-6 * float(ref.abs().max())
+    assert torch.equal(got, hd.apply_fine(lat, U, x))
