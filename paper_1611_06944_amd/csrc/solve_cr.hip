@@ -4,13 +4,24 @@
 //   repeat:  alpha = Re<r,Ar>/|Ap|^2;  x += alpha p;  r -= alpha Ap
 //            Ar = H r;  beta = Re<r',Ar'>/Re<r,Ar>;  p = r + beta p;  Ap = Ar + beta Ap
 //
-// The scalars live in device memory and are consumed by the update kernels
-// directly; the host reads back |r|^2, <r,Ar> and |Ar|^2 once per iteration
-// (one synchronisation) to test convergence and breakdown.  On convergence of
-// the updated residual the true residual b - H x is recomputed; if it does not
-// meet the tolerance the iteration restarts from it.
+// A step is three launches: Ar = H r, the inner products with Ar, and one update
+// of p, Ap, x and r.  The scalars live in device memory: every workgroup of the
+// update reduces the partial sums of the two kernels before it, in the same
+// fixed order, and so takes the same decisions; convergence and breakdown set a
+// flag that ends the later launches of a batch.  The host enqueues a batch of
+// steps and reads the flag and the residual norms back once per batch.  On
+// convergence of the updated residual the true residual b - H x is recomputed;
+// if it does not meet the tolerance the iteration restarts from it.
+//
+// The steps' vectors are streamed, so their bytes bound a step: |Ap|^2 comes from
+//   |Ar + beta Ap|^2 = |Ar|^2 + 2 beta Re<Ap,Ar> + beta^2 |Ap|^2,
+// so that one pass updates all four vectors, and x takes the steps two at a
+// time, from the old and the new p of the second: the update moves 8 vectors a
+// step on average (two passes with a reduction between them moved 12).
+#include <algorithm>
 #include <chrono>
 #include <cmath>
+#include <cstring>
 
 #include "solver.h"
 
@@ -18,108 +29,264 @@ namespace hdcr {
 
 namespace {
 
-enum { S_RAR = 0, S_RAR_NEW = 1, S_APAP = 2, S_RR = 3, S_ARAR = 4, S_BB = 5, S_COUNT = 8 };
+// device scalars of the iteration
+enum { S_RR0 = 0,    // |r|^2 of the residual the iteration starts from
+       S_BB = 1,     // |b|^2
+       S_RAR = 2,    // Re<r,Ar> of the even (2) and odd (3) steps
+       S_ALPHA = 4,  // alpha of the even (4) and odd (5) steps
+       S_HIST = 6 }; // |r|^2 after each step of the batch
+constexpr int CR_BATCH = 32;  // most steps between two read-backs
+constexpr int S_COUNT = S_HIST + CR_BATCH;
+// flags: stop reason and completed steps since the start
+enum { CR_RUN = 0, CR_CONVERGED = 1, CR_BREAKDOWN = 2, CR_NAN = 3 };
+struct CrState {
+    double S[S_COUNT];
+    int reason;
+    int steps;
+};
 
-__global__ void __launch_bounds__(REDUCE_THREADS) cr_update_xr_kernel(int64_t n, double2* __restrict__ x,
-                                                                      double2* __restrict__ r,
-                                                                      const double2* __restrict__ p,
-                                                                      const double2* __restrict__ Ap,
-                                                                      const double* __restrict__ S,
-                                                                      double* __restrict__ partials) {
-    const double alpha = S[S_RAR] / S[S_APAP];
-    double v[1] = {0.0};
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-        double2 xi = x[i], ri = r[i];
-        const double2 pi = p[i], api = Ap[i];
-        xi.x = fma(alpha, pi.x, xi.x);
-        xi.y = fma(alpha, pi.y, xi.y);
+// sums of NQ doubles over the workgroup (REDUCE_THREADS work-items, fixed order:
+// lanes by halves, then the wavefronts in order); every work-item gets them
+template <int NQ> __device__ __forceinline__ void wg_sums(double (&v)[NQ]) {
+    constexpr int WAVES = REDUCE_THREADS / 64;
+    __shared__ double sh[NQ][WAVES];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+#pragma unroll
+        for (int m = 32; m > 0; m >>= 1) v[q] += __shfl_xor(v[q], m);
+    __syncthreads();  // an earlier call may still be reading sh
+    if ((threadIdx.x & 63) == 0) {
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) sh[q][threadIdx.x >> 6] = v[q];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        v[q] = sh[q][0];
+#pragma unroll
+        for (int w = 1; w < WAVES; ++w) v[q] += sh[q][w];
+    }
+}
+
+// v[q0 + q] = sum of row q of the partials (np per row), for NQ rows
+template <int NQ, int N>
+__device__ __forceinline__ void add_partials(const double* __restrict__ part, int np, int q0, double (&v)[N]) {
+#pragma unroll 4
+    for (int i = threadIdx.x; i < np; i += REDUCE_THREADS) {
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) v[q0 + q] += part[(size_t)q * np + i];
+    }
+}
+
+// stop test of |r_k|^2, k >= 1
+__device__ __forceinline__ int cr_stop(double rr, double tol2) {
+    return !isfinite(rr) ? CR_NAN : (rr <= tol2 ? CR_CONVERGED : CR_RUN);
+}
+
+// Step `step` (1, 2, ... since the start), after Ar = H r and its inner products
+// (dpart: rows <r,Ar>, |Ar|^2, Re<Ap,Ar> of ndot partials):
+//   p = r + beta p, Ap = Ar + beta Ap, r -= alpha Ap  (step 1: p = r, Ap = Ar),
+// every second step x += alpha_old p_old + alpha p.  uin / uout: partials of |r|^2
+// and |Ap|^2 of the previous and of this step.  slot: place of the previous
+// step's |r|^2 in the batch's history, or -1.
+// Bound by the 8 or 10 vectors it streams; 256 x 1024 work-items with two
+// elements each in flight.
+template <bool FIRST, bool XUP>
+__global__ void __launch_bounds__(REDUCE_THREADS) cr_step_kernel(int64_t n, double2* __restrict__ x,
+                                                                 double2* __restrict__ r, double2* __restrict__ p,
+                                                                 const double2* __restrict__ Ar,
+                                                                 double2* __restrict__ Ap, const double* dpart, int ndot,
+                                                                 const double* uin, double* uout, CrState* st, int step,
+                                                                 int slot, double tol) {
+    if (st->reason != CR_RUN) return;
+    const bool lead = blockIdx.x == 0 && threadIdx.x == 0;
+    double t[5] = {0, 0, 0, 0, 0};
+    add_partials<3>(dpart, ndot, 0, t);
+    if constexpr (!FIRST) add_partials<2>(uin, (int)gridDim.x, 3, t);
+    wg_sums<5>(t);
+    const double rr = FIRST ? st->S[S_RR0] : t[3];
+    if constexpr (!FIRST) {
+        const int stop = cr_stop(rr, tol * tol * st->S[S_BB]);
+        if (lead && slot >= 0) st->S[S_HIST + slot] = rr;
+        if (stop != CR_RUN) {
+            if (lead) st->reason = stop;
+            return;
+        }
+    }
+    const double rar = t[0];
+    // (near-)breakdown: <r,Ar> at rounding level of |r||Ar|
+    if (!(fabs(rar) >= 1e-13 * sqrt(rr) * sqrt(t[1]))) {
+        if (lead) st->reason = isfinite(rar) ? CR_BREAKDOWN : CR_NAN;
+        return;
+    }
+    const double beta = FIRST ? 0.0 : rar / st->S[S_RAR + ((step - 1) & 1)];
+    const double apap = FIRST ? t[1] : t[1] + 2.0 * beta * t[2] + beta * beta * t[4];
+    const double alpha = rar / apap, aold = XUP ? st->S[S_ALPHA + ((step - 1) & 1)] : 0.0;
+    double v[2] = {0.0, 0.0};
+    const int64_t stride = (int64_t)gridDim.x * REDUCE_THREADS;
+    auto element = [&](int64_t i, double2 ri, double2 ari, double2 po, double2 apo, double2 xi) {
+        double2 pi = ri, api = ari;
+        if constexpr (!FIRST) {
+            pi.x = fma(beta, po.x, ri.x);
+            pi.y = fma(beta, po.y, ri.y);
+            api.x = fma(beta, apo.x, ari.x);
+            api.y = fma(beta, apo.y, ari.y);
+        }
+        if constexpr (XUP) {
+            xi.x = fma(alpha, pi.x, fma(aold, po.x, xi.x));
+            xi.y = fma(alpha, pi.y, fma(aold, po.y, xi.y));
+            x[i] = xi;
+        }
         ri.x = fma(-alpha, api.x, ri.x);
         ri.y = fma(-alpha, api.y, ri.y);
-        x[i] = xi;
-        r[i] = ri;
-        v[0] += ri.x * ri.x + ri.y * ri.y;
-    }
-    block_reduce<1>(v);
-    if (threadIdx.x == 0) partials[blockIdx.x] = v[0];
-}
-
-// p = r + beta p;  Ap = Ar + beta Ap;  partial |Ap|^2   (beta = S[RAR_NEW]/S[RAR]);
-// with init = true: p = r, Ap = Ar (beta = 0)
-__global__ void __launch_bounds__(REDUCE_THREADS) cr_update_p_kernel(int64_t n, const double2* __restrict__ r,
-                                                                     double2* __restrict__ p,
-                                                                     const double2* __restrict__ Ar,
-                                                                     double2* __restrict__ Ap,
-                                                                     const double* __restrict__ S, int init,
-                                                                     double* __restrict__ partials) {
-    const double beta = init ? 0.0 : S[S_RAR_NEW] / S[S_RAR];
-    double v[1] = {0.0};
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-        const double2 ri = r[i], ari = Ar[i];
-        double2 pi, api;
-        if (init) {
-            pi = ri;
-            api = ari;
-        } else {
-            pi = p[i];
-            api = Ap[i];
-            pi.x = fma(beta, pi.x, ri.x);
-            pi.y = fma(beta, pi.y, ri.y);
-            api.x = fma(beta, api.x, ari.x);
-            api.y = fma(beta, api.y, ari.y);
-        }
         p[i] = pi;
         Ap[i] = api;
-        v[0] += api.x * api.x + api.y * api.y;
+        r[i] = ri;
+        v[0] += ri.x * ri.x + ri.y * ri.y;
+        v[1] += api.x * api.x + api.y * api.y;
+    };
+    constexpr int U = 2;
+    int64_t i = (int64_t)blockIdx.x * REDUCE_THREADS + threadIdx.x;
+    for (; i + (U - 1) * stride < n; i += U * stride) {
+        double2 a[U], b[U], c[U], d[U], e[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            a[u] = r[i + u * stride];
+            b[u] = Ar[i + u * stride];
+            c[u] = FIRST ? make_double2(0, 0) : p[i + u * stride];
+            d[u] = FIRST ? make_double2(0, 0) : Ap[i + u * stride];
+            e[u] = XUP ? x[i + u * stride] : make_double2(0, 0);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) element(i + u * stride, a[u], b[u], c[u], d[u], e[u]);
     }
-    block_reduce<1>(v);
-    if (threadIdx.x == 0) partials[blockIdx.x] = v[0];
+    for (; i < n; i += stride)
+        element(i, r[i], Ar[i], FIRST ? make_double2(0, 0) : p[i], FIRST ? make_double2(0, 0) : Ap[i],
+                XUP ? x[i] : make_double2(0, 0));
+    wg_sums<2>(v);
+    if (threadIdx.x == 0) {
+        uout[blockIdx.x] = v[0];
+        uout[gridDim.x + blockIdx.x] = v[1];
+    }
+    if (lead) {
+        st->S[S_RAR + (step & 1)] = rar;
+        st->S[S_ALPHA + (step & 1)] = alpha;
+        st->steps = step;
+    }
 }
 
-// partials of (Re<r,Ar>, |Ar|^2)
+// |r|^2 after the last step of a batch, and its stop test
+__global__ void __launch_bounds__(REDUCE_THREADS) cr_check_kernel(const double* uin, int nu, CrState* st, int step,
+                                                                  int slot, double tol) {
+    if (st->reason != CR_RUN || st->steps != step) return;
+    double t[1] = {0.0};
+    add_partials<1>(uin, nu, 0, t);
+    wg_sums<1>(t);
+    if (threadIdx.x == 0) {
+        st->S[S_HIST + slot] = t[0];
+        st->reason = cr_stop(t[0], tol * tol * st->S[S_BB]);
+    }
+}
+
+// x += alpha p of an odd last step, which x has not taken yet
+__global__ void __launch_bounds__(REDUCE_THREADS) cr_flush_kernel(int64_t n, double2* __restrict__ x,
+                                                                  const double2* __restrict__ p, const CrState* st) {
+    const double alpha = st->S[S_ALPHA + 1];
+    const int64_t stride = (int64_t)gridDim.x * REDUCE_THREADS;
+    for (int64_t i = (int64_t)blockIdx.x * REDUCE_THREADS + threadIdx.x; i < n; i += stride) {
+        double2 xi = x[i];
+        const double2 pi = p[i];
+        xi.x = fma(alpha, pi.x, xi.x);
+        xi.y = fma(alpha, pi.y, xi.y);
+        x[i] = xi;
+    }
+}
+
+// partials of Re<r,Ar>, |Ar|^2 and (Ap not null) Re<Ap,Ar>
+template <bool FIRST>
 __global__ void __launch_bounds__(REDUCE_THREADS) cr_dots_kernel(int64_t n, const double2* __restrict__ r,
                                                                  const double2* __restrict__ Ar,
-                                                                 double* __restrict__ partials) {
-    double v[2] = {0.0, 0.0};
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
+                                                                 const double2* __restrict__ Ap,
+                                                                 const CrState* __restrict__ st,
+                                                                 double* __restrict__ dpart) {
+    if (st->reason != CR_RUN) return;
+    double v[3] = {0.0, 0.0, 0.0};
+    const int64_t stride = (int64_t)gridDim.x * REDUCE_THREADS;
+#pragma unroll 2
+    for (int64_t i = (int64_t)blockIdx.x * REDUCE_THREADS + threadIdx.x; i < n; i += stride) {
         const double2 a = r[i], b = Ar[i];
         v[0] += a.x * b.x + a.y * b.y;
         v[1] += b.x * b.x + b.y * b.y;
+        if constexpr (!FIRST) {
+            const double2 c = Ap[i];
+            v[2] += c.x * b.x + c.y * b.y;
+        }
     }
-    block_reduce<2>(v);
+    wg_sums<3>(v);
     if (threadIdx.x == 0) {
-        partials[blockIdx.x] = v[0];
-        partials[REDUCE_BLOCKS + blockIdx.x] = v[1];
+#pragma unroll
+        for (int q = 0; q < 3; ++q) dpart[(size_t)q * gridDim.x + blockIdx.x] = v[q];
     }
 }
 
-// r = b - Hx; partial |r|^2
+// r = b - Hx; partial |r|^2 (row 0) and |b|^2 (row 1)
 __global__ void __launch_bounds__(REDUCE_THREADS) residual_kernel(int64_t n, const double2* __restrict__ b,
                                                                   const double2* __restrict__ Hx,
                                                                   double2* __restrict__ r,
-                                                                  double* __restrict__ partials) {
-    double v[1] = {0.0};
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
+                                                                  double* __restrict__ part) {
+    double v[2] = {0.0, 0.0};
+    const int64_t stride = (int64_t)gridDim.x * REDUCE_THREADS;
+#pragma unroll 2
+    for (int64_t i = (int64_t)blockIdx.x * REDUCE_THREADS + threadIdx.x; i < n; i += stride) {
         const double2 bi = b[i], hi = Hx[i];
         const double2 ri = make_double2(bi.x - hi.x, bi.y - hi.y);
         r[i] = ri;
         v[0] += ri.x * ri.x + ri.y * ri.y;
+        v[1] += bi.x * bi.x + bi.y * bi.y;
     }
-    block_reduce<1>(v);
-    if (threadIdx.x == 0) partials[blockIdx.x] = v[0];
+    wg_sums<2>(v);
+    if (threadIdx.x == 0) {
+        part[blockIdx.x] = v[0];
+        part[gridDim.x + blockIdx.x] = v[1];
+    }
+}
+
+// start of the iteration: |r|^2 and |b|^2 from residual_kernel, flags cleared
+__global__ void __launch_bounds__(REDUCE_THREADS) cr_start_kernel(const double* part, int np, CrState* st) {
+    double t[2] = {0.0, 0.0};
+    add_partials<2>(part, np, 0, t);
+    wg_sums<2>(t);
+    if (threadIdx.x == 0) {
+        st->S[S_RR0] = t[0];
+        st->S[S_BB] = t[1];
+        st->reason = CR_RUN;
+        st->steps = 0;
+    }
+}
+
+struct CrBuffers {
+    double2 *r, *p, *Ar, *Ap;
+    double* dpart;     // 3 rows
+    double* upart[2];  // 2 rows each
+    CrState* st;
+};
+CrBuffers cr_carve(Carver& c, int64_t n) {
+    CrBuffers w;
+    w.r = c.take<double2>(n);
+    w.p = c.take<double2>(n);
+    w.Ar = c.take<double2>(n);
+    w.Ap = c.take<double2>(n);
+    w.dpart = c.take<double>(3 * REDUCE_BLOCKS);
+    for (int i = 0; i < 2; ++i) w.upart[i] = c.take<double>(2 * REDUCE_BLOCKS);
+    w.st = c.take<CrState>(1);
+    return w;
 }
 
 }  // namespace
 
 size_t cr_workspace_bytes(const FineGeom& g) {
     Carver c(nullptr, 0);
-    const int64_t n = 12LL * g.N5;
-    for (int k = 0; k < 4; ++k) c.take<double2>(n);
-    c.take<double>(2 * REDUCE_BLOCKS);
-    c.take<double>(S_COUNT);
+    cr_carve(c, 12LL * g.N5);
     return c.used();
 }
 
@@ -128,38 +295,36 @@ int cr_solve(const FineGeom& g, const hdcr_solve_params* prm, const double2* U, 
     const auto t0 = std::chrono::steady_clock::now();
     const int64_t n = 12LL * g.N5;
     Carver c(work, work_bytes);
-    double2* r = c.take<double2>(n);
-    double2* p = c.take<double2>(n);
-    double2* Ar = c.take<double2>(n);
-    double2* Ap = c.take<double2>(n);
-    double* part = c.take<double>(2 * REDUCE_BLOCKS);
-    double* S = c.take<double>(S_COUNT);
+    const CrBuffers w = cr_carve(c, n);
     if (!c.ok()) return fail(HDCR_ENOMEM, "hdcr_solve: workspace too small for CR");
 
-    const dim3 rg(REDUCE_BLOCKS), rt(REDUCE_THREADS);
-    double hS[S_COUNT];
-    auto readS = [&]() -> hipError_t {
-        hipError_t e = hipMemcpyAsync(hS, S, sizeof(hS), hipMemcpyDeviceToHost, s);
+    // two or more elements per work-item, at most REDUCE_BLOCKS workgroups
+    const int64_t want = (n + 2 * REDUCE_THREADS - 1) / (2 * REDUCE_THREADS);
+    const int nwg = (int)std::min<int64_t>(want < 1 ? 1 : want, REDUCE_BLOCKS);
+    const dim3 rg(nwg), rt(REDUCE_THREADS);
+    CrState h;
+    auto read = [&]() -> hipError_t {
+        hipError_t e = hipMemcpyAsync(&h, w.st, sizeof(h), hipMemcpyDeviceToHost, s);
         if (e != hipSuccess) return e;
         return hipStreamSynchronize(s);
     };
-
     int64_t napply = 0;
-    // |b|^2
-    hipLaunchKernelGGL(cr_dots_kernel, rg, rt, 0, s, n, b, b, part);
-    launch_finalize_real(part, 1, S, S_BB, -1, -1, -1, s);
-    // r = b - H x
-    launch_dslash<double>(g, U, x, Ar, s);
-    ++napply;
-    hipLaunchKernelGGL(residual_kernel, rg, rt, 0, s, n, b, Ar, r, part);
-    launch_finalize_real(part, 1, S, S_RR, -1, -1, -1, s);
-    HDCR_HIP_CHECK(readS());
-    const double bb = hS[S_BB];
+    // r = b - H x, |r|^2, |b|^2
+    auto true_residual = [&]() -> hipError_t {
+        launch_dslash<double>(g, U, x, w.Ar, s);
+        ++napply;
+        hipLaunchKernelGGL(residual_kernel, rg, rt, 0, s, n, b, w.Ar, w.r, w.dpart);
+        hipLaunchKernelGGL(cr_start_kernel, dim3(1), rt, 0, s, (const double*)w.dpart, nwg, w.st);
+        return read();
+    };
+
+    HDCR_HIP_CHECK(true_residual());
+    const double bb = h.S[S_BB];
     const double tol2 = prm->tol * prm->tol * bb;
     int status = HDCR_ENOTCONV;
     int it = 0;
     int hl = 0;
-    double rr = hS[S_RR];
+    double rr = h.S[S_RR0];
     if (bb == 0.0) {
         HDCR_HIP_CHECK(hipMemsetAsync(x, 0, n * sizeof(double2), s));
         HDCR_HIP_CHECK(hipStreamSynchronize(s));
@@ -170,70 +335,66 @@ int cr_solve(const FineGeom& g, const hdcr_solve_params* prm, const double2* U, 
     } else if (rr <= tol2) {
         status = HDCR_OK;
     }
-    bool need_init = true;
+    bool fresh = true;  // r is the true residual of x
     while (status == HDCR_ENOTCONV && it < prm->maxiter) {
-        if (need_init) {
-            // p = r, Ar = H r, Ap = Ar, <r,Ar>, |Ar|^2, |Ap|^2
-            launch_dslash<double>(g, U, r, Ar, s);
-            ++napply;
-            hipLaunchKernelGGL(cr_dots_kernel, rg, rt, 0, s, n, r, Ar, part);
-            launch_finalize_real(part, 2, S, S_RAR, S_ARAR, -1, -1, s);
-            hipLaunchKernelGGL(cr_update_p_kernel, rg, rt, 0, s, n, r, p, Ar, Ap, S, 1, part);
-            launch_finalize_real(part, 1, S, S_APAP, -1, -1, -1, s);
-            HDCR_HIP_CHECK(readS());
-            need_init = false;
-            const double rAr = hS[S_RAR];
-            if (!(std::fabs(rAr) >= 1e-13 * std::sqrt(rr) * std::sqrt(hS[S_ARAR]))) {
-                status = std::isfinite(rAr) ? HDCR_EBREAKDOWN : HDCR_ENAN;
-                break;
+        // steps from the residual in r, in batches
+        int step = 0, reason = CR_RUN, batch = 8;
+        ++napply;  // the first step's apply
+        while (reason == CR_RUN && it < prm->maxiter) {
+            const int nb = std::min(batch, prm->maxiter - it);
+            const int first = step + 1;
+            for (int k = 0; k < nb; ++k) {
+                ++step;
+                const double* uin = w.upart[(step - 1) & 1];
+                double* uout = w.upart[step & 1];
+                const int slot = k > 0 ? k - 1 : -1;
+                launch_dslash<double>(g, U, w.r, w.Ar, s);
+#define HDCR_CR_STEP(F, XU)                                                                                        \
+    hipLaunchKernelGGL((cr_step_kernel<F, XU>), rg, rt, 0, s, n, x, w.r, w.p, (const double2*)w.Ar, w.Ap,          \
+                       (const double*)w.dpart, nwg, uin, uout, w.st, step, slot, prm->tol)
+                if (step == 1) {
+                    hipLaunchKernelGGL(cr_dots_kernel<true>, rg, rt, 0, s, n, w.r, w.Ar, w.Ap, w.st, w.dpart);
+                    HDCR_CR_STEP(true, false);
+                } else {
+                    hipLaunchKernelGGL(cr_dots_kernel<false>, rg, rt, 0, s, n, w.r, w.Ar, w.Ap, w.st, w.dpart);
+                    if (step % 2 == 0)
+                        HDCR_CR_STEP(false, true);
+                    else
+                        HDCR_CR_STEP(false, false);
+                }
+#undef HDCR_CR_STEP
+            }
+            hipLaunchKernelGGL(cr_check_kernel, dim3(1), rt, 0, s, (const double*)w.upart[step & 1], nwg, w.st, step,
+                               nb - 1, prm->tol);
+            HDCR_HIP_CHECK(read());
+            reason = h.reason;
+            const int did = h.steps - (first - 1);  // steps of this batch that were taken
+            for (int k = 0; k < did; ++k)
+                if (history && hl < hcap) history[hl++] = std::sqrt(h.S[S_HIST + k] / bb);
+            const double before = rr;
+            if (did > 0) rr = h.S[S_HIST + did - 1];
+            it += did;
+            napply += did;
+            step = h.steps;
+            // the next batch: half the steps that this batch's rate predicts
+            batch = CR_BATCH;
+            if (reason == CR_RUN && did > 0 && rr < before) {
+                const double left = std::log(rr / tol2) / std::log(before / rr) * did;
+                if (left < 2.0 * CR_BATCH) batch = std::max(4, (int)(0.5 * left));
             }
         }
-        // x += alpha p; r -= alpha Ap; |r|^2; then speculatively Ar = H r, <r,Ar>, |Ar|^2
-        hipLaunchKernelGGL(cr_update_xr_kernel, rg, rt, 0, s, n, x, r, p, Ap, S, part);
-        launch_finalize_real(part, 1, S, S_RR, -1, -1, -1, s);
-        launch_dslash<double>(g, U, r, Ar, s);
-        ++napply;
-        hipLaunchKernelGGL(cr_dots_kernel, rg, rt, 0, s, n, r, Ar, part);
-        launch_finalize_real(part, 2, S, S_RAR_NEW, S_ARAR, -1, -1, s);
-        HDCR_HIP_CHECK(readS());
-        ++it;
-        rr = hS[S_RR];
-        if (history && hl < hcap) history[hl++] = std::sqrt(rr / bb);
-        if (!std::isfinite(rr)) {
-            status = HDCR_ENAN;
-            break;
-        }
-        if (rr <= tol2) {
-            // true residual
-            launch_dslash<double>(g, U, x, Ar, s);
-            ++napply;
-            hipLaunchKernelGGL(residual_kernel, rg, rt, 0, s, n, b, Ar, r, part);
-            launch_finalize_real(part, 1, S, S_RR, -1, -1, -1, s);
-            HDCR_HIP_CHECK(readS());
-            rr = hS[S_RR];
-            if (rr <= tol2) {
-                status = HDCR_OK;
-                break;
-            }
-            need_init = true;
-            continue;
-        }
-        const double rAr_new = hS[S_RAR_NEW];
-        const double ArAr = hS[S_ARAR];
-        if (!(std::fabs(rAr_new) >= 1e-13 * std::sqrt(rr) * std::sqrt(ArAr))) {
-            status = std::isfinite(rAr_new) ? HDCR_EBREAKDOWN : HDCR_ENAN;
-            break;
-        }
-        // p = r + beta p; Ap = Ar + beta Ap; |Ap|^2; then <r,Ar> becomes the old value
-        hipLaunchKernelGGL(cr_update_p_kernel, rg, rt, 0, s, n, r, p, Ar, Ap, S, 0, part);
-        launch_finalize_real(part, 1, S, S_APAP, -1, S_RAR_NEW, S_RAR, s);
+        if (step % 2 == 1) hipLaunchKernelGGL(cr_flush_kernel, rg, rt, 0, s, n, x, (const double2*)w.p, w.st);
+        fresh = false;
+        if (reason == CR_BREAKDOWN) status = HDCR_EBREAKDOWN;
+        if (reason == CR_NAN) status = HDCR_ENAN;
+        if (reason != CR_CONVERGED) break;
+        HDCR_HIP_CHECK(true_residual());
+        rr = h.S[S_RR0];
+        fresh = true;
+        if (rr <= tol2) status = HDCR_OK;
     }
     // final true residual (also when not converged)
-    launch_dslash<double>(g, U, x, Ar, s);
-    ++napply;
-    hipLaunchKernelGGL(residual_kernel, rg, rt, 0, s, n, b, Ar, r, part);
-    launch_finalize_real(part, 1, S, S_RR, -1, -1, -1, s);
-    HDCR_HIP_CHECK(readS());
+    if (!fresh || bb == 0.0) HDCR_HIP_CHECK(true_residual());
     HDCR_HIP_CHECK(hipGetLastError());
     const double t = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
     if (st) {
@@ -243,7 +404,7 @@ int cr_solve(const FineGeom& g, const hdcr_solve_params* prm, const double2* U, 
         st->fine_applies_f64 = napply;
         st->fine_applies_inner = 0;
         st->coarse_applies = 0;
-        st->true_rel_residual = bb > 0 ? std::sqrt(hS[S_RR] / bb) : 0.0;
+        st->true_rel_residual = bb > 0 ? std::sqrt(h.S[S_RR0] / bb) : 0.0;
         st->seconds_total = t;
         st->seconds_fine = 0;
         st->seconds_coarse = 0;
