@@ -301,6 +301,63 @@ __device__ __forceinline__ void store_out(const FieldRefs& f, uint32_t oo, const
     }
 }
 
+// Inner products of a conjugate residual step, taken where the apply Ar = H r is
+// written (in = r, out = Ar), to DOT_ROWS rows of partials.  r at the output
+// slices is in the staged tile, so only Ap is read on top of the apply; a pass of
+// its own would read r, Ar and Ap.
+struct DotOut {
+    const double2* Ap;
+    double* part;
+};
+template <typename R>
+__device__ __forceinline__ void store_out_dots(const FieldRefs& f, uint32_t oo, const DotOut& dt, const double2 (&acc)[12],
+                                               R&& rown, double* sh) {
+    const __amdgpu_buffer_rsrc_t ra = make_rsrc(dt.Ap, 12u * f.cstride);
+    double2 ap[12];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int c = 0; c < 12; ++c) ap[c] = Buf<double>::ld(ra, oo, (uint32_t)c * f.cstride);
+    __builtin_amdgcn_sched_barrier(0);
+    double rar = 0.0;
+    Sum2 arar = {0.0, 0.0}, apar = {0.0, 0.0};
+#pragma unroll
+    for (int c = 0; c < 12; ++c) {
+        const double2 o = (c < 6) ? acc[c] : cneg<double>(acc[c]);
+        const double2 r = rown(c);
+        Buf<double>::st_nt(o, f.out, oo, (uint32_t)c * f.cstride);
+        rar = fma(r.x, o.x, fma(r.y, o.y, rar));
+        add_product(arar, o.x, o.x);
+        add_product(arar, o.y, o.y);
+        add_product(apar, ap[c].x, o.x);
+        add_product(apar, ap[c].y, o.y);
+    }
+#pragma unroll
+    for (int m = 32; m > 0; m >>= 1) {
+        rar += __shfl_xor(rar, m);
+        arar = arar + shfl_xor2(arar, m);
+        apar = apar + shfl_xor2(apar, m);
+    }
+    __syncthreads();  // the links have been read: sh lies on top of them
+    const int waves = (int)blockDim.x >> 6, wave = (int)threadIdx.x >> 6;
+    if ((threadIdx.x & 63) == 0) {
+        const double v[DOT_ROWS] = {rar, arar.hi, arar.lo, apar.hi, apar.lo};
+#pragma unroll
+        for (int q = 0; q < DOT_ROWS; ++q) sh[wave * DOT_ROWS + q] = v[q];
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < waves; ++w) {
+            const double* o = sh + w * DOT_ROWS;
+            rar += o[0];
+            arar = arar + Sum2{o[1], o[2]};
+            apar = apar + Sum2{o[3], o[4]};
+        }
+        const double v[DOT_ROWS] = {rar, arar.hi, arar.lo, apar.hi, apar.lo};
+#pragma unroll
+        for (int q = 0; q < DOT_ROWS; ++q) dt.part[(size_t)q * gridDim.x + blockIdx.x] = v[q];
+    }
+}
+
 // Tile kernel: Ls = LS divides WG; a workgroup holds WG / LS whole 4d sites.
 // NT: stores with the non-temporal hint (streamed past the L2); NY: epilogue terms.
 template <typename T, int LS, bool NT, int NY>
@@ -389,9 +446,9 @@ struct TileGeom {
     FineGeom t;  // the lattice of tiles (extents L / 2), traversal order of the tiles
 };
 
-template <typename T, int NY>
+template <typename T, int NY, bool DOTS = false>
 __global__ void __launch_bounds__(WG) dslash_par_kernel(FineGeom g, TileGeom tg, const C2<T>* U, const C2<T>* in,
-                                                        C2<T>* out, Epi<T> ep) {
+                                                        C2<T>* out, Epi<T> ep, DotOut dt) {
     constexpr int LS = 16;
     constexpr uint32_t CB = sizeof(C2<T>);
     __shared__ C2<T> spin[12 * 16 * LS];   // [c][pattern][s]
@@ -467,7 +524,12 @@ __global__ void __launch_bounds__(WG) dslash_par_kernel(FineGeom g, TileGeom tg,
     HDCR_PAR_HOPS(2)
     HDCR_PAR_HOPS(3)
 #undef HDCR_PAR_HOPS
-    store_out<T, NY, true, (sizeof(T) == 8)>(f, (uint32_t)(st.site * LS + (LS - 1 - s)) * CB, ep, acc);
+    const uint32_t oo = (uint32_t)(st.site * LS + (LS - 1 - s)) * CB;
+    if constexpr (DOTS)
+        store_out_dots(f, oo, dt, acc, [&](int c) { return spin[(c * 16 + p) * LS + (LS - 1 - s)]; },
+                       reinterpret_cast<double*>(lds));
+    else
+        store_out<T, NY, true, (sizeof(T) == 8)>(f, oo, ep, acc);
 }
 
 // Paired parity-tile kernel (FP32, Ls = 16): the tile scheme above with each
@@ -717,9 +779,9 @@ template <> struct SliceWord<float, 2> {
     }
 };
 
-template <typename T, int W, int LS, int NY>
+template <typename T, int W, int LS, int NY, bool DOTS = false>
 __global__ void __launch_bounds__(16 * LS / W) __attribute__((amdgpu_waves_per_eu(2)))
-dslash_ptile_kernel(FineGeom g, TileGeom tg, const C2<T>* U, const C2<T>* in, C2<T>* out, Epi<T> ep) {
+dslash_ptile_kernel(FineGeom g, TileGeom tg, const C2<T>* U, const C2<T>* in, C2<T>* out, Epi<T> ep, DotOut dt) {
     typedef SliceWord<T, W> Wd;
     typedef typename Wd::type Word;
     constexpr uint32_t CB = sizeof(C2<T>);
@@ -846,7 +908,10 @@ dslash_ptile_kernel(FineGeom g, TileGeom tg, const C2<T>* U, const C2<T>* in, C2
 #undef HDCR_PT_GATHER
     // slice s goes to Ls-1-s (a pair to the pair at Ls-2-s0, reversed)
     const uint32_t oo = (uint32_t)(st.site * LS + (LS - W - s0)) * CB;
-    if constexpr (W == 2)
+    if constexpr (DOTS)
+        store_out_dots(f, oo, dt, a[0], [&](int c) { return spin[(c * 16 + p) * NK + (LS - 1 - s0)]; },
+                       reinterpret_cast<double*>(lds));
+    else if constexpr (W == 2)
         store_pair<NY, false>(f, oo, ep, a[0], a[1]);
     else
         store_out<T, NY, true, (sizeof(T) == 8)>(f, oo, ep, a[0]);
@@ -1385,7 +1450,7 @@ bool launch_default(const FineGeom& g, const C2<T>* U, const C2<T>* in, C2<T>* o
                                ep);
         } else {
             const int pad = lds_pad(g, dslash_par_kernel<T, NY>);
-            hipLaunchKernelGGL((dslash_par_kernel<T, NY>), dim3(tg.t.V4), dim3(WG), pad, s, g, tg, U, in, out, ep);
+            hipLaunchKernelGGL((dslash_par_kernel<T, NY>), dim3(tg.t.V4), dim3(WG), pad, s, g, tg, U, in, out, ep, DotOut{});
         }
         return true;
     }
@@ -1393,7 +1458,7 @@ bool launch_default(const FineGeom& g, const C2<T>* U, const C2<T>* in, C2<T>* o
         const TileGeom tg = tile_geom(g);
         const int pad = lds_pad(g, dslash_ptile_kernel<T, W, 8, NY>);
         hipLaunchKernelGGL((dslash_ptile_kernel<T, W, 8, NY>), dim3(tg.t.V4), dim3(16 * 8 / W), pad, s, g, tg, U, in, out,
-                           ep);
+                           ep, DotOut{});
         return true;
     }
     if (sizeof(T) == 4 && g.Ls == 16) return false;
@@ -1411,7 +1476,7 @@ void launch_ny(const FineGeom& g, const C2<T>* U, const C2<T>* in, C2<T>* out, c
     if (g.variant == 4 && par_ok(g)) {
         const TileGeom tg = tile_geom(g);
         const int pad = lds_pad(g, dslash_par_kernel<T, NY>);
-        hipLaunchKernelGGL((dslash_par_kernel<T, NY>), dim3(tg.t.V4), dim3(WG), pad, s, g, tg, U, in, out, ep);
+        hipLaunchKernelGGL((dslash_par_kernel<T, NY>), dim3(tg.t.V4), dim3(WG), pad, s, g, tg, U, in, out, ep, DotOut{});
         return;
     }
     if (g.variant != 2) {
@@ -1429,6 +1494,24 @@ void launch_ny(const FineGeom& g, const C2<T>* U, const C2<T>* in, C2<T>* out, c
 template <typename T>
 void launch_dslash(const FineGeom& g, const C2<T>* U, const C2<T>* in, C2<T>* out, hipStream_t s) {
     launch_ny<T, 0>(g, U, in, out, Epi<T>{{nullptr, nullptr, nullptr, nullptr}, {0, 0, 0, 0}, (T)1, 0}, s);
+}
+
+int dslash_dots_blocks(const FineGeom& g) {
+    if (g.variant != 0 || !even_extents(g) || (g.Ls != 16 && g.Ls != 8)) return 0;
+    return g.V4 / 16;
+}
+
+void launch_dslash_dots(const FineGeom& g, const double2* U, const double2* in, double2* out, const double2* Ap,
+                        double* part, hipStream_t s) {
+    const TileGeom tg = tile_geom(g);
+    const Epi<double> none{{nullptr, nullptr, nullptr, nullptr}, {0, 0, 0, 0}, 1.0, 0};
+    const DotOut dt{Ap, part};
+    if (g.Ls == 16)
+        hipLaunchKernelGGL((dslash_par_kernel<double, 0, true>), dim3(tg.t.V4), dim3(WG),
+                           lds_pad(g, dslash_par_kernel<double, 0, true>), s, g, tg, U, in, out, none, dt);
+    else
+        hipLaunchKernelGGL((dslash_ptile_kernel<double, 1, 8, 0, true>), dim3(tg.t.V4), dim3(16 * 8),
+                           lds_pad(g, dslash_ptile_kernel<double, 1, 8, 0, true>), s, g, tg, U, in, out, none, dt);
 }
 
 template <typename T>

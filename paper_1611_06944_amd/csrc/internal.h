@@ -208,6 +208,15 @@ int check_ptr(const void* p, size_t align, const char* name);
 template <typename T>
 void launch_dslash(const FineGeom& g, const C2<T>* U, const C2<T>* in, C2<T>* out, hipStream_t s);
 
+// The FP64 apply out = H in with the inner products of a conjugate residual step:
+// part[q * nwg + w] = workgroup w's sums of Re<in,out> (q = 0), |out|^2 (hi, lo: 1,
+// 2) and Re<Ap,out> (hi, lo: 3, 4), nwg = dslash_dots_blocks(g) (0: no kernel of
+// this form for the lattice).
+constexpr int DOT_ROWS = 5;
+int dslash_dots_blocks(const FineGeom& g);
+void launch_dslash_dots(const FineGeom& g, const double2* U, const double2* in, double2* out, const double2* Ap,
+                        double* part, hipStream_t s);
+
 // Fused epilogue of a stencil launch: out = beta (H in) + sum_{i < ny} g[i] y[i]
 // (0 <= ny <= 4).  y[i] is read at the element the work-item writes, before the
 // write, so y[i] may be the output buffer itself; it must not be `in`.
@@ -291,6 +300,43 @@ __device__ __forceinline__ void block_reduce(double (&v)[NQ]) {
 #pragma unroll
     for (int q = 0; q < NQ; ++q) v[q] = sh[q][0];
 }
+
+// Sums carried as hi + lo, for inner products whose combination cancels: the
+// error terms of every product and sum are kept (TwoProduct by FMA and Knuth's
+// TwoSum), so a sum of n products is good to about n 2^-106 of the sum of their
+// magnitudes.  Free beside memory traffic: some ten operations per product.
+struct Sum2 {
+    double hi, lo;
+};
+// The compiler may otherwise contract a * b + c across the roundings that the
+// error terms are about.
+__device__ __forceinline__ double rounded(double v) {
+    asm("" : "+v"(v));
+    return v;
+}
+__device__ __forceinline__ Sum2 two_sum(double a, double b) {
+    const double s = rounded(a + b), t = rounded(s - a);
+    return {s, (a - rounded(s - t)) + (b - t)};
+}
+// s += a b
+__device__ __forceinline__ void add_product(Sum2& s, double a, double b) {
+    const double p = rounded(a * b), e = fma(a, b, -p);
+    const Sum2 t = two_sum(s.hi, p);
+    s.hi = t.hi;
+    s.lo += t.lo + e;
+}
+__device__ __forceinline__ Sum2 operator+(Sum2 a, Sum2 b) {
+    Sum2 t = two_sum(a.hi, b.hi);
+    t.lo += a.lo + b.lo;
+    return t;
+}
+// a + b x, and the value as one double
+__device__ __forceinline__ Sum2 add_scaled(Sum2 a, double x, Sum2 b) {
+    add_product(a, x, b.hi);
+    a.lo += x * b.lo;
+    return a;
+}
+__device__ __forceinline__ Sum2 shfl_xor2(Sum2 v, int m) { return {__shfl_xor(v.hi, m), __shfl_xor(v.lo, m)}; }
 
 template <typename T>
 void launch_dot(int64_t n, const C2<T>* x, const C2<T>* y, double2* partials, double2* result, hipStream_t s);

@@ -35,7 +35,9 @@ enum { S_RR0 = 0,    // |r|^2 of the residual the iteration starts from
        S_RAR = 2,    // Re<r,Ar> of the even (2) and odd (3) steps
        S_ALPHA = 4,  // alpha of the even (4) and odd (5) steps
        S_HIST = 6 }; // |r|^2 after each step of the batch
+constexpr int CR_BLOCKS = 512;  // most workgroups of the update: each of them adds up the others' partials
 constexpr int CR_BATCH = 32;  // most steps between two read-backs
+constexpr int CR_COMPRESS = 32;  // workgroups that sum the apply's own partials
 constexpr int S_COUNT = S_HIST + CR_BATCH;
 // flags: stop reason and completed steps since the start
 enum { CR_RUN = 0, CR_CONVERGED = 1, CR_BREAKDOWN = 2, CR_NAN = 3 };
@@ -68,13 +70,65 @@ template <int NQ> __device__ __forceinline__ void wg_sums(double (&v)[NQ]) {
     }
 }
 
-// v[q0 + q] = sum of row q of the partials (np per row), for NQ rows
-template <int NQ, int N>
-__device__ __forceinline__ void add_partials(const double* __restrict__ part, int np, int q0, double (&v)[N]) {
-#pragma unroll 4
-    for (int i = threadIdx.x; i < np; i += REDUCE_THREADS) {
+// Columns i, i + REDUCE_THREADS, ... of ROWS rows of np partials, four at a time,
+// zeros past the end: every load is issued before the first is used (the sums
+// with error terms keep the compiler from unrolling the loop over them).
+template <int ROWS>
+__device__ __forceinline__ void load_partials(const double* __restrict__ part, int np, int i, double (&o)[ROWS][4]) {
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) v[q0 + q] += part[(size_t)q * np + i];
+    for (int r = 0; r < ROWS; ++r)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int k = i + u * REDUCE_THREADS;
+            const double v = part[(size_t)r * np + (k < np ? k : 0)];
+            o[r][u] = k < np ? v : 0.0;
+        }
+}
+// v[q] = sums of NQ rows of partials
+template <int NQ> __device__ __forceinline__ void add_partials(const double* __restrict__ part, int np, double (&v)[NQ]) {
+    for (int i = threadIdx.x; i < np; i += 4 * REDUCE_THREADS) {
+        double o[NQ][4];
+        load_partials<NQ>(part, np, i, o);
+#pragma unroll
+        for (int q = 0; q < NQ; ++q)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[q] += o[q][u];
+    }
+}
+
+// the same for a sum with its error terms; NS of them from NS row pairs (hi, lo)
+template <int NS> __device__ __forceinline__ void wg_sums2(Sum2 (&v)[NS]) {
+    constexpr int WAVES = REDUCE_THREADS / 64;
+    __shared__ Sum2 sh[NS][WAVES];
+#pragma unroll
+    for (int q = 0; q < NS; ++q)
+#pragma unroll
+        for (int m = 32; m > 0; m >>= 1) v[q] = v[q] + shfl_xor2(v[q], m);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) {
+#pragma unroll
+        for (int q = 0; q < NS; ++q) sh[q][threadIdx.x >> 6] = v[q];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < NS; ++q) {
+        v[q] = sh[q][0];
+#pragma unroll
+        for (int w = 1; w < WAVES; ++w) v[q] = v[q] + sh[q][w];
+    }
+}
+// v += row 0, q[k] += rows 1 + 2 k (hi) and 2 + 2 k (lo) of the partials
+template <int NS>
+__device__ __forceinline__ void add_rows(const double* __restrict__ part, int np, double& v, Sum2* q) {
+    for (int i = threadIdx.x; i < np; i += 4 * REDUCE_THREADS) {
+        double o[1 + 2 * NS][4];
+        load_partials<1 + 2 * NS>(part, np, i, o);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            v += o[0][u];
+#pragma unroll
+            for (int k = 0; k < NS; ++k) q[k] = q[k] + Sum2{o[1 + 2 * k][u], o[2 + 2 * k][u]};
+        }
     }
 }
 
@@ -84,13 +138,14 @@ __device__ __forceinline__ int cr_stop(double rr, double tol2) {
 }
 
 // Step `step` (1, 2, ... since the start), after Ar = H r and its inner products
-// (dpart: rows <r,Ar>, |Ar|^2, Re<Ap,Ar> of ndot partials):
+// (dpart: DOT_ROWS rows of ndot partials):
 //   p = r + beta p, Ap = Ar + beta Ap, r -= alpha Ap  (step 1: p = r, Ap = Ar),
 // every second step x += alpha_old p_old + alpha p.  uin / uout: partials of |r|^2
-// and |Ap|^2 of the previous and of this step.  slot: place of the previous
+// and |Ap|^2 (hi, lo) of the previous and of this step.  slot: place of the previous
 // step's |r|^2 in the batch's history, or -1.
-// Bound by the 8 or 10 vectors it streams; 256 x 1024 work-items with two
-// elements each in flight.
+// Bound by the 8 or 10 vectors it streams, and on small lattices by the start:
+// 512 workgroups with three elements in flight per work-item take 39.6 us a step at
+// 8^4 x 16 with the apply, 1024 with two 43.2, 256 with four 39.1.
 template <bool FIRST, bool XUP>
 __global__ void __launch_bounds__(REDUCE_THREADS) cr_step_kernel(int64_t n, double2* __restrict__ x,
                                                                  double2* __restrict__ r, double2* __restrict__ p,
@@ -100,11 +155,13 @@ __global__ void __launch_bounds__(REDUCE_THREADS) cr_step_kernel(int64_t n, doub
                                                                  int slot, double tol) {
     if (st->reason != CR_RUN) return;
     const bool lead = blockIdx.x == 0 && threadIdx.x == 0;
-    double t[5] = {0, 0, 0, 0, 0};
-    add_partials<3>(dpart, ndot, 0, t);
-    if constexpr (!FIRST) add_partials<2>(uin, (int)gridDim.x, 3, t);
-    wg_sums<5>(t);
-    const double rr = FIRST ? st->S[S_RR0] : t[3];
+    double t[2] = {0.0, 0.0};                     // <r,Ar>, |r|^2
+    Sum2 q[3] = {{0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}};  // |Ar|^2, Re<Ap,Ar>, |Ap|^2 of the old Ap
+    add_rows<2>(dpart, ndot, t[0], q);
+    if constexpr (!FIRST) add_rows<1>(uin, (int)gridDim.x, t[1], q + 2);
+    wg_sums<2>(t);
+    wg_sums2<3>(q);
+    const double rr = FIRST ? st->S[S_RR0] : t[1], arar = q[0].hi + q[0].lo;
     if constexpr (!FIRST) {
         const int stop = cr_stop(rr, tol * tol * st->S[S_BB]);
         if (lead && slot >= 0) st->S[S_HIST + slot] = rr;
@@ -115,14 +172,16 @@ __global__ void __launch_bounds__(REDUCE_THREADS) cr_step_kernel(int64_t n, doub
     }
     const double rar = t[0];
     // (near-)breakdown: <r,Ar> at rounding level of |r||Ar|
-    if (!(fabs(rar) >= 1e-13 * sqrt(rr) * sqrt(t[1]))) {
+    if (!(fabs(rar) >= 1e-13 * sqrt(rr) * sqrt(arar))) {
         if (lead) st->reason = isfinite(rar) ? CR_BREAKDOWN : CR_NAN;
         return;
     }
     const double beta = FIRST ? 0.0 : rar / st->S[S_RAR + ((step - 1) & 1)];
-    const double apap = FIRST ? t[1] : t[1] + 2.0 * beta * t[2] + beta * beta * t[4];
+    const Sum2 e = add_scaled(add_scaled(q[0], 2.0 * beta, q[1]), beta, add_scaled(Sum2{0.0, 0.0}, beta, q[2]));
+    const double apap = FIRST ? arar : e.hi + e.lo;
     const double alpha = rar / apap, aold = XUP ? st->S[S_ALPHA + ((step - 1) & 1)] : 0.0;
-    double v[2] = {0.0, 0.0};
+    double v[1] = {0.0};
+    Sum2 an[1] = {{0.0, 0.0}};
     const int64_t stride = (int64_t)gridDim.x * REDUCE_THREADS;
     auto element = [&](int64_t i, double2 ri, double2 ari, double2 po, double2 apo, double2 xi) {
         double2 pi = ri, api = ari;
@@ -143,9 +202,10 @@ __global__ void __launch_bounds__(REDUCE_THREADS) cr_step_kernel(int64_t n, doub
         Ap[i] = api;
         r[i] = ri;
         v[0] += ri.x * ri.x + ri.y * ri.y;
-        v[1] += api.x * api.x + api.y * api.y;
+        add_product(an[0], api.x, api.x);
+        add_product(an[0], api.y, api.y);
     };
-    constexpr int U = 2;
+    constexpr int U = 3;
     int64_t i = (int64_t)blockIdx.x * REDUCE_THREADS + threadIdx.x;
     for (; i + (U - 1) * stride < n; i += U * stride) {
         double2 a[U], b[U], c[U], d[U], e[U];
@@ -163,10 +223,12 @@ __global__ void __launch_bounds__(REDUCE_THREADS) cr_step_kernel(int64_t n, doub
     for (; i < n; i += stride)
         element(i, r[i], Ar[i], FIRST ? make_double2(0, 0) : p[i], FIRST ? make_double2(0, 0) : Ap[i],
                 XUP ? x[i] : make_double2(0, 0));
-    wg_sums<2>(v);
+    wg_sums<1>(v);
+    wg_sums2<1>(an);
     if (threadIdx.x == 0) {
         uout[blockIdx.x] = v[0];
-        uout[gridDim.x + blockIdx.x] = v[1];
+        uout[gridDim.x + blockIdx.x] = an[0].hi;
+        uout[2 * gridDim.x + blockIdx.x] = an[0].lo;
     }
     if (lead) {
         st->S[S_RAR + (step & 1)] = rar;
@@ -180,7 +242,7 @@ __global__ void __launch_bounds__(REDUCE_THREADS) cr_check_kernel(const double* 
                                                                   int slot, double tol) {
     if (st->reason != CR_RUN || st->steps != step) return;
     double t[1] = {0.0};
-    add_partials<1>(uin, nu, 0, t);
+    add_partials<1>(uin, nu, t);
     wg_sums<1>(t);
     if (threadIdx.x == 0) {
         st->S[S_HIST + slot] = t[0];
@@ -202,7 +264,35 @@ __global__ void __launch_bounds__(REDUCE_THREADS) cr_flush_kernel(int64_t n, dou
     }
 }
 
-// partials of Re<r,Ar>, |Ar|^2 and (Ap not null) Re<Ap,Ar>
+// the workgroup's sums to its column of DOT_ROWS rows
+__device__ __forceinline__ void store_dots(double* __restrict__ part, double (&v)[1], Sum2 (&q)[2]) {
+    wg_sums<1>(v);
+    wg_sums2<2>(q);
+    if (threadIdx.x == 0) {
+        const double o[DOT_ROWS] = {v[0], q[0].hi, q[0].lo, q[1].hi, q[1].lo};
+#pragma unroll
+        for (int r = 0; r < DOT_ROWS; ++r) part[(size_t)r * gridDim.x + blockIdx.x] = o[r];
+    }
+}
+
+// The apply's own partials (nin columns) summed into gridDim.x columns: a large
+// lattice has more of them than every workgroup of the update can add up.
+__global__ void __launch_bounds__(REDUCE_THREADS) cr_compress_kernel(const double* __restrict__ in, int nin,
+                                                                     const CrState* __restrict__ st,
+                                                                     double* __restrict__ out) {
+    if (st->reason != CR_RUN) return;
+    double v[1] = {0.0};
+    Sum2 q[2] = {{0.0, 0.0}, {0.0, 0.0}};
+    for (int i = blockIdx.x * REDUCE_THREADS + threadIdx.x; i < nin; i += gridDim.x * REDUCE_THREADS) {
+        v[0] += in[i];
+#pragma unroll
+        for (int r = 0; r < 2; ++r)
+            q[r] = q[r] + Sum2{in[(size_t)(1 + 2 * r) * nin + i], in[(size_t)(2 + 2 * r) * nin + i]};
+    }
+    store_dots(out, v, q);
+}
+
+// the inner products in a pass of their own, for the applies that do not take them
 template <bool FIRST>
 __global__ void __launch_bounds__(REDUCE_THREADS) cr_dots_kernel(int64_t n, const double2* __restrict__ r,
                                                                  const double2* __restrict__ Ar,
@@ -210,23 +300,28 @@ __global__ void __launch_bounds__(REDUCE_THREADS) cr_dots_kernel(int64_t n, cons
                                                                  const CrState* __restrict__ st,
                                                                  double* __restrict__ dpart) {
     if (st->reason != CR_RUN) return;
-    double v[3] = {0.0, 0.0, 0.0};
+    double v[1] = {0.0};
+    Sum2 q[2] = {{0.0, 0.0}, {0.0, 0.0}};
     const int64_t stride = (int64_t)gridDim.x * REDUCE_THREADS;
-#pragma unroll 2
-    for (int64_t i = (int64_t)blockIdx.x * REDUCE_THREADS + threadIdx.x; i < n; i += stride) {
-        const double2 a = r[i], b = Ar[i];
+    auto element = [&](double2 a, double2 b, double2 c) {
         v[0] += a.x * b.x + a.y * b.y;
-        v[1] += b.x * b.x + b.y * b.y;
+        add_product(q[0], b.x, b.x);
+        add_product(q[0], b.y, b.y);
         if constexpr (!FIRST) {
-            const double2 c = Ap[i];
-            v[2] += c.x * b.x + c.y * b.y;
+            add_product(q[1], c.x, b.x);
+            add_product(q[1], c.y, b.y);
         }
+    };
+    const double2 zero = make_double2(0, 0);
+    int64_t i = (int64_t)blockIdx.x * REDUCE_THREADS + threadIdx.x;
+    for (; i + stride < n; i += 2 * stride) {
+        const double2 a0 = r[i], b0 = Ar[i], c0 = FIRST ? zero : Ap[i];
+        const double2 a1 = r[i + stride], b1 = Ar[i + stride], c1 = FIRST ? zero : Ap[i + stride];
+        element(a0, b0, c0);
+        element(a1, b1, c1);
     }
-    wg_sums<3>(v);
-    if (threadIdx.x == 0) {
-#pragma unroll
-        for (int q = 0; q < 3; ++q) dpart[(size_t)q * gridDim.x + blockIdx.x] = v[q];
-    }
+    if (i < n) element(r[i], Ar[i], FIRST ? zero : Ap[i]);
+    store_dots(dpart, v, q);
 }
 
 // r = b - Hx; partial |r|^2 (row 0) and |b|^2 (row 1)
@@ -254,7 +349,7 @@ __global__ void __launch_bounds__(REDUCE_THREADS) residual_kernel(int64_t n, con
 // start of the iteration: |r|^2 and |b|^2 from residual_kernel, flags cleared
 __global__ void __launch_bounds__(REDUCE_THREADS) cr_start_kernel(const double* part, int np, CrState* st) {
     double t[2] = {0.0, 0.0};
-    add_partials<2>(part, np, 0, t);
+    add_partials<2>(part, np, t);
     wg_sums<2>(t);
     if (threadIdx.x == 0) {
         st->S[S_RR0] = t[0];
@@ -266,18 +361,22 @@ __global__ void __launch_bounds__(REDUCE_THREADS) cr_start_kernel(const double* 
 
 struct CrBuffers {
     double2 *r, *p, *Ar, *Ap;
-    double* dpart;     // 3 rows
-    double* upart[2];  // 2 rows each
+    double* dpart;     // DOT_ROWS rows
+    double* apart;     // the same of the apply's own partials, where there are more than REDUCE_BLOCKS
+    double* upart[2];  // 3 rows each
     CrState* st;
 };
-CrBuffers cr_carve(Carver& c, int64_t n) {
+CrBuffers cr_carve(Carver& c, const FineGeom& g) {
+    const size_t n = (size_t)12 * g.N5;
     CrBuffers w;
     w.r = c.take<double2>(n);
     w.p = c.take<double2>(n);
     w.Ar = c.take<double2>(n);
     w.Ap = c.take<double2>(n);
-    w.dpart = c.take<double>(3 * REDUCE_BLOCKS);
-    for (int i = 0; i < 2; ++i) w.upart[i] = c.take<double>(2 * REDUCE_BLOCKS);
+    w.dpart = c.take<double>(DOT_ROWS * REDUCE_BLOCKS);
+    const int nd = dslash_dots_blocks(g);
+    w.apart = c.take<double>(nd > REDUCE_BLOCKS ? (size_t)DOT_ROWS * nd : 0);
+    for (int i = 0; i < 2; ++i) w.upart[i] = c.take<double>(3 * CR_BLOCKS);
     w.st = c.take<CrState>(1);
     return w;
 }
@@ -286,7 +385,7 @@ CrBuffers cr_carve(Carver& c, int64_t n) {
 
 size_t cr_workspace_bytes(const FineGeom& g) {
     Carver c(nullptr, 0);
-    cr_carve(c, 12LL * g.N5);
+    cr_carve(c, g);
     return c.used();
 }
 
@@ -295,13 +394,14 @@ int cr_solve(const FineGeom& g, const hdcr_solve_params* prm, const double2* U, 
     const auto t0 = std::chrono::steady_clock::now();
     const int64_t n = 12LL * g.N5;
     Carver c(work, work_bytes);
-    const CrBuffers w = cr_carve(c, n);
+    const CrBuffers w = cr_carve(c, g);
     if (!c.ok()) return fail(HDCR_ENOMEM, "hdcr_solve: workspace too small for CR");
 
-    // two or more elements per work-item, at most REDUCE_BLOCKS workgroups
-    const int64_t want = (n + 2 * REDUCE_THREADS - 1) / (2 * REDUCE_THREADS);
-    const int nwg = (int)std::min<int64_t>(want < 1 ? 1 : want, REDUCE_BLOCKS);
+    // three or more elements per work-item, at most CR_BLOCKS workgroups
+    const int64_t want = (n + 3 * REDUCE_THREADS - 1) / (3 * REDUCE_THREADS);
+    const int nwg = (int)std::min<int64_t>(want < 1 ? 1 : want, CR_BLOCKS);
     const dim3 rg(nwg), rt(REDUCE_THREADS);
+    const int ndots = dslash_dots_blocks(g);  // partials of the apply that takes the inner products with it
     CrState h;
     auto read = [&]() -> hipError_t {
         hipError_t e = hipMemcpyAsync(&h, w.st, sizeof(h), hipMemcpyDeviceToHost, s);
@@ -339,46 +439,56 @@ int cr_solve(const FineGeom& g, const hdcr_solve_params* prm, const double2* U, 
     while (status == HDCR_ENOTCONV && it < prm->maxiter) {
         // steps from the residual in r, in batches
         int step = 0, reason = CR_RUN, batch = 8;
+        const int nd = ndots > REDUCE_BLOCKS ? CR_COMPRESS : (ndots > 0 ? ndots : nwg);  // rows of dpart past step 1
         ++napply;  // the first step's apply
         while (reason == CR_RUN && it < prm->maxiter) {
+            const int done = step;
             const int nb = std::min(batch, prm->maxiter - it);
-            const int first = step + 1;
             for (int k = 0; k < nb; ++k) {
                 ++step;
                 const double* uin = w.upart[(step - 1) & 1];
                 double* uout = w.upart[step & 1];
                 const int slot = k > 0 ? k - 1 : -1;
-                launch_dslash<double>(g, U, w.r, w.Ar, s);
 #define HDCR_CR_STEP(F, XU)                                                                                        \
     hipLaunchKernelGGL((cr_step_kernel<F, XU>), rg, rt, 0, s, n, x, w.r, w.p, (const double2*)w.Ar, w.Ap,          \
-                       (const double*)w.dpart, nwg, uin, uout, w.st, step, slot, prm->tol)
+                   (const double*)w.dpart, step == 1 ? nwg : nd, uin, uout, w.st, step, slot, prm->tol)
                 if (step == 1) {
+                    launch_dslash<double>(g, U, w.r, w.Ar, s);
                     hipLaunchKernelGGL(cr_dots_kernel<true>, rg, rt, 0, s, n, w.r, w.Ar, w.Ap, w.st, w.dpart);
                     HDCR_CR_STEP(true, false);
-                } else {
-                    hipLaunchKernelGGL(cr_dots_kernel<false>, rg, rt, 0, s, n, w.r, w.Ar, w.Ap, w.st, w.dpart);
-                    if (step % 2 == 0)
-                        HDCR_CR_STEP(false, true);
-                    else
-                        HDCR_CR_STEP(false, false);
+                    continue;
                 }
+                if (ndots > REDUCE_BLOCKS) {
+                    launch_dslash_dots(g, U, w.r, w.Ar, w.Ap, w.apart, s);
+                    hipLaunchKernelGGL(cr_compress_kernel, dim3(CR_COMPRESS), rt, 0, s, (const double*)w.apart, ndots,
+                                       w.st, w.dpart);
+                } else if (ndots > 0) {
+                    launch_dslash_dots(g, U, w.r, w.Ar, w.Ap, w.dpart, s);
+                } else {
+                    launch_dslash<double>(g, U, w.r, w.Ar, s);
+                    hipLaunchKernelGGL(cr_dots_kernel<false>, rg, rt, 0, s, n, w.r, w.Ar, w.Ap, w.st, w.dpart);
+                }
+                if (step % 2 == 0)
+                    HDCR_CR_STEP(false, true);
+                else
+                    HDCR_CR_STEP(false, false);
 #undef HDCR_CR_STEP
             }
             hipLaunchKernelGGL(cr_check_kernel, dim3(1), rt, 0, s, (const double*)w.upart[step & 1], nwg, w.st, step,
                                nb - 1, prm->tol);
             HDCR_HIP_CHECK(read());
             reason = h.reason;
-            const int did = h.steps - (first - 1);  // steps of this batch that were taken
+            step = h.steps;
+            const int did = step - done;
             for (int k = 0; k < did; ++k)
                 if (history && hl < hcap) history[hl++] = std::sqrt(h.S[S_HIST + k] / bb);
             const double before = rr;
             if (did > 0) rr = h.S[S_HIST + did - 1];
             it += did;
             napply += did;
-            step = h.steps;
             // the next batch: half the steps that this batch's rate predicts
             batch = CR_BATCH;
-            if (reason == CR_RUN && did > 0 && rr < before) {
+            if (did > 0 && rr < before) {
                 const double left = std::log(rr / tol2) / std::log(before / rr) * did;
                 if (left < 2.0 * CR_BATCH) batch = std::max(4, (int)(0.5 * left));
             }
