@@ -52,18 +52,10 @@ CoarseGeom make_coarse_geom(const hdcr_coarse_desc* d) {
     return c;
 }
 
-// columns of A built per pass of the class-split stencil
-// columns per projection launch: at most 4 (one per wavefront of the projection work-group)
-static int build_chunk(const CoarseGeom& c) { return c.Nb < 4 ? c.Nb : 4; }
-
 size_t build_workspace_bytes(const CoarseGeom& c) {
     Carver w(nullptr, 0);
-    const size_t fsz = (size_t)12 * c.f.N5;
-    const int kc = build_chunk(c);
-    w.take<double2>(fsz * kc);          // expanded basis fields
-    w.take<double2>(fsz * kc * 9);      // class-split images
     w.take<double2>(coarse_elems(c));   // A in FP64
-    w.take<double2>(coarse_project_scratch_elems(c));  // projection partial sums
+    w.take<double2>(coarse_build_scratch_elems(c));  // partial sums of its class 0
     w.take<int>(64);                    // flags of the orthonormalisation
     w.take<double2>(chq_scratch_elems(c));  // Gram matrices and R^-1 of the Cholesky QR
     return w.used();
@@ -136,13 +128,9 @@ int hdcr_build_coarse(const hdcr_coarse_desc* desc, const void* U, const void* v
         return e;
     const CoarseGeom c = make_coarse_geom(desc);
     if (work_bytes < build_workspace_bytes(c)) return fail(HDCR_ENOMEM, "hdcr_build_coarse: workspace too small");
-    const size_t fsz = (size_t)12 * c.f.N5;
-    const int kc = build_chunk(c);
     Carver w(work, work_bytes);
-    double2* X = w.take<double2>(fsz * kc);
-    double2* Y = w.take<double2>(fsz * kc * 9);
     double2* A64 = w.take<double2>(coarse_elems(c));
-    double2* Pp = w.take<double2>(coarse_project_scratch_elems(c));
+    double2* Pp = w.take<double2>(coarse_build_scratch_elems(c));
     int* flag = w.take<int>(64);
     double2* chq = w.take<double2>(chq_scratch_elems(c));
     double2* b64 = basis64(basis);
@@ -168,17 +156,9 @@ int hdcr_build_coarse(const hdcr_coarse_desc* desc, const void* U, const void* v
     launch_basis_to_f32(c, b64, basis32(c, basis), stream);
     launch_basis_to_f16(c, b64, basis16(c, basis), stream);
     HDCR_HIP_CHECK(hipGetLastError());
-    // A = P^dag H P, kc columns at a time
-    double2* Adst = (A_dtype == HDCR_C128) ? static_cast<double2*>(A) : A64;
-    const double2* U64 = static_cast<const double2*>(U);
-    for (int k0 = 0; k0 < c.Nb; k0 += kc) {
-        const int nk = (c.Nb - k0 < kc) ? c.Nb - k0 : kc;
-        launch_basis_expand(c, b64, k0, nk, X, stream);
-        for (int kk = 0; kk < nk; ++kk)
-            launch_dslash_classes(c, U64, X + kk * fsz, Y + kk * 9 * fsz, fsz, stream);
-        launch_coarse_project(c, b64, Y, k0, nk, Pp, Adst, stream);
-        HDCR_HIP_CHECK(hipGetLastError());
-    }
+    // A = P^dag H P
+    launch_coarse_build(c, b64, static_cast<const double2*>(U), Pp,
+                        (A_dtype == HDCR_C128) ? static_cast<double2*>(A) : A64, stream);
     if (A_dtype != HDCR_C128) launch_coarse_convert(c, A64, A_dtype, A, stream);
     HDCR_HIP_CHECK(hipGetLastError());
     int hflag[3] = {0, 0, 0};

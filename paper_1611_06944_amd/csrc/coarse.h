@@ -163,19 +163,13 @@ template <typename T>
 void launch_ccr_step(const CoarseGeom& c, hdcr_dtype A_dtype, const void* A, C2<T>* x, const CoarseCRWork<T>& w,
                      int step, hipStream_t s);
 
-// little Dirac operator build: A64[a][d][k][j] for basis vectors in [k0, k0+nk),
-// nk <= 4, given the class-split fine fields Y[(kk*9 + d)] = H^(d) Phi_{k0+kk}
-// (read only on the sites of class d); P: coarse_project_scratch_elems() of
+// little Dirac operator A64[a][d][k][j] from the block basis and the links: d = 0:
+// diagonal, fifth dimension and hops inside a block, d = 1+mu / 5+mu: the forward /
+// backward mu hop that crosses the block face.  P: coarse_build_scratch_elems() of
 // partial sums
-size_t coarse_project_scratch_elems(const CoarseGeom& c);
-void launch_coarse_project(const CoarseGeom& c, const double2* b64, const double2* Y, int k0, int nk, double2* P,
-                           double2* A64, hipStream_t s);
-// The nine hop classes of H in: out + d * fstride = H^(d) in, d = 0: diagonal,
-// fifth dimension and hops inside a block, at every site; d = 1+mu / 5+mu: the
-// forward / backward mu hop that crosses the block face, written only at the
-// sites on that face (the other entries of those fields are left as they were)
-void launch_dslash_classes(const CoarseGeom& c, const double2* U, const double2* in, double2* out, size_t fstride,
-                           hipStream_t s);
+size_t coarse_build_scratch_elems(const CoarseGeom& c);
+void launch_coarse_build(const CoarseGeom& c, const double2* b64, const double2* U, double2* P, double2* A64,
+                         hipStream_t s);
 // A64 (column-major) -> other storage
 void launch_coarse_convert(const CoarseGeom& c, const double2* A64, hdcr_dtype dt, void* dst, hipStream_t s);
 // any storage -> logical A[a][d][j][k] complex double

@@ -1125,122 +1125,308 @@ void ccr_apply_dispatch(const CoarseGeom& c, hdcr_dtype dt, const void* A, const
 }
 
 // ---------------------------------------------------------------------------
-// coarse build: projection of the class-split fields onto the block basis
+// little Dirac operator build on the FP64 matrix cores
 // ---------------------------------------------------------------------------
+//
+// A[a][d][j][k] = <phi^a_j | H^(d) | phi^{a+d}_k>, images and projection in one
+// kernel: no image of a basis vector is ever stored.
+//
+// H is Hermitian, so only half of it is formed: A[a][5+mu] is the adjoint of
+// A[a-mu][1+mu], and A[a][0] = M + M^dag with M the interior forward hops and half of
+// the diagonal and fifth-dimension terms (build_finish_kernel).
+//
+// A column is an eigenvector of Gamma5 = gamma5 R5 with eigenvalue sigma, so its
+// image splits over the row chiralities by itself.  With b the stored half (s <
+// Ls/2), V = U_mu(x) b(x + mu) and c the hop coefficient, a forward hop (1 - g_mu) U
+// contributes
+//   sigma c V          to the rows of chirality sigma,
+//   sigma c g_mu V     to the rows of chirality -sigma,
+// on the stored slices alone; the diagonal and fifth-dimension terms split the
+// same way (local_terms below).
+//
+// A wavefront owns 16 columns and the rows of one chirality, and walks the sites of
+// a class (class 0: a part of the block's sites; class 1 + mu: the sites of that
+// face, with the one hop that crosses it), four stored slices at a time: lane (q, c)
+// forms the image X of column c at slice 4 sq + q for its row chirality, which is the
+// B operand of the 16 x 16 x 4 product as it stands (k = q, n = c).  The A operand
+// (k = q, m = row) is the rows' conjugates at the same site and slices, staged in LDS
+// for the workgroup.  re: br Xr + bi Xi, im: br Xi - bi Xr, so four products per
+// component and row tile.  The site is the same for the whole workgroup, so the links
+// come through the scalar unit.
+//
+// Bound by the latency of the hops' loads at three wavefronts per SIMD (waiting 87% of
+// the time; the matrix cores need 4 ms of 17.6 at 16^4 x 16, nvec = 24, 4^4 blocks): a
+// block's columns are 19 MB there, so a site's neighbours come from memory again.
+// Images of all basis vectors in memory and two dot-product kernels took 62 ms; the
+// whole H on the matrix cores 24; both row chiralities in one wavefront, two per SIMD,
+// the same.
+typedef double f64x4 __attribute__((ext_vector_type(4)));
 
-constexpr int PROJ_NK = 4;     // basis vectors (columns) per launch: one per wavefront of the work-group
-constexpr int PROJ_ROWS = 64;  // basis rows per work-group
-constexpr int PROJ_CHUNK = 16; // compressed indices of the block staged per step
-constexpr int PROJ_PARTS = 4;  // work-groups splitting one block's indices
+__device__ __forceinline__ f64x4 mfma64(double a, double b, f64x4 c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
 
-// grid (Nc, ceil(Nb / 64), PROJ_PARTS): the work-group sums conj(phi^a_j) . (H^(d) Phi_k)
-// for all nine classes d, 64 rows j and nk <= 4 columns kk over part blockIdx.z of
-// block a's compressed indices, and writes the partial sums to
-// P[((part * Nc + a) * 9 + d) * PROJ_NK + kk][j].  One pass over the indices
-// serves all classes: class 0 takes every site, the face classes only the sites
-// on their face (a per-index test, the same for the whole work-group), so every
-// basis entry is read once per launch.  Chunks of the 64 basis rows are staged
-// in LDS with coalesced loads.
-__global__ void __launch_bounds__(CWG) coarse_project_kernel(CoarseGeom c, const double2* __restrict__ b64,
-                                                             const double2* __restrict__ Y, int nk,
-                                                             double2* __restrict__ P) {
-    __shared__ double2 F[2][PROJ_NK][9][PROJ_CHUNK];  // chiral folds of the class fields
-    __shared__ double2 Bs[PROJ_ROWS][PROJ_CHUNK + 1];  // basis rows of the chunk
-    __shared__ int mask[PROJ_CHUNK];                  // classes of each staged index
-    const int a = blockIdx.x;
-    const int j0 = blockIdx.y * PROJ_ROWS;
-    const int ntot = 12 * c.bvol * c.Lh;
-    // this part's index range, in whole chunks
-    const int nchunk = (ntot + PROJ_CHUNK - 1) / PROJ_CHUNK;
-    const int cb = (int)(((long long)nchunk * blockIdx.z) / gridDim.z);
-    const int ce = (int)(((long long)nchunk * (blockIdx.z + 1)) / gridDim.z);
-    const int nidx = min(ntot, ce * PROJ_CHUNK);
-    const size_t fsz = (size_t)12 * c.f.N5;
-    const int jl = threadIdx.x % PROJ_ROWS, kk = threadIdx.x / PROJ_ROWS;
-    const int j = j0 + jl;
-    const int h = (j < c.nvec) ? 0 : 1;
-    double2 acc[9];
-#pragma unroll
-    for (int d = 0; d < 9; ++d) acc[d] = make_double2(0, 0);
-    for (int i0 = cb * PROJ_CHUNK; i0 < nidx; i0 += PROJ_CHUNK) {
-        // classes of the staged indices: 0, and the faces the site lies on
-        if (threadIdx.x < PROJ_CHUNK) {
-            const int idx = i0 + threadIdx.x;
-            int m = 0;
-            if (idx < nidx) {
-                int f = (idx / c.Lh) % c.bvol;
-                m = 1;
-#pragma unroll
-                for (int mu = 0; mu < 4; ++mu) {
-                    const int x = f % c.B[mu];
-                    f /= c.B[mu];
-                    if (x == c.B[mu] - 1) m |= 1 << (1 + mu);
-                    if (x == 0) m |= 1 << (5 + mu);
-                }
-            }
-            mask[threadIdx.x] = m;
-        }
-        // basis rows: 64 rows x 16 consecutive indices, one 256-byte run per row
-        for (int e = threadIdx.x; e < PROJ_ROWS * PROJ_CHUNK; e += CWG) {
-            const int r = e / PROJ_CHUNK, ii = e % PROJ_CHUNK;
-            const int jr = j0 + r, idx = i0 + ii;
-            double2 v = make_double2(0, 0);
-            if (jr < c.Nb && idx < nidx) {
-                const int hr = (jr < c.nvec) ? 0 : 1;
-                v = b64[(((size_t)a * 2 + hr) * c.nvec + (jr - hr * c.nvec)) * c.nhalf + idx];
-            }
-            Bs[r][ii] = v;
-        }
-        __syncthreads();
-        // folds of the class fields at the staged indices (only the classes present)
-        for (int e = threadIdx.x; e < nk * 9 * PROJ_CHUNK; e += CWG) {
-            const int ii = e % PROJ_CHUNK, dk = e / PROJ_CHUNK;
-            const int d = dk % 9, q = dk / 9;
-            const int idx = i0 + ii;
-            if (idx >= nidx || !((mask[ii] >> d) & 1)) continue;
-            const int s = idx % c.Lh;
-            const int f = (idx / c.Lh) % c.bvol;
-            const int comp = idx / (c.Lh * c.bvol);
-            const int site = block_site(c, a, f);
-            const size_t fb = (((size_t)q * 9 + d) * fsz) + ((size_t)comp * c.f.V4 + site) * c.f.Ls;
-            const double2 p1 = Y[fb + s], p2 = Y[fb + c.f.Ls - 1 - s];
-            const double g = (comp < 6) ? 1.0 : -1.0;
-            F[0][q][d][ii] = make_double2((p1.x + g * p2.x) * RSQRT2, (p1.y + g * p2.y) * RSQRT2);
-            F[1][q][d][ii] = make_double2((p1.x - g * p2.x) * RSQRT2, (p1.y - g * p2.y) * RSQRT2);
-        }
-        __syncthreads();
-        if (j < c.Nb && kk < nk) {
-            const int iend = min(PROJ_CHUNK, nidx - i0);
-            for (int ii = 0; ii < iend; ++ii) {
-                const double2 bv = Bs[jl][ii];
-                const int m = mask[ii];
-                acc[0] = cjfma<double>(bv, F[h][kk][0][ii], acc[0]);
-#pragma unroll
-                for (int d = 1; d < 9; ++d)
-                    if ((m >> d) & 1) acc[d] = cjfma<double>(bv, F[h][kk][d][ii], acc[d]);
-            }
-        }
-        __syncthreads();
-    }
-    if (j < c.Nb && kk < nk) {
-#pragma unroll
-        for (int d = 0; d < 9; ++d)
-            P[((((size_t)blockIdx.z * c.Nc + a) * 9 + d) * PROJ_NK + kk) * c.Nb + j] = acc[d];
+// v += x (i^P y), x real
+template <int P> __device__ __forceinline__ void axpy_phase(double x, double2 y, double2& v) {
+    if constexpr (P == 0) {
+        v.x = fma(x, y.x, v.x);
+        v.y = fma(x, y.y, v.y);
+    } else if constexpr (P == 1) {
+        v.x = fma(-x, y.y, v.x);
+        v.y = fma(x, y.x, v.y);
+    } else if constexpr (P == 2) {
+        v.x = fma(-x, y.x, v.x);
+        v.y = fma(-x, y.y, v.y);
+    } else {
+        v.x = fma(x, y.y, v.x);
+        v.y = fma(-x, y.x, v.y);
     }
 }
 
-// A64[a][d][k0+kk][j] = sum over the parts, in part order
-__global__ void __launch_bounds__(CWG) coarse_project_sum_kernel(CoarseGeom c, const double2* __restrict__ P, int k0,
-                                                                 int nk, double2* __restrict__ A64) {
-    const size_t n = (size_t)c.Nc * 9 * nk * c.Nb;
-    for (size_t e = (size_t)blockIdx.x * CWG + threadIdx.x; e < n; e += (size_t)gridDim.x * CWG) {
-        const int j = (int)(e % c.Nb);
-        const size_t r = e / c.Nb;
-        const int kk = (int)(r % nk);
-        const size_t ad = r / nk;  // a * 9 + d
-        double2 sum = P[(ad * PROJ_NK + kk) * c.Nb + j];
-        for (int q = 1; q < PROJ_PARTS; ++q) sum = cadd<double>(sum, P[(((size_t)q * c.Nc * 9 + ad) * PROJ_NK + kk) * c.Nb + j]);
-        A64[(ad * c.Nb + (k0 + kk)) * c.Nb + j] = sum;
+// g_mu moves spin SP to spin gamma_spin with the phase i^gamma_phase (chiral basis)
+template <int MU, int SP> constexpr int gamma_spin() { return MU < 2 ? 3 - SP : (SP + 2) % 4; }
+template <int MU, int SP> constexpr int gamma_phase() {
+    if (MU == 0) return SP < 2 ? 1 : 3;
+    if (MU == 1) return SP == 0 || SP == 3 ? 2 : 0;
+    if (MU == 2) return SP == 0 || SP == 3 ? 1 : 3;
+    return 0;
+}
+
+// one forward hop: p the lane's column and slice at the neighbouring site (component
+// stride cst), u its link (uniform); X += cs V + cf g_mu V
+template <int MU>
+__device__ __forceinline__ void build_hop(const double2* __restrict__ p, size_t cst, const double2* __restrict__ u,
+                                          double cs, double cf, double2 (&X)[12]) {
+    double2 v[12], m[9];
+#pragma unroll
+    for (int e = 0; e < 12; ++e) v[e] = p[e * cst];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int e = 0; e < 9; ++e) m[e] = u[e];
+    auto spin = [&](auto SPc) {
+        constexpr int SP = decltype(SPc)::value;
+        constexpr int D = gamma_spin<MU, SP>(), P = gamma_phase<MU, SP>();
+#pragma unroll
+        for (int r = 0; r < 3; ++r) {
+            double2 o = make_double2(0, 0);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) o = cfma<double>(m[r * 3 + k], v[SP * 3 + k], o);
+            axpy_phase<0>(cs, o, X[SP * 3 + r]);
+            axpy_phase<P>(cf, o, X[D * 3 + r]);
+        }
+    };
+    spin(std::integral_constant<int, 0>{});
+    spin(std::integral_constant<int, 1>{});
+    spin(std::integral_constant<int, 2>{});
+    spin(std::integral_constant<int, 3>{});
+}
+
+// half the diagonal and fifth-dimension terms of stored slice s of a column (its
+// entry at p; slices s + 1 and s - 1 are the next and the previous entry, reflected
+// at the ends of the stored half), for the rows of the column's chirality (same) or
+// of the other one
+__device__ __forceinline__ void local_terms(const CoarseGeom& c, const double2* __restrict__ p, size_t cst, int s,
+                                            double sg, bool same, double2 (&X)[12]) {
+    const bool top = s == c.Lh - 1, bot = s == 0;
+    const int ou = top ? 0 : 1, od = bot ? 0 : -1;
+    const double mf = c.f.mf, dg = same ? 0.5 * sg * c.f.diag : 0.0, fl = same ? 1.0 : -1.0;
+    // the whole terms: upper spins -sigma/2 b(s+1) +- sigma/2 x, x = -b(s-1) (s = 0: mf
+    // sigma b(0)); lower spins y/2 -+ sigma/2 b(s+1), y = -sigma b(s-1) (s = 0: -mf
+    // b(0)); upper sign: same chirality.  Past the stored half b(Ls/2) is sigma b(Ls/2
+    // - 1) for upper and -sigma b(Ls/2 - 1) for lower spins.
+    const double au = -0.25 * sg * (top ? sg : 1.0), ad = -0.25 * sg * (top ? -sg : 1.0) * fl;
+    const double xu = 0.25 * sg * (bot ? mf * sg : -1.0) * fl, xd = 0.25 * (bot ? -mf : -sg);
+    double2 v[12];
+#pragma unroll
+    for (int e = 0; e < 12; ++e) X[e] = p[e * cst];
+#pragma unroll
+    for (int e = 0; e < 12; ++e) v[e] = p[e * cst + ou];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int e = 0; e < 12; ++e) {
+        X[e] = make_double2(dg * X[e].x, dg * X[e].y);
+        axpy_phase<0>(e < 6 ? au : ad, v[e], X[e]);
+    }
+#pragma unroll
+    for (int e = 0; e < 12; ++e) v[e] = p[(ptrdiff_t)(e * cst) + od];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int e = 0; e < 12; ++e) axpy_phase<0>(e < 6 ? xu : xd, v[e], X[e]);
+}
+
+// most parts that class 0 of a block is split into (their sums are added in part
+// order)
+constexpr int BUILD_PARTS_MAX = 8;
+constexpr int BUILD_TILES = 3;  // most column tiles per workgroup (two wavefronts each)
+
+struct BuildSplit {
+    int parts;  // of class 0
+    int nrg;    // row groups of 16 MT rows of each chirality
+    int ncg;    // column groups of up to BUILD_TILES tiles
+    int tiles;  // column tiles per group
+};
+
+// MT: row tiles per chirality and row group
+template <int MT>
+__global__ void __launch_bounds__(128 * BUILD_TILES) __attribute__((amdgpu_waves_per_eu(3)))
+coarse_build_kernel(CoarseGeom c, BuildSplit bs, const double2* __restrict__ b64, const double2* __restrict__ U,
+                    double2* __restrict__ A64, double2* __restrict__ P) {
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    double2* rows = reinterpret_cast<double2*>(smem_raw);  // [12][2][16 MT][4]: component, chirality, row, slice
+    const int units = bs.parts + 4, Nb = c.Nb;
+    int lb = logical_block(blockIdx.x, gridDim.x);
+    const int cg = lb % bs.ncg;
+    lb /= bs.ncg;
+    const int rg = lb % bs.nrg;
+    lb /= bs.nrg;
+    const int unit = lb % units, a = lb / units;
+    const int r0 = rg * 16 * MT, rn = min(16 * MT, c.nvec - r0);  // the group's rows of each chirality
+    const int lane = threadIdx.x & 63, q = lane >> 4, cl = lane & 15;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), h = wave & 1;  // row chirality
+    const int col = (cg * bs.tiles + (wave >> 1)) * 16 + cl, colc = min(col, Nb - 1);
+    const bool same = (colc >= c.nvec) == (h == 1);
+    const double sg = colc >= c.nvec ? -1.0 : 1.0;
+    const int nsq = (c.Lh + 3) / 4;  // slice groups per site
+    const size_t cst = (size_t)c.bvol * c.Lh;
+    const int cls = max(unit - bs.parts + 1, 0);  // class 0, or face 1 + fmu
+    const int fmu = cls - 1;
+    int nsite = c.bvol, fst = 1, fb = 1;  // sites of the class; stride and extent of its direction in the block
+    if (cls > 0) {
+        for (int nu = 0; nu < fmu; ++nu) fst *= c.B[nu];
+        fb = fmu == 0 ? c.B[0] : fmu == 1 ? c.B[1] : fmu == 2 ? c.B[2] : c.B[3];
+        nsite /= fb;
+    }
+    const int nit = nsite * nsq;
+    const int it0 = cls > 0 ? 0 : (int)((long long)nit * unit / bs.parts);
+    const int it1 = cls > 0 ? nit : (int)((long long)nit * (unit + 1) / bs.parts);
+    const int an = cls > 0 ? coarse_nbr(c, a, cls) : a;
+    const double2* nbr = b64 + ((size_t)an * Nb + colc) * c.nhalf;
+    // site and slice group of iteration it
+    auto site_of = [&](int it, int& sl, int& sq) {
+        sl = it / nsq;
+        sq = it - sl * nsq;
+        if (cls > 0) {  // the sl-th site of the face
+            const int hi = sl / fst;
+            sl = (hi * fb + fb - 1) * fst + (sl - hi * fst);
+        }
+    };
+    // The rows of a site go to LDS directly, 64 lanes (16 rows of a chirality by 4
+    // slices) an instruction; rows past the chirality's last one repeat it.
+    const double2* const rsrc = b64 + (size_t)a * Nb * c.nhalf;
+    const int rr = lane >> 2, rh = wave & 1;
+    auto load_rows = [&](int sl, int sq) {
+        const int s = min(4 * sq + (lane & 3), c.Lh - 1);
+        for (int pr = wave >> 1; pr < 12 * MT; pr += bs.tiles) {
+            const int e = pr / MT, t = pr % MT;
+            const int row = rh * c.nvec + r0 + min(t * 16 + rr, rn - 1);
+            __builtin_amdgcn_global_load_lds(rsrc + (size_t)row * c.nhalf + (e * cst + (size_t)sl * c.Lh + s),
+                                             (__attribute__((address_space(3))) void*)(rows + ((e * 2 + rh) * 16 * MT + t * 16) * 4),
+                                             16, 0, 0);
+        }
+    };
+    f64x4 re[MT], im[MT];
+#pragma unroll
+    for (int t = 0; t < MT; ++t) re[t] = im[t] = f64x4{0, 0, 0, 0};
+
+    for (int it = it0; it < it1; ++it) {
+        int sl, sq;
+        site_of(it, sl, sq);
+        const int site = __builtin_amdgcn_readfirstlane(block_site(c, a, sl));
+        int lx[4];
+        {
+            int r = sl;
+#pragma unroll
+            for (int nu = 0; nu < 3; ++nu) {
+                lx[nu] = r % c.B[nu];
+                r /= c.B[nu];
+            }
+            lx[3] = r;
+        }
+        __syncthreads();  // the last site's rows have been used
+        load_rows(sl, sq);
+        // lanes past the last stored slice repeat it in both operands; X is cleared there below
+        const int s = min(4 * sq + q, c.Lh - 1);
+        double2 X[12];
+        if (cls == 0) {
+            local_terms(c, nbr + (size_t)sl * c.Lh + s, cst, s, sg, same, X);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 12; ++e) X[e] = make_double2(0, 0);
+        }
+        // block-interior hops (class 0), or the hop across the face
+#define HDCR_BUILD_DIR(MU, ST)                                                                               \
+    if (cls == 0 ? lx[MU] < c.B[MU] - 1 : fmu == MU) {                                                       \
+        const int gx = (MU == 0 ? site : site / c.f.stride[MU]) % c.f.L[MU];                                 \
+        const int sn = cls == 0 ? sl + ST : sl - lx[MU] * ST;                                                \
+        const double k = sg * (gx == c.f.L[MU] - 1 ? c.f.hop * c.f.bc[MU] : c.f.hop);                        \
+        build_hop<MU>(nbr + (size_t)sn * c.Lh + s, cst, U + ((size_t)site * 4 + MU) * 9, same ? k : 0.0, \
+                      same ? 0.0 : k, X);                                                                    \
+    }
+        const int st1 = c.B[0], st2 = st1 * c.B[1], st3 = st2 * c.B[2];
+        HDCR_BUILD_DIR(0, 1)
+        HDCR_BUILD_DIR(1, st1)
+        HDCR_BUILD_DIR(2, st2)
+        HDCR_BUILD_DIR(3, st3)
+#undef HDCR_BUILD_DIR
+        if (4 * sq + 4 > c.Lh) {  // slices past the stored half contribute nothing
+            const bool in = 4 * sq + q < c.Lh;
+#pragma unroll
+            for (int e = 0; e < 12; ++e) X[e] = in ? X[e] : make_double2(0, 0);
+        }
+        __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wavefront's rows are in LDS
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < 12; ++e) {
+            const double br = X[e].x, bi = X[e].y;
+#pragma unroll
+            for (int t = 0; t < MT; ++t) {
+                const double2 ra = rows[((e * 2 + h) * 16 * MT + t * 16 + cl) * 4 + q];
+                re[t] = mfma64(ra.x, br, re[t]);
+                im[t] = mfma64(ra.x, bi, im[t]);
+                re[t] = mfma64(ra.y, bi, re[t]);
+                im[t] = mfma64(ra.y, -br, im[t]);
+            }
+        }
+    }
+    // lane (q, c) holds rows q + 4 i of column c
+    double2* dst = cls == 0 ? P + ((size_t)unit * c.Nc + a) * Nb * Nb : A64 + ((size_t)a * 9 + cls) * Nb * Nb;
+    if (col < Nb) {
+#pragma unroll
+        for (int t = 0; t < MT; ++t)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int j = t * 16 + q + 4 * i;
+                if (j < rn) dst[(size_t)col * Nb + h * c.nvec + r0 + j] = make_double2(re[t][i], im[t][i]);
+            }
+    }
+}
+
+// the other half of A64: A[a][0] = M + M^dag, M the sum of class 0's parts, and
+// A[a][5+mu] = A[a-mu][1+mu]^dag; grid (Nc, 5)
+__global__ void __launch_bounds__(CWG) build_finish_kernel(CoarseGeom c, int parts, const double2* __restrict__ P,
+                                                           double2* __restrict__ A64) {
+    const int a = blockIdx.x, mu = (int)blockIdx.y - 1, Nb = c.Nb;
+    const size_t n2 = (size_t)Nb * Nb;
+    if (mu < 0) {
+        const double2* M = P + (size_t)a * n2;
+        double2* dst = A64 + (size_t)a * 9 * n2;
+        for (int e = threadIdx.x; e < Nb * Nb; e += CWG) {
+            const int k = e / Nb, j = e - k * Nb;
+            double2 m = make_double2(0, 0), t = make_double2(0, 0);
+            for (int z = 0; z < parts; ++z) {
+                m = cadd<double>(m, M[(size_t)z * c.Nc * n2 + e]);
+                t = cadd<double>(t, M[(size_t)z * c.Nc * n2 + (size_t)j * Nb + k]);
+            }
+            dst[e] = make_double2(m.x + t.x, m.y - t.y);
+        }
+    } else {
+        const double2* src = A64 + ((size_t)coarse_nbr(c, a, 5 + mu) * 9 + 1 + mu) * n2;
+        double2* dst = A64 + ((size_t)a * 9 + 5 + mu) * n2;
+        for (int e = threadIdx.x; e < Nb * Nb; e += CWG) {
+            const int k = e / Nb, j = e - k * Nb;
+            const double2 v = src[(size_t)j * Nb + k];
+            dst[e] = make_double2(v.x, -v.y);
+        }
     }
 }
 
@@ -1623,14 +1809,29 @@ void launch_coarse_apply_bf16(const CoarseGeom& c, const uint16_t* A, const floa
     coarse_apply_launch<float, uint32_t>(c, reinterpret_cast<const uint32_t*>(A), v, out, nrhs, s);
 }
 
-size_t coarse_project_scratch_elems(const CoarseGeom& c) { return (size_t)PROJ_PARTS * c.Nc * 9 * PROJ_NK * c.Nb; }
+// parts of class 0: the block extent, so that a part has about the sites of a face
+static int build_parts(const CoarseGeom& c) {
+    const int b = std::max(std::max(c.B[0], c.B[1]), std::max(c.B[2], c.B[3]));
+    return std::min(b, BUILD_PARTS_MAX);
+}
+size_t coarse_build_scratch_elems(const CoarseGeom& c) { return (size_t)build_parts(c) * c.Nc * c.Nb * c.Nb; }
 
-void launch_coarse_project(const CoarseGeom& c, const double2* b64, const double2* Y, int k0, int nk, double2* P,
-                           double2* A64, hipStream_t s) {
-    hipLaunchKernelGGL(coarse_project_kernel, dim3(c.Nc, (c.Nb + PROJ_ROWS - 1) / PROJ_ROWS, PROJ_PARTS), dim3(CWG), 0,
-                       s, c, b64, Y, nk, P);
-    hipLaunchKernelGGL(coarse_project_sum_kernel, dim3(grid_for((size_t)c.Nc * 9 * nk * c.Nb)), dim3(CWG), 0, s, c,
-                       (const double2*)P, k0, nk, A64);
+void launch_coarse_build(const CoarseGeom& c, const double2* b64, const double2* U, double2* P, double2* A64,
+                         hipStream_t s) {
+    const int parts = build_parts(c), tiles = (c.Nb + 15) / 16;
+    const int mt = c.nvec > 16 ? 2 : 1;
+    BuildSplit bs;
+    bs.parts = parts;
+    bs.nrg = (c.nvec + 16 * mt - 1) / (16 * mt);
+    bs.ncg = (tiles + BUILD_TILES - 1) / BUILD_TILES;
+    bs.tiles = (tiles + bs.ncg - 1) / bs.ncg;
+    const size_t lds = (size_t)12 * 2 * 16 * mt * 4 * sizeof(double2);
+    const dim3 grid((unsigned)((size_t)c.Nc * (parts + 4) * bs.nrg * bs.ncg)), wg(128 * bs.tiles);
+    if (mt == 2)
+        hipLaunchKernelGGL(coarse_build_kernel<2>, grid, wg, lds, s, c, bs, b64, U, A64, P);
+    else
+        hipLaunchKernelGGL(coarse_build_kernel<1>, grid, wg, lds, s, c, bs, b64, U, A64, P);
+    hipLaunchKernelGGL(build_finish_kernel, dim3(c.Nc, 5), dim3(CWG), 0, s, c, parts, (const double2*)P, A64);
 }
 
 void launch_coarse_convert(const CoarseGeom& c, const double2* A64, hdcr_dtype dt, void* dst, hipStream_t s) {
