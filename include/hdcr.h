@@ -409,15 +409,15 @@ HDCR_API int hdcr_coarse_solve(const hdcr_coarse_desc* desc, hdcr_dtype A_dtype,
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc): the
  * same kernels and results, with the scratch taken from a static device array
  * of the library instead of a workspace argument.  That array holds
- * HDCR_COARSE_STATIC_BYTES (8 MiB) per GPU for as long as the process runs; a
+ * HDCR_COARSE_STATIC_BYTES (14 MiB) per GPU for as long as the process runs; a
  * coarse space whose solve needs more (hdcr_workspace_bytes(HDCR_WS_COARSE)) is
- * rejected with HDCR_ENOMEM before any launch (8 MiB covers, e.g., 6^4 coarse
+ * rejected with HDCR_ENOMEM before any launch (14 MiB covers, e.g., 6^4 coarse
  * sites with Nb = 64 in FP64).  The caller passes A, defl, b and x as for
  * hdcr_coarse_solve.  Every call on one GPU uses that GPU's single array, so
  * calls that overlap on one GPU (other host threads, other streams) race and
  * must be serialised by the caller; each call clears the counters it needs.
  * The call itself allocates nothing.  Synchronous. */
-#define HDCR_COARSE_STATIC_BYTES (8u << 20)
+#define HDCR_COARSE_STATIC_BYTES (14u << 20)
 HDCR_API int hdcr_coarse_solve_static(const hdcr_coarse_desc* desc, hdcr_dtype A_dtype, const void* A,
                                       const hdcr_coarse_deflation* defl, const void* b, void* x, int32_t maxiter,
                                       double tol, int32_t* iters, hipStream_t stream);

@@ -22,7 +22,7 @@ PRECOND_NONE, PRECOND_TWO_LEVEL = 0, 1
 WS_SOLVE, WS_BUILD, WS_SUBSPACE, WS_SMOOTH, WS_VCYCLE, WS_COARSE = 0, 1, 2, 3, 4, 5
 DEFL_MAX = 64
 DOT_WORK_BYTES = 32768
-COARSE_STATIC_BYTES = 8 << 20
+COARSE_STATIC_BYTES = 14 << 20
 
 
 TUNE_FIELDS = ("dslash_variant", "tslab", "ysplit", "xsplit", "force_r", "force_ms", "force_p", "force_sum",

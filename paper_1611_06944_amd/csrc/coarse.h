@@ -115,12 +115,12 @@ void launch_coarse_apply_bf16(const CoarseGeom& c, const uint16_t* A, const floa
 // synchronising; reductions finish in the last-arriving workgroup in a fixed
 // order (reproducible).
 template <typename T> struct CoarseCRWork {
-    C2<T>* r;
+    C2<T>* r[2];    // of the even / odd steps, as Ar and Ap
+    C2<T>* Ar[2];
+    C2<T>* Ap[2];
     C2<T>* p;
-    C2<T>* Ar;
-    C2<T>* Ap;
-    double* part;   // partial sums: [3][Nc] of the apply, [2][work-groups] of the start kernels,
-                    // then two halves of [2][CCR_UPDATE_MAX] of the update kernel (even / odd steps)
+    double* part;   // partial sums: CCR_START_PARTS of the start kernels, then two halves of
+                    // [5][ccr_groups<T>(Nc)] of the step kernel (even / odd steps)
     double* cs;     // scalars: 3 |r|^2 of the start, 4 |b|^2, 5 tol^2, 6 / 7 <r,Ar> of the even / odd steps
     int* flags;     // 0 done, 1 iterations, 2 (unused), 3 maxiter,
                     // 4 stop reason (0 none, 2 near-breakdown, 3 not finite);
@@ -140,7 +140,15 @@ template <typename T> struct DeflView {
     const C2<T>* W;
 };
 constexpr int CCR_BLOCKS = 64;        // work-groups of the start kernel
-constexpr int CCR_UPDATE_MAX = 512;   // most work-groups of the update kernel (one element per work-item below it)
+constexpr int CCR_START_PARTS = 2 * (CCR_BLOCKS > DEFL_INIT_BLOCKS ? CCR_BLOCKS : DEFL_INIT_BLOCKS);
+// workgroups of the step kernel: one per coarse site, or as many sites to each as keep
+// them to the number that is resident (four per CU, three in FP64): each reads the
+// partial sums of all (8 sites to a workgroup at 8192 sites, Nb = 32, BF16: 61 us a step,
+// the matrix at 5.0 TB/s)
+template <typename T> int ccr_groups(int Nc) {
+    const int most = 256 * (sizeof(T) == 8 ? 3 : 4), spw = (Nc + most - 1) / most;
+    return (Nc + spw - 1) / spw;
+}
 constexpr int ARRIVE_GROUPS = 16;   // group counters of the last-arrival test
 constexpr int ARRIVE_STRIDE = 64;   // ints between counters (each counter on its own 256-byte line)
 constexpr int CCR_COUNTERS = 64;    // first arrival counter in flags
@@ -158,7 +166,7 @@ template <typename T>
 void launch_ccr_init_defl(const CoarseGeom& c, const C2<T>* b, C2<T>* x, const CoarseCRWork<T>& w,
                           const DeflView<T>& d, int maxiter, double tol, hipStream_t s);
 // CR step `step` (1, 2, ...: the p, x and r updates of step `step`, then
-// Ar = A r for the next one); step 0 issues the first apply Ar = A r instead
+// Ar = A r for the next one); step 0 is the first apply Ar = A r alone
 template <typename T>
 void launch_ccr_step(const CoarseGeom& c, hdcr_dtype A_dtype, const void* A, C2<T>* x, const CoarseCRWork<T>& w,
                      int step, hipStream_t s);

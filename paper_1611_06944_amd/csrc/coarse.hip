@@ -961,167 +961,322 @@ __global__ void __launch_bounds__(CWG) ccr_init_defl_kernel(int n, const C2<T>* 
     }
 }
 
-// Ar = A r for coarse site a (one workgroup).  Partial sums per coarse site:
-// <r,Ar> to part[a], |Ar|^2 to part[Nc+a] and Re<Ap,Ar> (Ap of the previous
-// step; 0 on the first apply, FIRST) to part[2Nc+a].
-template <typename T, typename S, int E, bool FIRST>
-__global__ void __launch_bounds__(CWG) ccr_apply_kernel(CoarseGeom c, const S* __restrict__ A,
-                                                        const C2<T>* __restrict__ r, C2<T>* __restrict__ Ar,
-                                                        const C2<T>* __restrict__ Ap, double* part, int* flags) {
-    if (flags[0]) return;
-    extern __shared__ unsigned char smem_raw[];
-    C2<T>* vs = reinterpret_cast<C2<T>*>(smem_raw);   // [9][Nb]
-    C2<T>* res = vs + 9 * c.Nb;                        // [Nb]
-    C2<T>* red = res + c.Nb;                           // [CWG * E]
-    const int a = blockIdx.x;
-    for (int e = threadIdx.x; e < 9 * c.Nb; e += CWG) {
-        const int d = e / c.Nb, k = e - d * c.Nb;
-        vs[e] = r[(size_t)coarse_nbr(c, a, d) * c.Nb + k];
+// 16 bytes of A as loaded, and the entries in them
+template <typename T, typename S, int E> struct RawA;
+template <> struct RawA<double, double2, 1> {
+    double2 w;
+    __device__ __forceinline__ double2 get(int) const { return w; }
+};
+template <> struct RawA<float, float2, 1> {
+    float2 w;
+    __device__ __forceinline__ float2 get(int) const { return w; }
+};
+template <> struct RawA<float, float2, 2> {
+    float4 w;
+    __device__ __forceinline__ float2 get(int q) const { return q ? make_float2(w.z, w.w) : make_float2(w.x, w.y); }
+};
+template <> struct RawA<float, uint32_t, 1> {
+    uint32_t w;
+    __device__ __forceinline__ float2 get(int) const {
+        return make_float2(__uint_as_float(w << 16), __uint_as_float(w & 0xffff0000u));
+    }
+};
+template <> struct RawA<float, uint32_t, 4> {
+    uint4 w;
+    __device__ __forceinline__ float2 get(int q) const {
+        const uint32_t v = q == 0 ? w.x : q == 1 ? w.y : q == 2 ? w.z : w.w;
+        return make_float2(__uint_as_float(v << 16), __uint_as_float(v & 0xffff0000u));
+    }
+};
+
+// Sums of five values over the workgroup, the same in every work-item: over rows of 16
+// lanes by data-parallel moves (each lane ends with the row's sum, added in the same
+// tree in every lane), then over the rows through sh.  One barrier, where a tree in LDS
+// has nine: 0.2 us against 0.9 us in a kernel of 9 us.
+template <int CTRL> __device__ __forceinline__ double dpp_add(double v) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xf, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, false);
+    return v + __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+__device__ __forceinline__ double row_sum(double v) {
+    v = dpp_add<0xB1>(v);     // lane ^ 1
+    v = dpp_add<0x4E>(v);     // lane ^ 2
+    v = dpp_add<0x141>(v);    // the other four of eight
+    return dpp_add<0x140>(v);  // the other eight
+}
+__device__ __forceinline__ void block_sum5(double (&v)[5], double (&sh)[5][CWG / 16]) {
+    static_assert(CWG == 256, "one row of 16 lanes holds the workgroup's row sums");
+    const int t = threadIdx.x;
+#pragma unroll
+    for (int q = 0; q < 5; ++q) {
+        v[q] = row_sum(v[q]);
+        if (t % 16 == 0) sh[q][t / 16] = v[q];
     }
     __syncthreads();
-    site_gemv<T, S, E>(c, A, a, vs, red, res);
-    double sums[3] = {0.0, 0.0, 0.0};
-    for (int j = threadIdx.x; j < c.Nb; j += CWG) {
-        const C2<T> o = res[j];
-        const size_t idx = (size_t)a * c.Nb + j;
-        Ar[idx] = o;
-        const C2<T> rv = vs[j];  // d = 0 slot holds r(a)
-        sums[0] += (double)rv.x * o.x + (double)rv.y * o.y;
-        sums[1] += (double)o.x * o.x + (double)o.y * o.y;
-        if (!FIRST) {
-            const C2<T> q = Ap[idx];
-            sums[2] += (double)q.x * o.x + (double)q.y * o.y;
-        }
-    }
-    block_reduce<3>(sums);
-    // partial sums only: the update kernel reduces them in every one of its
-    // workgroups (no device-scope fence and atomic per coarse site here)
-    if (threadIdx.x == 0) {
-        part[a] = sums[0];
-        part[c.Nc + a] = sums[1];
-        part[2 * c.Nc + a] = sums[2];
-    }
+#pragma unroll
+    for (int q = 0; q < 5; ++q) v[q] = row_sum(sh[q][t % 16]);
 }
 
-// CR step k (k >= 1) after the apply of r_k, in a single pass:
+// how a step is split
+struct CcrSplit {
+    int spw;       // coarse sites per workgroup
+    int kg;        // row groups of the site's matrix
+    int nb;        // batches of PB loads per site
+    int rnj, rnb;  // ceil(2^20 / (Nb / E)), ceil(2^20 / Nb): e / n = (e r) >> 20 for e n < 2^20
+};
+
+// the fields a step reads, or those it writes
+template <typename T> struct CcrFields {
+    C2<T>* r;
+    C2<T>* Ar;
+    C2<T>* Ap;
+};
+
+// CR step k (k >= 1; step 0 is its second half alone), one kernel:
 //   beta = <r,Ar>_k / <r,Ar>_{k-1}, p = r + beta p, Ap = Ar + beta Ap
 //   (step 1: p = r, Ap = Ar),
 //   alpha = <r,Ar>_k / |Ap|^2,  x += alpha p,  r -= alpha Ap,
-// with |Ap|^2 = |Ar|^2 + 2 beta Re<Ap_old,Ar> + beta^2 |Ap_old|^2 from the
-// apply's partials, so no reduction separates the p update from the x, r update.
-// The step needs no grid-wide arrival either: it stores its per-work-group
-// partials of |r_{k+1}|^2 and |Ap_k|^2 (uout), and step k+1 reduces them
-// (uin, the other half of a ping-pong pair) in each of its work-groups, ordered
-// by the kernel boundary.  So the convergence test of r_k runs at the start of
-// step k (from step 2 on; step 1 runs unconditionally, as the start kernel only
-// stops on a zero or non-finite b), and a converged r_k costs one apply that is
-// not used.  All work-groups reduce the same partials in the same order and so
-// take the same decisions; work-group 0 records them.
-template <typename T>
-__global__ void __launch_bounds__(CWG) ccr_update_kernel(int n, C2<T>* __restrict__ x, C2<T>* __restrict__ r,
-                                                         C2<T>* __restrict__ p, const C2<T>* __restrict__ Ar,
-                                                         C2<T>* __restrict__ Ap, const double* apart, int nc,
-                                                         const double* uin, double* uout, double* cs, int* flags,
-                                                         int step) {
-    if (flags[0]) return;
-    const bool first = step == 1;
-    const bool lead = blockIdx.x == 0 && threadIdx.x == 0;
-    // the apply's partials (t[0..2]) and the previous step's (t[3..4]) in one
-    // pass and one workgroup reduction, each sum in the order of sum_partials
-    double t[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-#pragma unroll 4
-    for (int i = threadIdx.x; i < nc; i += CWG) {
+//   then Ar = A r,
+// with |Ap|^2 = |Ar|^2 + 2 beta Re<Ap_old,Ar> + beta^2 |Ap_old|^2, so that no
+// reduction separates the p update from the x, r update.  A workgroup owns spw
+// coarse sites; it forms the new r of a site's neighbours itself from the old r, Ar
+// and Ap (27 Nb more entries than its own, beside the 9 Nb^2 of A), so that no launch
+// separates the update from the apply either.  in and out are the two halves of a
+// ping-pong pair.
+// The step needs no grid-wide arrival: it stores per-workgroup partials (pout: <r,Ar>,
+// |Ar|^2, Re<Ap,Ar>, |r|^2, |Ap|^2) and step k+1 reduces them (pin) in each of its
+// workgroups, ordered by the kernel boundary.  So the convergence test of r_k runs at
+// the start of step k (from step 2 on; step 1 runs unconditionally, as the start
+// kernel only stops on a zero or non-finite b), and a converged r_k costs one apply
+// that is not used.  All workgroups reduce the same partials in the same order and so
+// take the same decisions; workgroup 0 records them.
+//
+// A work-item covers E consecutive rows j (t % (Nb/E)) and the rows of the site's 9 Nb
+// x Nb matrix (d, k) = kk, kk + kg, ... (kk = t / (Nb/E), kg = CWG / (Nb/E) groups),
+// with PB 16-byte loads of A in flight: the next batch's load is issued as an entry is
+// used, across sites too, and the first batch before anything else, so that the
+// reduction and the neighbours' r hide behind it; the next site's fields are loaded
+// ahead in the same way.
+// Bound by A where it is large (8192 sites, Nb = 32, BF16: 61 us a step, 5.0 TB/s;
+// separate apply and update kernels 79) and by a chain of some 10000 cycles of
+// latencies where it is not (512 sites, Nb = 24, FP64: 12.0 us against 21.1; 32 sites,
+// Nb = 8: 6.1 against 12.7).  FP64 takes three wavefronts per SIMD: four spill.
+template <typename T, typename S, int E, int PB>
+__global__ void __launch_bounds__(CWG) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 3 : 4)))
+ccr_step_kernel(CoarseGeom c, CcrSplit sp, const S* __restrict__ A, CcrFields<T> in, CcrFields<T> out,
+                C2<T>* __restrict__ x, C2<T>* __restrict__ p, const double* __restrict__ pin, double* __restrict__ pout,
+                double* cs, int* flags, int step) {
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    __shared__ double sh[2][5][CWG / 16];
+    const int Nb = c.Nb, nrow = 9 * Nb, kg = sp.kg, nb = sp.nb;
+    C2<T>* vs = reinterpret_cast<C2<T>*>(smem_raw);      // [nb kg PB]: r of the site and its neighbours, then zeros
+    C2<T>* apn = vs + nb * kg * PB;                      // [Nb]: Ap of the site
+    C2<T>* red = apn + Nb;                               // [kg Nb]
+    const int t = threadIdx.x, G = gridDim.x;
+    const int kt = (t * sp.rnj) >> 20, jq = t - kt * (Nb / E), kk = min(kt, kg - 1);
+    const int w = logical_block(blockIdx.x, G);
+    const int a0 = w * sp.spw, a1 = min(a0 + sp.spw, c.Nc);
+    const bool first = step == 1, lead = w == 0 && t == 0;
+    const int done = flags[0];
+    const double rr0 = cs[3], stop = cs[5] * cs[4], rar_old = cs[6 + ((step - 1) & 1)];
+    double v[5];  // the work-item's first entry of each row of partials
 #pragma unroll
-        for (int q = 0; q < 3; ++q) t[q] += apart[(size_t)q * nc + i];
+    for (int q = 0; q < 5; ++q) v[q] = pin[(size_t)q * G + min(t, G - 1)];
+
+    // the first VR rounds of a site's old r, Ar, Ap (its neighbours' and its own) and its x, p
+    constexpr int VR = 2;
+    C2<T> ro[VR], aro[VR], apo[VR], xo = mk<T>(0, 0), po = mk<T>(0, 0);
+    int dv[VR], kv[VR];
+#pragma unroll
+    for (int u = 0; u < VR; ++u) {
+        const int e = min(t + u * CWG, nrow - 1);
+        dv[u] = (e * sp.rnb) >> 20;
+        kv[u] = e - dv[u] * Nb;
     }
-    if (!first) {
-        const int nu = (int)gridDim.x;
-        for (int i = threadIdx.x; i < nu; i += CWG) {
-            t[3] += uin[i];
-            t[4] += uin[nu + i];
+    // lane d < 9: the site's neighbour d
+    auto nbrs = [&](int a) {
+        const int d = min(t & 63, 8), mu = (d - 1) & 3;
+        const int st = mu == 0 ? c.cstride[0] : mu == 1 ? c.cstride[1] : mu == 2 ? c.cstride[2] : c.cstride[3];
+        const int C = mu == 0 ? c.C[0] : mu == 1 ? c.C[1] : mu == 2 ? c.C[2] : c.C[3];
+        const int xm = ((unsigned)a / (unsigned)st) % (unsigned)C;
+        const int up = xm == C - 1 ? a - xm * st : a + st, dn = xm == 0 ? a + (C - 1) * st : a - st;
+        return d == 0 ? a : d <= 4 ? up : dn;
+    };
+    auto fetch = [&](int a) {
+        const int nv = nbrs(a);
+#pragma unroll
+        for (int u = 0; u < VR; ++u) {
+            const size_t i = (size_t)__shfl(nv, dv[u]) * Nb + kv[u];
+            ro[u] = in.r[i];
+            aro[u] = in.Ar[i];
+            apo[u] = in.Ap[i];
         }
-    }
-    block_reduce<5>(t);
-    double rr = cs[3], apold = 0.0;
-    if (!first) {
-        rr = t[3];
-        apold = t[4];
-        if (rr <= cs[5] * cs[4] || !isfinite(rr)) {  // r_k converged (or not finite): x_k is the result
+        if (t < Nb) {
+            xo = x[(size_t)a * Nb + t];
+            po = p[(size_t)a * Nb + t];
+        }
+    };
+    typedef RawA<T, S, E> Raw;
+    Raw buf[PB];
+    auto load = [&](int a, int row) {  // rows past the last one repeat it (they meet zeros in vs)
+        const S* As = A + (size_t)a * nrow * Nb;
+        return *reinterpret_cast<const Raw*>(As + (unsigned)(min(row, nrow - 1) * Nb + jq * E));
+    };
+    fetch(a0);
+#pragma unroll
+    for (int u = 0; u < PB; ++u) buf[u] = load(a0, kk + u * kg);
+    for (int e = nrow + t; e < nb * kg * PB; e += CWG) vs[e] = mk<T>(0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    if (done) return;
+
+    T bt = 0, alpha = 0;
+    double rar = 0;
+    if (step > 0) {
+#pragma unroll
+        for (int q = 0; q < 5; ++q) v[q] = t < G ? v[q] : 0.0;
+#pragma unroll 3
+        for (int i = t + CWG; i < G; i += CWG) {
+#pragma unroll
+            for (int q = 0; q < 5; ++q) v[q] += pin[(size_t)q * G + i];
+        }
+        block_sum5(v, sh[0]);
+        const double rr = first ? rr0 : v[3];
+        if (!first && (rr <= stop || !isfinite(rr))) {  // r_k converged (or not finite): x_k is the result
             if (lead) flags[0] = 1;
             return;
         }
-    }
-    const double rar = t[0];
-    const int bd = ccr_breakdown<T>(rar, rr, t[1]);
-    const double beta = first ? 0.0 : rar / cs[6 + ((step - 1) & 1)];
-    const double apap = first ? t[1] : t[1] + 2.0 * beta * t[2] + beta * beta * apold;
-    if (bd || !(apap > 0.0)) {  // (near-)breakdown ends the coarse solve
-        if (lead) {
-            flags[4] = bd ? bd : 2;
-            flags[0] = 1;
+        rar = v[0];
+        const int bd = ccr_breakdown<T>(rar, rr, v[1]);
+        const double beta = first ? 0.0 : rar / rar_old;
+        const double apap = first ? v[1] : v[1] + 2.0 * beta * v[2] + beta * beta * v[4];
+        if (bd || !(apap > 0.0)) {  // (near-)breakdown ends the coarse solve
+            if (lead) {
+                flags[4] = bd ? bd : 2;
+                flags[0] = 1;
+            }
+            return;
         }
-        return;
+        bt = (T)beta;
+        alpha = (T)(rar / apap);
     }
-    const T bt = (T)beta, alpha = (T)(rar / apap);
-    double v[2] = {0.0, 0.0};
-    for (int i = blockIdx.x * CWG + threadIdx.x; i < n; i += gridDim.x * CWG) {
-        C2<T> rv = r[i], pv, apv;
-        const C2<T> arv = Ar[i];
-        if (first) {
-            pv = rv;
-            apv = arv;
-        } else {
-            pv = p[i];
-            apv = Ap[i];
-            pv.x = rv.x + bt * pv.x;
-            pv.y = rv.y + bt * pv.y;
-            apv.x = arv.x + bt * apv.x;
-            apv.y = arv.y + bt * apv.y;
+    // lanes per row in the sum over kg: 4 where 4 Nb work-items are there, else 2
+    const int lpr = Nb <= CWG / 4 ? 4 : 2, js = t / lpr;
+    double sums[5] = {0, 0, 0, 0, 0};
+    for (int a = a0; a < a1; ++a) {
+        // new r of entry e; for the site's own (e < Nb, e == t) the new p, x and Ap too
+        auto stage = [&](int e, C2<T> rv, C2<T> arv, C2<T> apv) {
+            if (step > 0) {
+                apv.x = first ? arv.x : arv.x + bt * apv.x;
+                apv.y = first ? arv.y : arv.y + bt * apv.y;
+                const C2<T> rold = rv;
+                rv.x -= alpha * apv.x;
+                rv.y -= alpha * apv.y;
+                if (e < Nb) {
+                    const size_t i = (size_t)a * Nb + e;
+                    C2<T> pv = rold, xv = xo;
+                    pv.x = first ? rold.x : rold.x + bt * po.x;
+                    pv.y = first ? rold.y : rold.y + bt * po.y;
+                    xv.x += alpha * pv.x;
+                    xv.y += alpha * pv.y;
+                    p[i] = pv;
+                    x[i] = xv;
+                    out.Ap[i] = apv;
+                    out.r[i] = rv;
+                    apn[e] = apv;
+                    sums[3] += (double)rv.x * rv.x + (double)rv.y * rv.y;
+                    sums[4] += (double)apv.x * apv.x + (double)apv.y * apv.y;
+                }
+            }
+            vs[e] = rv;
+        };
+#pragma unroll
+        for (int u = 0; u < VR; ++u)
+            if (t + u * CWG < nrow) stage(t + u * CWG, ro[u], aro[u], apo[u]);
+        if (nrow > VR * CWG) {
+            const int nv = nbrs(a);
+            for (int e0 = VR * CWG; e0 < nrow; e0 += CWG) {
+                const int e = min(e0 + t, nrow - 1), d = (e * sp.rnb) >> 20;
+                const size_t i = (size_t)__shfl(nv, d) * Nb + (e - d * Nb);
+                if (e0 + t < nrow) stage(e, in.r[i], in.Ar[i], in.Ap[i]);
+            }
         }
-        C2<T> xv = x[i];
-        xv.x += alpha * pv.x;
-        xv.y += alpha * pv.y;
-        rv.x -= alpha * apv.x;
-        rv.y -= alpha * apv.y;
-        p[i] = pv;
-        Ap[i] = apv;
-        x[i] = xv;
-        r[i] = rv;
-        v[0] += (double)rv.x * rv.x + (double)rv.y * rv.y;
-        v[1] += (double)apv.x * apv.x + (double)apv.y * apv.y;
+        fetch(min(a + 1, a1 - 1));
+        __syncthreads();
+        C2<T> acc[E];
+#pragma unroll
+        for (int q = 0; q < E; ++q) acc[q] = mk<T>(0, 0);
+        for (int b = 0; b < nb; ++b) {
+            const bool more = b + 1 < nb;
+            const int an = more ? a : min(a + 1, a1 - 1), rn = kk + (more ? (b + 1) * kg * PB : 0);
+            const C2<T>* vb = vs + kk + b * kg * PB;
+#pragma unroll
+            for (int u = 0; u < PB; ++u) {
+                const C2<T> y = vb[u * kg];
+#pragma unroll
+                for (int q = 0; q < E; ++q) acc[q] = cfma<T>(buf[u].get(q), y, acc[q]);
+                buf[u] = load(an, rn + u * kg);
+            }
+        }
+        if (kt < kg) {
+#pragma unroll
+            for (int q = 0; q < E; ++q) red[kk * Nb + jq * E + q] = acc[q];
+        }
+        __syncthreads();
+        C2<T> o = mk<T>(0, 0);
+        if (js < Nb) {
+#pragma unroll 4
+            for (int g = t % lpr; g < kg; g += lpr) o = cadd<T>(o, red[g * Nb + js]);
+        }
+        o = cadd<T>(o, shfl_xor_c<T>(o, 1));
+        if (lpr == 4) o = cadd<T>(o, shfl_xor_c<T>(o, 2));
+        if (js < Nb && t % lpr == 0) {
+            out.Ar[(size_t)a * Nb + js] = o;
+            const C2<T> rv = vs[js];
+            sums[0] += (double)rv.x * o.x + (double)rv.y * o.y;
+            sums[1] += (double)o.x * o.x + (double)o.y * o.y;
+            if (step > 0) {
+                const C2<T> q = apn[js];
+                sums[2] += (double)q.x * o.x + (double)q.y * o.y;
+            }
+        }
+        if (a + 1 < a1) __syncthreads();
     }
-    block_reduce<2>(v);
-    if (threadIdx.x == 0) {
-        uout[blockIdx.x] = v[0];
-        uout[gridDim.x + blockIdx.x] = v[1];
+    block_sum5(sums, sh[1]);
+    if (t == 0) {
+#pragma unroll
+        for (int q = 0; q < 5; ++q) pout[(size_t)q * G + w] = sums[q];
     }
-    if (lead) {
+    if (lead && step > 0) {
         cs[6 + (step & 1)] = rar;
         flags[1] = step;
     }
 }
 
 // coarse vectors are FP64 with C128 storage and FP32 with C64 / BF16 storage
-template <typename T, typename S, bool FIRST>
-void ccr_apply_launch(const CoarseGeom& c, const S* A, const CoarseCRWork<T>& w, hipStream_t s) {
-    constexpr int E = wide_entries<S>();
-    if (c.Nb % E == 0)
-        hipLaunchKernelGGL((ccr_apply_kernel<T, S, E, FIRST>), dim3(c.Nc), dim3(CWG), (apply_lds<T, E>(c)), s, c, A,
-                           w.r, w.Ar, w.Ap, w.part, w.flags);
+template <typename T, typename S, int E>
+void ccr_step_launch(const CoarseGeom& c, const S* A, C2<T>* x, const CoarseCRWork<T>& w, int step, hipStream_t s) {
+    const int G = ccr_groups<T>(c.Nc), nj = c.Nb / E, kg = CWG / nj, rows = (9 * c.Nb + kg - 1) / kg;
+    const int o = step & 1, i = step > 0 ? 1 - o : 0;
+    const CcrFields<T> in{w.r[i], w.Ar[i], w.Ap[i]}, out{w.r[o], w.Ar[o], w.Ap[o]};
+    double* part = w.part + CCR_START_PARTS;
+    auto go = [&](auto pbc) {
+        constexpr int PB = decltype(pbc)::value;
+        const CcrSplit sp{(c.Nc + G - 1) / G, kg, (rows + PB - 1) / PB, ((1 << 20) + nj - 1) / nj,
+                          ((1 << 20) + c.Nb - 1) / c.Nb};
+        const size_t lds = ((size_t)sp.nb * kg * PB + c.Nb + (size_t)kg * c.Nb) * sizeof(C2<T>);
+        hipLaunchKernelGGL((ccr_step_kernel<T, S, E, PB>), dim3(G), dim3(CWG), lds, s, c, sp, A, in, out, x, w.p,
+                           (const double*)(part + (size_t)i * 5 * G), part + (size_t)o * 5 * G, w.cs, w.flags, step);
+    };
+    // loads per batch: 9 where that wastes no more of them past the last row than 8 does
+    // (9 Nb rows over a power of two: 68 against 79 us a step at 8192 sites, Nb = 32, BF16,
+    // measured with the two alone different), 4 for the smallest matrices
+    if (rows <= 4)
+        go(std::integral_constant<int, 4>{});
+    else if ((rows + 8) / 9 * 9 <= (rows + 7) / 8 * 8)
+        go(std::integral_constant<int, 9>{});
     else
-        hipLaunchKernelGGL((ccr_apply_kernel<T, S, 1, FIRST>), dim3(c.Nc), dim3(CWG), (apply_lds<T, 1>(c)), s, c, A,
-                           w.r, w.Ar, w.Ap, w.part, w.flags);
-}
-
-template <typename T, bool FIRST>
-void ccr_apply_dispatch(const CoarseGeom& c, hdcr_dtype dt, const void* A, const CoarseCRWork<T>& w, hipStream_t s) {
-    if constexpr (sizeof(T) == 8) {
-        ccr_apply_launch<T, double2, FIRST>(c, static_cast<const double2*>(A), w, s);
-    } else if (dt == HDCR_C64) {
-        ccr_apply_launch<T, float2, FIRST>(c, static_cast<const float2*>(A), w, s);
-    } else {
-        ccr_apply_launch<T, uint32_t, FIRST>(c, static_cast<const uint32_t*>(A), w, s);
-    }
+        go(std::integral_constant<int, 8>{});
 }
 
 // ---------------------------------------------------------------------------
@@ -1496,8 +1651,8 @@ template <typename T>
 void launch_ccr_init(const CoarseGeom& c, const C2<T>* b, C2<T>* x, const CoarseCRWork<T>& w, int maxiter, double tol,
                      hipStream_t s) {
     const double tol2 = tol > 0 ? tol * tol : 0.0;
-    hipLaunchKernelGGL(ccr_init_kernel<T>, dim3(CCR_BLOCKS), dim3(CWG), 0, s, c.Nc * c.Nb, b, x, w.r,
-                       w.part + 3 * (size_t)c.Nc, w.cs, w.flags, maxiter, tol2);
+    hipLaunchKernelGGL(ccr_init_kernel<T>, dim3(CCR_BLOCKS), dim3(CWG), 0, s, c.Nc * c.Nb, b, x, w.r[0],
+                       w.part, w.cs, w.flags, maxiter, tol2);
 }
 
 template <typename T>
@@ -1507,29 +1662,27 @@ void launch_ccr_init_defl(const CoarseGeom& c, const C2<T>* b, C2<T>* x, const C
     const int n = c.Nc * c.Nb;
     hipLaunchKernelGGL(defl_dot_kernel<T>, dim3(DEFL_BLOCKS, (d.k + 7) / 8), dim3(CWG), 0, s, n, d, b, w.dpart);
     hipLaunchKernelGGL(defl_coef_kernel<T>, dim3(2 * d.k), dim3(CWG), 0, s, d, (const double*)w.dpart, w.dcoef);
-    hipLaunchKernelGGL(ccr_init_defl_kernel<T>, dim3(DEFL_INIT_BLOCKS), dim3(CWG), 0, s, n, b, x, w.r, d,
-                       (const double*)w.dcoef, w.part + 3 * (size_t)c.Nc, w.cs, w.flags, maxiter, tol2);
-}
-
-static int ccr_update_blocks(int n) {
-    const int b = (n + CWG - 1) / CWG;
-    return b < 1 ? 1 : (b > CCR_UPDATE_MAX ? CCR_UPDATE_MAX : b);
+    hipLaunchKernelGGL(ccr_init_defl_kernel<T>, dim3(DEFL_INIT_BLOCKS), dim3(CWG), 0, s, n, b, x, w.r[0], d,
+                       (const double*)w.dcoef, w.part, w.cs, w.flags, maxiter, tol2);
 }
 
 template <typename T>
 void launch_ccr_step(const CoarseGeom& c, hdcr_dtype A_dtype, const void* A, C2<T>* x, const CoarseCRWork<T>& w,
                      int step, hipStream_t s) {
-    const int n = c.Nc * c.Nb;
-    if (step == 0) {
-        ccr_apply_dispatch<T, true>(c, A_dtype, A, w, s);
-        return;
-    }
-    double* upart = w.part + 3 * (size_t)c.Nc + 2 * (size_t)std::max(CCR_BLOCKS, DEFL_INIT_BLOCKS);
-    const size_t half = 2 * (size_t)CCR_UPDATE_MAX;
-    hipLaunchKernelGGL(ccr_update_kernel<T>, dim3(ccr_update_blocks(n)), dim3(CWG), 0, s, n, x, w.r, w.p, w.Ar, w.Ap,
-                       (const double*)w.part, c.Nc, (const double*)(upart + ((step - 1) & 1) * half),
-                       upart + (step & 1) * half, w.cs, w.flags, step);
-    ccr_apply_dispatch<T, false>(c, A_dtype, A, w, s);
+    auto go = [&](auto* Ap) {
+        typedef std::remove_cv_t<std::remove_pointer_t<decltype(Ap)>> S;
+        constexpr int E = wide_entries<S>();
+        if (c.Nb % E == 0)
+            ccr_step_launch<T, S, E>(c, Ap, x, w, step, s);
+        else
+            ccr_step_launch<T, S, 1>(c, Ap, x, w, step, s);
+    };
+    if constexpr (sizeof(T) == 8)
+        go(static_cast<const double2*>(A));
+    else if (A_dtype == HDCR_C64)
+        go(static_cast<const float2*>(A));
+    else
+        go(static_cast<const uint32_t*>(A));
 }
 
 template void launch_ccr_init<double>(const CoarseGeom&, const double2*, double2*, const CoarseCRWork<double>&, int,

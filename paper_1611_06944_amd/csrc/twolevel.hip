@@ -69,12 +69,13 @@ PhaseTimer::~PhaseTimer() {
 template <typename T> CoarseCRWork<T> coarse_cr_carve(Carver& w, const CoarseGeom& c) {
     const size_t n = (size_t)c.Nc * c.Nb;
     CoarseCRWork<T> k;
-    k.r = w.take<C2<T>>(n);
+    for (int h = 0; h < 2; ++h) {
+        k.r[h] = w.take<C2<T>>(n);
+        k.Ar[h] = w.take<C2<T>>(n);
+        k.Ap[h] = w.take<C2<T>>(n);
+    }
     k.p = w.take<C2<T>>(n);
-    k.Ar = w.take<C2<T>>(n);
-    k.Ap = w.take<C2<T>>(n);
-    k.part = w.take<double>(3 * (size_t)c.Nc + 2 * (size_t)std::max(CCR_BLOCKS, DEFL_INIT_BLOCKS) +
-                            4 * (size_t)CCR_UPDATE_MAX);
+    k.part = w.take<double>(CCR_START_PARTS + 2 * 5 * (size_t)ccr_groups<T>(c.Nc));
     k.cs = w.take<double>(8);
     k.flags = w.take<int>(CCR_FLAGS);
     k.dpart = w.take<double>((size_t)2 * DEFL_KMAX * DEFL_BLOCKS);
