@@ -104,7 +104,10 @@ int coarse_cr(const CoarseGeom& c, hdcr_dtype A_dtype, const void* A, const C2<T
         HDCR_HIP_CHECK(hipGetLastError());
         return HDCR_OK;
     }
-    // enqueue a batch sized by the previous solve, then check the device flag
+    // Enqueue a batch sized by the previous solve, then check the device flag.  Later
+    // batches are a quarter of the steps so far: a check leaves the GPU idle for some 40
+    // us, a step past the end returns at once.  A coarse solve of 184 steps (8^3 x 16, 2^4
+    // blocks, Nb = 24, FP64) took 2.95 ms with 8 steps a batch and takes 2.48.
     int enq = 0;
     int batch = std::max(4, std::min(hint > 0 ? hint + 2 : 16, maxiter));
     int hf[5] = {0, 0, 0, 0, 0};
@@ -115,7 +118,7 @@ int coarse_cr(const CoarseGeom& c, hdcr_dtype A_dtype, const void* A, const C2<T
         HDCR_HIP_CHECK(hipMemcpyAsync(hf, w.flags, 5 * sizeof(int), hipMemcpyDeviceToHost, s));
         HDCR_HIP_CHECK(hipStreamSynchronize(s));
         if (hf[0]) break;
-        batch = 8;
+        batch = std::max(8, std::min(enq / 4, 64));
     }
     if (iters) *iters = hf[1];
     if (reason) *reason = hf[4];
