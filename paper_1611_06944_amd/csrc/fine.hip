@@ -1095,11 +1095,50 @@ dslash_quad_h16_kernel(FineGeom g, TileGeom tg, const float2* U, const uint4_t* 
 // sites, work-item (j, kk) the site j of the workgroup and W adjacent slices.
 // The 72 link entries of a site are loaded once, split over its work-items, and
 // staged in LDS with the workgroup's own spinors (the fifth-dimension
-// neighbours); all eight hops gather from the field.
+// neighbours); all eight hops gather from the field, two hops ahead of their use.
 struct SiteSplit {
     int NK;     // work-items per site (Ls / W)
     int sites;  // sites per workgroup
 };
+// the eight link matrices of a site to lds, by its NK work-items (kk)
+template <typename T, int W>
+__device__ __forceinline__ void stage_site_links(const FieldRefs& f, const Site& st, const Nbrs<T>& n, int kk, int NK,
+                                                 C2<T>* lds) {
+    constexpr uint32_t CB = sizeof(C2<T>);
+    constexpr int LB = (W == 2) ? 18 : 9;
+    for (int i0 = 0; i0 * NK < 72; i0 += LB) {
+        C2<T> lk[LB];
+#pragma unroll
+        for (int i = 0; i < LB; ++i) {
+            const int id = min(kk + (i0 + i) * NK, 71), d = id / 9, e = id - 9 * d, mu = d & 3;
+            const int src = d < 4 ? st.site : (mu == 0 ? n.b[0] : mu == 1 ? n.b[1] : mu == 2 ? n.b[2] : n.b[3]);
+            lk[i] = Buf<T>::ld(f.U, (uint32_t)(src * 36 + mu * 9 + e) * CB, 0u);
+        }
+#pragma unroll
+        for (int i = 0; i < LB; ++i) {
+            const int id = min(kk + (i0 + i) * NK, 71), d = id / 9;
+            lds[d * LPAD + id - 9 * d] = lk[i];
+        }
+    }
+}
+// The hops of the site kernels: a gather issues a neighbour's loads, two hops before
+// they are used.
+#define HDCR_SITE_GATHER(MU, FWD, X)                                                                          \
+    {                                                                                                         \
+        const uint32_t noff = (uint32_t)((FWD ? n.f[MU] : n.b[MU]) * Ls + s0) * CB;                           \
+        __builtin_amdgcn_sched_barrier(0);                                                                    \
+        _Pragma("unroll") for (int c = 0; c < 12; ++c) X[c] = Wd::ld(f.in, noff, (uint32_t)c * f.cstride);    \
+        __builtin_amdgcn_sched_barrier(0);                                                                    \
+    }
+#define HDCR_SITE_HOP(MU, FWD, X)                                                                             \
+    {                                                                                                         \
+        C2<T> u[9], w[12];                                                                                    \
+        _Pragma("unroll") for (int e = 0; e < 9; ++e) u[e] = lnk[(FWD ? MU : 4 + MU) * LPAD + e];             \
+        _Pragma("unroll") for (int i = 0; i < W; ++i) {                                                       \
+            _Pragma("unroll") for (int c = 0; c < 12; ++c) w[c] = Wd::slice(X[c], i);                         \
+            hop_core<T, MU, FWD>(w, u, FWD ? n.cf[MU] : n.cb[MU], a[i]);                                      \
+        }                                                                                                     \
+    }
 template <typename T, int W, int NY>
 __global__ void __launch_bounds__(256) dslash_site_kernel(FineGeom g, SiteSplit ss, const C2<T>* U, const C2<T>* in,
                                                           C2<T>* out, Epi<T> ep) {
@@ -1124,21 +1163,7 @@ __global__ void __launch_bounds__(256) dslash_site_kernel(FineGeom g, SiteSplit 
     f.in = make_rsrc(in, 12u * f.cstride);
     f.out = make_rsrc(out, 12u * f.cstride);
     f.U = make_rsrc(U, (uint32_t)g.V4 * 36u * CB);
-    constexpr int LB = (W == 2) ? 18 : 9;
-    for (int i0 = 0; i0 * NK < 72; i0 += LB) {
-        C2<T> lk[LB];
-#pragma unroll
-        for (int i = 0; i < LB; ++i) {
-            const int id = min(kk + (i0 + i) * NK, 71), d = id / 9, e = id - 9 * d, mu = d & 3;
-            const int src = d < 4 ? st.site : (mu == 0 ? n.b[0] : mu == 1 ? n.b[1] : mu == 2 ? n.b[2] : n.b[3]);
-            lk[i] = Buf<T>::ld(f.U, (uint32_t)(src * 36 + mu * 9 + e) * CB, 0u);
-        }
-#pragma unroll
-        for (int i = 0; i < LB; ++i) {
-            const int id = min(kk + (i0 + i) * NK, 71), d = id / 9;
-            lds[(j * 8 + d) * LPAD + id - 9 * d] = lk[i];
-        }
-    }
+    stage_site_links<T, W>(f, st, n, kk, NK, lds + j * 8 * LPAD);
     const int s0 = W * kk;
     const uint32_t o0 = (uint32_t)(st.site * Ls + s0) * CB;
     C2<T> v[W][12];
@@ -1149,6 +1174,9 @@ __global__ void __launch_bounds__(256) dslash_site_kernel(FineGeom g, SiteSplit 
 #pragma unroll
         for (int i = 0; i < W; ++i) v[i][c] = Wd::slice(q, i);
     }
+    Word x0[12], x1[12];
+    HDCR_SITE_GATHER(0, true, x0)
+    HDCR_SITE_GATHER(0, false, x1)
     __syncthreads();
     if (!active) return;
     const C2<T>* lnk = lds + j * 8 * LPAD;
@@ -1174,27 +1202,20 @@ __global__ void __launch_bounds__(256) dslash_site_kernel(FineGeom g, SiteSplit 
             }
         }
     }
-#define HDCR_SITE_HOP(MU, FWD)                                                                                \
-    {                                                                                                         \
-        const uint32_t noff = (uint32_t)((FWD ? n.f[MU] : n.b[MU]) * Ls + s0) * CB;                           \
-        C2<T> u[9];                                                                                           \
-        _Pragma("unroll") for (int e = 0; e < 9; ++e) u[e] = lnk[(FWD ? MU : 4 + MU) * LPAD + e];             \
-        _Pragma("unroll") for (int c = 0; c < 12; ++c) {                                                      \
-            const Word q = Wd::ld(f.in, noff, (uint32_t)c * f.cstride);                                       \
-            _Pragma("unroll") for (int i = 0; i < W; ++i) v[i][c] = Wd::slice(q, i);                          \
-        }                                                                                                     \
-        _Pragma("unroll") for (int i = 0; i < W; ++i)                                                         \
-            hop_core<T, MU, FWD>(v[i], u, FWD ? n.cf[MU] : n.cb[MU], a[i]);                                   \
-    }
-    HDCR_SITE_HOP(0, true)
-    HDCR_SITE_HOP(0, false)
-    HDCR_SITE_HOP(1, true)
-    HDCR_SITE_HOP(1, false)
-    HDCR_SITE_HOP(2, true)
-    HDCR_SITE_HOP(2, false)
-    HDCR_SITE_HOP(3, true)
-    HDCR_SITE_HOP(3, false)
-#undef HDCR_SITE_HOP
+    HDCR_SITE_HOP(0, true, x0)
+    HDCR_SITE_GATHER(1, true, x0)
+    HDCR_SITE_HOP(0, false, x1)
+    HDCR_SITE_GATHER(1, false, x1)
+    HDCR_SITE_HOP(1, true, x0)
+    HDCR_SITE_GATHER(2, true, x0)
+    HDCR_SITE_HOP(1, false, x1)
+    HDCR_SITE_GATHER(2, false, x1)
+    HDCR_SITE_HOP(2, true, x0)
+    HDCR_SITE_GATHER(3, true, x0)
+    HDCR_SITE_HOP(2, false, x1)
+    HDCR_SITE_GATHER(3, false, x1)
+    HDCR_SITE_HOP(3, true, x0)
+    HDCR_SITE_HOP(3, false, x1)
     const uint32_t oo = (uint32_t)(st.site * Ls + (Ls - W - s0)) * CB;
     if constexpr (W == 2)
         store_pair<NY, false>(f, oo, ep, a[0], a[1]);
@@ -1327,10 +1348,10 @@ bool par_ok(const FineGeom& g) { return g.Ls == 16 && even_extents(g); }
 // slices a work-item would stage 18 or more link entries by itself, and above
 // 256 work-items a site does not fit the workgroup.  The LDS cap leaves room for
 // two workgroups per compute unit.
-template <typename T, int W> bool site_split(const FineGeom& g, SiteSplit& ss, int& lds) {
+template <typename T, int W> bool site_split(const FineGeom& g, SiteSplit& ss, int& lds, int least = 4) {
     const int per = (12 * g.Ls + 8 * LPAD) * (int)sizeof(C2<T>);  // LDS bytes per site
     ss.NK = g.Ls / W;
-    if (g.Ls < 4 || ss.NK > WG) return false;
+    if (g.Ls < least || ss.NK > WG) return false;
     ss.sites = WG / ss.NK;
     if (ss.sites * per > LDS_PER_CU / 2) ss.sites = LDS_PER_CU / 2 / per;
     lds = ss.sites * per;
@@ -1495,76 +1516,96 @@ bool dslash_h16_ok(const FineGeom& g) { return par_ok(g); }
 
 namespace {
 
-// Continued-fraction operator (Sec. 3): one work-item per 5d site (4d site j of
-// the workgroup, slice s), s fastest, k.sites whole 4d sites per workgroup.
-// The 8 link matrices of each site (U_mu(x), then U_mu(x - mu)) and the
-// workgroup's own spinors are staged in LDS: the slice couplings read their
-// partners psi(s -+ 1) from there, so only the 4d hops gather through the
-// vector-memory path.  Each output is written once, at its own slice.
-constexpr int CF_WG = 256;
-constexpr int CF_SITES_MAX = 16;
-
-template <typename T>
-__global__ void __launch_bounds__(CF_WG) cf_kernel(FineGeom g, CfCoef k, const C2<T>* U, const C2<T>* in, C2<T>* out) {
+// Continued-fraction operator (Sec. 3), any extents and Ls: the split of the domain
+// wall site kernel.  The slice couplings read their partners psi(s -+ 1) from the
+// staged spinors, and each output is written once, at its own slice.  Bound by the
+// neighbours' re-reads: 268 us at 24^4 x 9 in FP32 (2.2 TB/s of the two fields).
+template <typename T, int W>
+__global__ void __launch_bounds__(256) cf_site_kernel(FineGeom g, SiteSplit ss, CfCoef k, const C2<T>* U, const C2<T>* in,
+                                                      C2<T>* out) {
+    typedef SliceWord<T, W> Wd;
+    typedef typename Wd::type Word;
     constexpr uint32_t CB = sizeof(C2<T>);
-    __shared__ C2<T> lds[CF_SITES_MAX * 8 * LPAD];
-    __shared__ C2<T> spin[12 * CF_WG];  // [c][work-item]
-    const int Ls = g.Ls, m = Ls - 1;
-    const int lb = logical_block(blockIdx.x, gridDim.x);
-    const int tid = threadIdx.x;
-    const int j = tid / Ls, s = tid - (tid / Ls) * Ls;
-    const int lsite = lb * k.sites + j;
-    const bool active = (j < k.sites) && (lsite < g.V4);
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    const int Ls = g.Ls, m = Ls - 1, NK = ss.NK, row = ss.sites * NK;
+    Word* spin = reinterpret_cast<Word*>(smem_raw);          // [c][j][kk]
+    C2<T>* lds = reinterpret_cast<C2<T>*>(spin + 12 * row);  // [j][matrix][entry]
+    const int t = (int)threadIdx.x / NK, kk = (int)threadIdx.x - t * NK;
+    const int j = min(t, ss.sites - 1);  // work-items past the last site: as in dslash_site_kernel
+    const int lsite = logical_block(blockIdx.x, gridDim.x) * ss.sites + j;
+    const bool active = t < ss.sites && lsite < g.V4;
+    const Site st = traverse(g, min(lsite, g.V4 - 1));
+    const Nbrs<T> n = neighbours<T>(g, st);
     FieldRefs f;
     f.cstride = (uint32_t)g.N5 * CB;
     f.in = make_rsrc(in, 12u * f.cstride);
     f.out = make_rsrc(out, 12u * f.cstride);
     f.U = make_rsrc(U, (uint32_t)g.V4 * 36u * CB);
-    const Site st = traverse(g, active ? lsite : 0);
-    const Nbrs<T> n = neighbours<T>(g, st);
-    const uint32_t o0 = (uint32_t)(st.site * Ls + s) * CB;
-    C2<T> v[12];
-    if (active) {
-#pragma unroll
-        for (int c = 0; c < 12; ++c) {
-            v[c] = Buf<T>::ld(f.in, o0, (uint32_t)c * f.cstride);
-            spin[c * CF_WG + tid] = v[c];
-        }
-        // matrix d < 4: U_d(x); d >= 4: U_(d-4)(x - (d-4)); the site's Ls work-items share the loads
-        for (int q = s; q < 72; q += Ls) {
-            const int d = q / 9, e = q - 9 * (q / 9);
-            // a select, not n.b[d - 4]: a run-time index would put the neighbour table in scratch
-            const int src = (d < 4) ? st.site : (d == 4 ? n.b[0] : d == 5 ? n.b[1] : d == 6 ? n.b[2] : n.b[3]);
-            lds[(j * 8 + d) * LPAD + e] = Buf<T>::ld(f.U, (uint32_t)(src * 36 + (d & 3) * 9 + e) * CB, 0u);
-        }
-    }
-    __syncthreads();
-    if (!active) return;
+    stage_site_links<T, W>(f, st, n, kk, NK, lds + j * 8 * LPAD);
+    const int s0 = W * kk;
+    const uint32_t o0 = (uint32_t)(st.site * Ls + s0) * CB;
+    C2<T> a[W][12];
     // D_W(-M5) psi_s: diagonal 4 - M5, then the eight 4d hops
-    C2<T> acc[12];
     const T wd = (T)k.wdiag;
 #pragma unroll
-    for (int c = 0; c < 12; ++c) acc[c] = cscale<T>(wd, v[c]);
+    for (int c = 0; c < 12; ++c) {
+        const Word q = Wd::ld(f.in, o0, (uint32_t)c * f.cstride);
+        spin[c * row + j * NK + kk] = q;
+#pragma unroll
+        for (int i = 0; i < W; ++i) a[i][c] = cscale<T>(wd, Wd::slice(q, i));
+    }
+    Word x0[12], x1[12];
+    HDCR_SITE_GATHER(0, true, x0)
+    HDCR_SITE_GATHER(0, false, x1)
+    __syncthreads();
+    if (!active) return;
     const C2<T>* lnk = lds + j * 8 * LPAD;
-    hop_pair_lds<T, 0>(f, n, Ls, s, lnk, acc);
-    hop_pair_lds<T, 1>(f, n, Ls, s, lnk, acc);
-    hop_pair_lds<T, 2>(f, n, Ls, s, lnk, acc);
-    hop_pair_lds<T, 3>(f, n, Ls, s, lnk, acc);
-    // sigma_s gamma5 D_W psi_s + [s = m] R gamma5 psi_s + couplings to the neighbouring slices
-    const T sg = (T)k.sigma[s];
-    const T rr = (s == m) ? (T)k.R : (T)0;
-    const T cd = (T)k.cdn[s], cu = (T)k.cup[s];
-    const int td = (s > 0) ? tid - 1 : tid, tu = (s < m) ? tid + 1 : tid;
+    HDCR_SITE_HOP(0, true, x0)
+    HDCR_SITE_GATHER(1, true, x0)
+    HDCR_SITE_HOP(0, false, x1)
+    HDCR_SITE_GATHER(1, false, x1)
+    HDCR_SITE_HOP(1, true, x0)
+    HDCR_SITE_GATHER(2, true, x0)
+    HDCR_SITE_HOP(1, false, x1)
+    HDCR_SITE_GATHER(2, false, x1)
+    HDCR_SITE_HOP(2, true, x0)
+    HDCR_SITE_GATHER(3, true, x0)
+    HDCR_SITE_HOP(2, false, x1)
+    HDCR_SITE_GATHER(3, false, x1)
+    HDCR_SITE_HOP(3, true, x0)
+    HDCR_SITE_HOP(3, false, x1)
+    // sigma_s gamma5 D_W psi_s + [s = m] R gamma5 psi_s + couplings to the neighbouring
+    // slices (0 at s = 0 and s = m)
+    T sg[W], rr[W], cd[W], cu[W];
+#pragma unroll
+    for (int i = 0; i < W; ++i) {
+        sg[i] = (T)k.sigma[s0 + i];
+        rr[i] = (s0 + i == m) ? (T)k.R : (T)0;
+        cd[i] = (T)k.cdn[s0 + i];
+        cu[i] = (T)k.cup[s0 + i];
+    }
+    const int kd = kk > 0 ? kk - 1 : kk, ku = kk < NK - 1 ? kk + 1 : kk;
 #pragma unroll
     for (int c = 0; c < 12; ++c) {
         const T g5 = (c < 6) ? (T)1 : (T)-1;
-        C2<T> o = cscale<T>(g5 * sg, acc[c]);
-        axpy<T>(g5 * rr, v[c], o);
-        axpy<T>(cd, spin[c * CF_WG + td], o);
-        axpy<T>(cu, spin[c * CF_WG + tu], o);
-        Buf<T>::st_nt(o, f.out, o0, (uint32_t)c * f.cstride);
+        const Word* sp = spin + c * row + j * NK;
+        const Word own = sp[kk], dn = sp[kd], up = sp[ku];
+        C2<T> o[W];
+#pragma unroll
+        for (int i = 0; i < W; ++i) {
+            o[i] = cscale<T>(g5 * sg[i], a[i][c]);
+            axpy<T>(g5 * rr[i], Wd::slice(own, i), o[i]);
+            axpy<T>(cd[i], i > 0 ? Wd::slice(own, i > 0 ? i - 1 : 0) : Wd::slice(dn, W - 1), o[i]);
+            axpy<T>(cu[i], i < W - 1 ? Wd::slice(own, i < W - 1 ? i + 1 : i) : Wd::slice(up, 0), o[i]);
+        }
+        if constexpr (W == 2)
+            st_pair_nt(make_float4(o[0].x, o[0].y, o[1].x, o[1].y), f.out, o0, (uint32_t)c * f.cstride);
+        else
+            Buf<T>::st_nt(o[0], f.out, o0, (uint32_t)c * f.cstride);
     }
 }
+#undef HDCR_SITE_HOP
+#undef HDCR_SITE_GATHER
 
 // Continued-fraction operator on 2^4 parity tiles (even extents, Ls <= 16): the
 // tile scheme of the domain wall kernels.  A workgroup holds one tile, 16 sites
@@ -1717,13 +1758,28 @@ __global__ void __launch_bounds__(16 * CFT_LS / W) __attribute__((amdgpu_waves_p
 
 }  // namespace
 
+template <typename T, int W>
+void launch_cf_site(const FineGeom& g, const CfCoef& k, const C2<T>* U, const C2<T>* in, C2<T>* out, hipStream_t s) {
+    SiteSplit ss;
+    int lds;
+    if (!site_split<T, W>(g, ss, lds, 1)) return;  // not reachable: Ls <= CF_MAX_LS
+    hipLaunchKernelGGL((cf_site_kernel<T, W>), dim3((g.V4 + ss.sites - 1) / ss.sites), dim3(ss.sites * ss.NK), lds, s, g,
+                       ss, k, U, in, out);
+}
+
 template <typename T>
 void launch_cf(const FineGeom& g, const CfCoef& k, const C2<T>* U, const C2<T>* in, C2<T>* out, hipStream_t s) {
-    // parity tiles for even extents and Ls <= 16 (paired slices in FP32 with even
-    // Ls; tune.dslash_variant 4: one slice per work-item), else one work-item
-    // per 5d site (tune.dslash_variant 2 forces it)
-    const bool tiles = g.variant != 2 && g.Ls <= CFT_LS && g.L[0] % 2 == 0 && g.L[1] % 2 == 0 && g.L[2] % 2 == 0 &&
-                       g.L[3] % 2 == 0;
+    // Even extents with Ls = 16: parity tiles (paired slices in FP32; 347 against 368 us
+    // at 24^4, 67 against 72 at 16^4; FP64 144 against 147).  Otherwise the site kernel
+    // (24^4 x 9: 268 against 351 us in FP32, 434 against 560 in FP64; 24^4 x 8: 212
+    // against 235; 16^4 x 2: 24 against 49), but for Ls near 16: tiles in FP32 from 12 on
+    // below SITE_PAIRS 5d sites (16^4 x 12: 55 against 58 us; 24^4 x 12: 355 against 312),
+    // and in FP64 at 12 from there on (24^4: 554 against 564 us; 16^4: 111 against 107).
+    // tune.dslash_variant 2 forces the site kernel, 4 the tiles with one slice per
+    // work-item where Ls <= 16.
+    const bool big = g.N5 >= SITE_PAIRS;
+    const bool pick = g.Ls == 16 || (sizeof(T) == 4 ? g.Ls >= 12 && !big : g.Ls == 12 && big);
+    const bool tiles = g.variant != 2 && g.Ls <= CFT_LS && even_extents(g) && (pick || g.variant == 4);
     if (tiles) {
         const TileGeom tg = tile_geom(g);
         if constexpr (sizeof(T) == 4) {
@@ -1736,8 +1792,10 @@ void launch_cf(const FineGeom& g, const CfCoef& k, const C2<T>* U, const C2<T>* 
         hipLaunchKernelGGL((cf_tile_kernel<T, 1>), dim3(tg.t.V4), dim3(16 * g.Ls), 0, s, g, tg, k, U, in, out);
         return;
     }
-    const int blocks = (g.V4 + k.sites - 1) / k.sites;
-    hipLaunchKernelGGL((cf_kernel<T>), dim3(blocks), dim3(k.sites * g.Ls), 0, s, g, k, U, in, out);
+    if constexpr (sizeof(T) == 4) {
+        if (g.Ls % 2 == 0 && big) return launch_cf_site<float, 2>(g, k, U, in, out, s);
+    }
+    launch_cf_site<T, 1>(g, k, U, in, out, s);
 }
 
 template void launch_cf<double>(const FineGeom&, const CfCoef&, const double2*, const double2*, double2*, hipStream_t);

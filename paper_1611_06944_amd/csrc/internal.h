@@ -252,7 +252,6 @@ struct CfCoef {
     double cup[CF_MAX_LS];  // coupling to slice s + 1 (0 at s = m)
     double R;
     double wdiag;
-    int sites;
 };
 template <typename T>
 void launch_cf(const FineGeom& g, const CfCoef& k, const C2<T>* U, const C2<T>* in, C2<T>* out, hipStream_t s);

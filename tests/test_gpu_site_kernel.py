@@ -71,3 +71,36 @@ def test_slice_pairs_match_single_slices():
     ref = hd.apply_fine(lat.with_tune(dslash_variant=2), U, x)
     assert float((got - ref).abs().max()) <= 1e-6 * float(ref.abs().max())
     assert torch.equal(got, hd.apply_fine(lat, U, x))
+
+
+@pytest.mark.parametrize("L,m", [((3, 5, 2, 3), 1), ((2, 4, 2, 2), 2), ((4, 2, 2, 6), 7), ((1, 3, 2, 2), 11),
+                                 ((2, 3, 3, 2), 12), ((2, 2, 1, 1), 63)])
+def test_continued_fraction_site_kernel(L, m):
+    """Ls = 2 (sites capped by LDS), 3, 8, 12, 13 and 64: ragged last workgroups, extent 1, idle
+    work-items.  The slice pairs are taken on large lattices only, so they are held against single
+    slices there; sums of about 10^2 roundings of 2^-24."""
+    torch = torch_dev()
+    Ls, bc, M5, R = m + 1, (1, -1, 1, -1), 1.7, 0.35
+    log(f"cf site kernel L={L} m={m}")
+    beta = list(0.2 + 2.0 * np.random.default_rng(m).random(m))
+    U = hi.gauge_field(L, seed=8)
+    x = hi.gaussian_fermion(L, Ls, seed=9)
+    ref = oracle.apply_cf(U, x, M5, beta, R, bc)
+    lat = hd.Lattice(L, Ls, M5=M5, bc=bc)
+    for dt, tol in ((torch.complex128, 1e-10), (torch.complex64, 1e-5)):
+        out = hd.apply_cf(lat, to_dev(hd.pack_gauge(U), dt), to_dev(hd.pack_fermion(x), dt), beta, R)
+        assert max_rel_elem(hd.unpack_fermion(to_host(out), L, Ls), ref) <= tol, dt
+
+
+def test_continued_fraction_slice_pairs():
+    torch = torch_dev()
+    L, Ls = (16, 16, 16, 18), 18  # 1.3M 5d sites
+    log("cf slice pairs")
+    lat = hd.Lattice(L, Ls, M5=1.7, bc=(1, -1, 1, -1))
+    U = to_dev(hd.pack_gauge(hi.gauge_field(L, seed=2)))
+    g = torch.Generator(device="cuda").manual_seed(6)
+    x = torch.randn((12, lat.V4, Ls), dtype=torch.complex128, device="cuda", generator=g)
+    beta = list(0.3 + 0.1 * np.arange(Ls - 1))
+    ref = hd.apply_cf(lat, U, x, beta, 0.35)  # FP64: single slices
+    got = hd.apply_cf(lat, U.to(torch.complex64), x.to(torch.complex64), beta, 0.35)
+    assert float((got - ref).abs().max()) <= 1e-5 * float(ref.abs().max())
