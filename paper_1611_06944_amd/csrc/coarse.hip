@@ -667,100 +667,173 @@ template <> __device__ __forceinline__ float2 ldA<float, uint32_t>(const uint32_
     return make_float2(__uint_as_float(w << 16), __uint_as_float(w & 0xffff0000u));
 }
 
-// E consecutive entries A[.][k][j..j+E) with one 16-byte load (E = 16 / entry
-// size; E = 1 falls back to single-entry loads)
-template <typename T, typename S, int E> struct WideA;
-template <typename T, typename S> struct WideA<T, S, 1> {
-    static __device__ __forceinline__ void ld(const S* p, C2<T> (&e)[1]) { e[0] = ldA<T, S>(p, 0); }
-};
-template <> struct WideA<double, double2, 1> {
-    static __device__ __forceinline__ void ld(const double2* p, double2 (&e)[1]) { e[0] = *p; }
-};
-template <> struct WideA<float, float2, 2> {
-    static __device__ __forceinline__ void ld(const float2* p, float2 (&e)[2]) {
-        const float4 q = *reinterpret_cast<const float4*>(p);
-        e[0] = make_float2(q.x, q.y);
-        e[1] = make_float2(q.z, q.w);
-    }
-};
-template <> struct WideA<float, uint32_t, 4> {
-    static __device__ __forceinline__ void ld(const uint32_t* p, float2 (&e)[4]) {
-        const uint4 q = *reinterpret_cast<const uint4*>(p);
-        const uint32_t w[4] = {q.x, q.y, q.z, q.w};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) e[i] = make_float2(__uint_as_float(w[i] << 16), __uint_as_float(w[i] & 0xffff0000u));
-    }
-};
+// entries in a 16-byte load of A
 template <typename S> constexpr int wide_entries() { return (int)(16 / sizeof(S)); }
 
-// res[j] = sum_d sum_k A[a][d][k][j] vs[d][k] for one coarse site a (one
-// workgroup).  Work-item t covers E consecutive rows j (t % (Nb/E)) and the
-// columns k = kk, kk + kg, ... (kk = t / (Nb/E), kg = CWG / (Nb/E) groups), so
-// every load of A is a contiguous 16-byte run and a work-item issues
-// 9 Nb / kg independent loads; the kg partial sums are added in a fixed order.
-// red: LDS of CWG * E complex; ends with a barrier.
-template <typename T, typename S, int E>
-__device__ __forceinline__ void site_gemv(const CoarseGeom& c, const S* __restrict__ A, int a, const C2<T>* vs,
-                                          C2<T>* red, C2<T>* res) {
-    const int Nb = c.Nb;
-    const int nj = Nb / E;
-    const int kg = CWG / nj;
-    const int t = threadIdx.x;
-    const int jq = t % nj, kk = t / nj;
-    C2<T> acc[E];
+// 16 bytes of A as loaded, and the entries in them
+template <typename T, typename S, int E> struct RawA;
+template <> struct RawA<double, double2, 1> {
+    double2 w;
+    __device__ __forceinline__ double2 get(int) const { return w; }
+};
+template <> struct RawA<float, float2, 1> {
+    float2 w;
+    __device__ __forceinline__ float2 get(int) const { return w; }
+};
+template <> struct RawA<float, float2, 2> {
+    float4 w;
+    __device__ __forceinline__ float2 get(int q) const { return q ? make_float2(w.z, w.w) : make_float2(w.x, w.y); }
+};
+template <> struct RawA<float, uint32_t, 1> {
+    uint32_t w;
+    __device__ __forceinline__ float2 get(int) const {
+        return make_float2(__uint_as_float(w << 16), __uint_as_float(w & 0xffff0000u));
+    }
+};
+template <> struct RawA<float, uint32_t, 4> {
+    uint4 w;
+    __device__ __forceinline__ float2 get(int q) const {
+        const uint32_t v = q == 0 ? w.x : q == 1 ? w.y : q == 2 ? w.z : w.w;
+        return make_float2(__uint_as_float(v << 16), __uint_as_float(v & 0xffff0000u));
+    }
+};
+
+// a coarse site's nine neighbours, one to a lane (lanes 0 .. 8 of every wavefront)
+__device__ __forceinline__ int lane_nbrs(const CoarseGeom& c, int a) {
+    const int d = min((int)threadIdx.x & 63, 8), mu = (d - 1) & 3;
+    const int st = mu == 0 ? c.cstride[0] : mu == 1 ? c.cstride[1] : mu == 2 ? c.cstride[2] : c.cstride[3];
+    const int C = mu == 0 ? c.C[0] : mu == 1 ? c.C[1] : mu == 2 ? c.C[2] : c.C[3];
+    const int xm = ((unsigned)a / (unsigned)st) % (unsigned)C;
+    const int up = xm == C - 1 ? a - xm * st : a + st, dn = xm == 0 ? a + (C - 1) * st : a - st;
+    return d == 0 ? a : d <= 4 ? up : dn;
+}
+
+// out[r] = A v[r] for R right-hand sides at one coarse site per workgroup.  The site's
+// matrix is 9 Nb rows (d, k) of Nb entries j; work-item t covers E consecutive j (t %
+// (Nb/E)) of the rows kk, kk + kg, ... (kk = t / (Nb/E), kg = CWG / (Nb/E) groups), with
+// PB 16-byte loads in flight, the first of them before the vectors are staged; the kg
+// partial sums are added in a fixed order.  One R or another, an output takes the same
+// products in the same order, so the results agree bit for bit.
+// Bound by A for one right-hand side (8192 sites, Nb = 32: 101 us in C64, 50 in BF16),
+// by the FMAs and their LDS reads for many (256 sites, Nb = 48, 12 right-hand sides: 15.0
+// us in C64, 25 in C128; 1296 sites, Nb = 64, 24: 160 us).  Loads two at a time behind the staged vectors took 107, 58, 32.7, 62 and 323 us.
+struct ApplySplit {
+    int kg;        // row groups
+    int ng;        // groups of R right-hand sides
+    int rnj, rnb;  // ceil(2^20 / (Nb / E)), ceil(2^20 / Nb): e / n = (e r) >> 20 for e n < 2^20
+};
+template <typename T, typename S, int E, int R, int PB>
+__global__ void __launch_bounds__(CWG) coarse_apply_kernel(CoarseGeom c, ApplySplit sp, const S* __restrict__ A,
+                                                           const C2<T>* __restrict__ v, C2<T>* __restrict__ out,
+                                                           int nrhs) {
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    struct alignas(sizeof(C2<T>) * (R % 2 == 0 && sizeof(T) == 4 ? 2 : 1)) Row {
+        C2<T> x[R];
+    };
+    Row* vs = reinterpret_cast<Row*>(smem_raw);      // [9 Nb]: the vectors at the site's neighbours
+    C2<T>* red = reinterpret_cast<C2<T>*>(smem_raw);  // then [R][kg][Nb]
+    const int Nb = c.Nb, nrow = 9 * Nb, kg = sp.kg, t = threadIdx.x;
+    const int lb = logical_block(blockIdx.x, gridDim.x), a = lb / sp.ng, r0 = (lb - a * sp.ng) * R;
+    const int nr = min(R, nrhs - r0);
+    const int kt = (t * sp.rnj) >> 20, jq = t - kt * (Nb / E), kk = min(kt, kg - 1);
+    typedef RawA<T, S, E> Raw;
+    Raw buf[PB];
+    const S* As = A + (size_t)a * nrow * Nb;
+    auto load = [&](int row) { return *reinterpret_cast<const Raw*>(As + (unsigned)(min(row, nrow - 1) * Nb + jq * E)); };
 #pragma unroll
-    for (int q = 0; q < E; ++q) acc[q] = mk<T>(0, 0);
-    if (kk < kg) {
-        const size_t blk = (size_t)Nb * Nb;
-        const S* Aa = A + (size_t)a * 9 * blk + (size_t)jq * E;
-        for (int d = 0; d < 9; ++d) {
-            const S* Ad = Aa + d * blk;
-            const C2<T>* vd = vs + d * Nb;
-#pragma unroll 4
-            for (int k = kk; k < Nb; k += kg) {
-                C2<T> e[E];
-                WideA<T, S, E>::ld(Ad + (size_t)k * Nb, e);
-                const C2<T> x = vd[k];
+    for (int u = 0; u < PB; ++u) buf[u] = load(kk + u * kg);
+    const int nv = lane_nbrs(c, a);
+    for (int i0 = 0; i0 < nrow; i0 += CWG) {
+        const int i = min(i0 + t, nrow - 1), d = (i * sp.rnb) >> 20;
+        const C2<T>* vi = v + (size_t)__shfl(nv, d) * Nb + (i - d * Nb);
+        C2<T> w[R];
 #pragma unroll
-                for (int q = 0; q < E; ++q) acc[q] = cfma<T>(e[q], x, acc[q]);
-            }
+        for (int r = 0; r < R; ++r) w[r] = vi[(size_t)(r0 + min(r, nr - 1)) * c.Nc * Nb];
+#pragma unroll
+        for (int r = 0; r < R; ++r) vs[i].x[r] = w[r];
+    }
+    __syncthreads();
+    C2<T> acc[R][E];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int q = 0; q < E; ++q) acc[r][q] = mk<T>(0, 0);
+    auto use = [&](const Raw& e, int row) {
+        C2<T> w[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) w[r] = vs[row].x[r];
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int q = 0; q < E; ++q) acc[r][q] = cfma<T>(e.get(q), w[r], acc[r][q]);
+    };
+    int row = kk;
+    for (int b = nrow / (kg * PB); b > 0; --b, row += kg * PB) {
+#pragma unroll
+        for (int u = 0; u < PB; ++u) {
+            use(buf[u], row + u * kg);
+            buf[u] = load(row + (PB + u) * kg);
         }
+    }
 #pragma unroll
-        for (int q = 0; q < E; ++q) red[kk * Nb + jq * E + q] = acc[q];
+    for (int u = 0; u < PB; ++u)
+        if (row + u * kg < nrow) use(buf[u], row + u * kg);
+    __syncthreads();
+    if (kt < kg) {
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int q = 0; q < E; ++q) red[(r * kg + kk) * Nb + jq * E + q] = acc[r][q];
     }
     __syncthreads();
-    for (int j = t; j < Nb; j += CWG) {
-        C2<T> sum = red[j];
-        for (int g = 1; g < kg; ++g) sum = cadd<T>(sum, red[g * Nb + j]);
-        res[j] = sum;
+    for (int o = t; o < nr * Nb; o += CWG) {
+        const int r = (o * sp.rnb) >> 20, j = o - r * Nb;
+        C2<T> sum = red[r * kg * Nb + j];
+#pragma unroll 4
+        for (int g = 1; g < kg; ++g) sum = cadd<T>(sum, red[(r * kg + g) * Nb + j]);
+        out[((size_t)(r0 + r) * c.Nc + a) * Nb + j] = sum;
     }
-    __syncthreads();
 }
 
-// LDS bytes of a coarse-apply workgroup: vs [9][Nb], red [CWG * E], res [Nb]
-template <typename T, int E> size_t apply_lds(const CoarseGeom& c) {
-    return (size_t)(10 * c.Nb + CWG * E) * sizeof(C2<T>);
+template <typename T, typename S, int E, int R> size_t apply_lds(const CoarseGeom& c) {
+    const int kg = CWG / (c.Nb / E);
+    return (size_t)R * std::max(9, kg) * c.Nb * sizeof(C2<T>);
 }
-
-// one workgroup per (coarse site, right-hand side); the neighbour vectors are
-// staged in LDS
+constexpr size_t APPLY_LDS_MAX = 80 * 1024;  // two workgroups per CU
+template <typename T, typename S, int E, int R>
+void coarse_apply_go(const CoarseGeom& c, const S* A, const C2<T>* v, C2<T>* out, int nrhs, hipStream_t s) {
+    const int nj = c.Nb / E, ng = (nrhs + R - 1) / R;
+    const ApplySplit sp{CWG / nj, ng, ((1 << 20) + nj - 1) / nj, ((1 << 20) + c.Nb - 1) / c.Nb};
+    hipLaunchKernelGGL((coarse_apply_kernel<T, S, E, R, 8>), dim3((unsigned)(c.Nc * ng)), dim3(CWG),
+                       (apply_lds<T, S, E, R>(c)), s, c, sp, A, v, out, nrhs);
+}
+// the R of least work: right-hand sides taken, idle ones included, and two for the reads
+// of A (in us, C64: 256 sites, Nb = 48, 12 right-hand sides R = 4, 6, 8: 14.2, 14.8, 17.9;
+// 8192 sites, Nb = 32, 8: 147, 165, 134; 1296 sites, Nb = 64, 24: 168, 153, 157; one: 393)
 template <typename T, typename S, int E>
-__global__ void __launch_bounds__(CWG) coarse_apply_kernel(CoarseGeom c, const S* __restrict__ A,
-                                                           const C2<T>* __restrict__ v, C2<T>* __restrict__ out) {
-    extern __shared__ unsigned char smem_raw[];
-    C2<T>* vs = reinterpret_cast<C2<T>*>(smem_raw);   // [9][Nb]
-    C2<T>* res = vs + 9 * c.Nb;                        // [Nb]
-    C2<T>* red = res + c.Nb;                           // [CWG * E]
-    const int a = blockIdx.x;
-    const int rhs = blockIdx.y;
-    const C2<T>* vr = v + (size_t)rhs * c.Nc * c.Nb;
-    for (int e = threadIdx.x; e < 9 * c.Nb; e += CWG) {
-        const int d = e / c.Nb, k = e - d * c.Nb;
-        vs[e] = vr[(size_t)coarse_nbr(c, a, d) * c.Nb + k];
+void coarse_apply_pick(const CoarseGeom& c, const S* A, const C2<T>* v, C2<T>* out, int nrhs, hipStream_t s) {
+    int best = 1, cost = nrhs * 3;
+    auto look = [&](auto rc) {
+        constexpr int R = decltype(rc)::value;
+        const int k = (nrhs + R - 1) / R * (R + 2);
+        if (k < cost && apply_lds<T, S, E, R>(c) <= APPLY_LDS_MAX) {
+            cost = k;
+            best = R;
+        }
+    };
+    look(std::integral_constant<int, 2>{});
+    look(std::integral_constant<int, 3>{});
+    look(std::integral_constant<int, 4>{});
+    look(std::integral_constant<int, 6>{});
+    look(std::integral_constant<int, 8>{});
+    switch (best) {
+        case 1: return coarse_apply_go<T, S, E, 1>(c, A, v, out, nrhs, s);
+        case 2: return coarse_apply_go<T, S, E, 2>(c, A, v, out, nrhs, s);
+        case 3: return coarse_apply_go<T, S, E, 3>(c, A, v, out, nrhs, s);
+        case 4: return coarse_apply_go<T, S, E, 4>(c, A, v, out, nrhs, s);
+        case 6: return coarse_apply_go<T, S, E, 6>(c, A, v, out, nrhs, s);
+        default: return coarse_apply_go<T, S, E, 8>(c, A, v, out, nrhs, s);
     }
-    __syncthreads();
-    site_gemv<T, S, E>(c, A, a, vs, red, res);
-    for (int j = threadIdx.x; j < c.Nb; j += CWG) out[((size_t)rhs * c.Nc + a) * c.Nb + j] = res[j];
 }
 
 // ---------------------------------------------------------------------------
@@ -961,34 +1034,6 @@ __global__ void __launch_bounds__(CWG) ccr_init_defl_kernel(int n, const C2<T>* 
     }
 }
 
-// 16 bytes of A as loaded, and the entries in them
-template <typename T, typename S, int E> struct RawA;
-template <> struct RawA<double, double2, 1> {
-    double2 w;
-    __device__ __forceinline__ double2 get(int) const { return w; }
-};
-template <> struct RawA<float, float2, 1> {
-    float2 w;
-    __device__ __forceinline__ float2 get(int) const { return w; }
-};
-template <> struct RawA<float, float2, 2> {
-    float4 w;
-    __device__ __forceinline__ float2 get(int q) const { return q ? make_float2(w.z, w.w) : make_float2(w.x, w.y); }
-};
-template <> struct RawA<float, uint32_t, 1> {
-    uint32_t w;
-    __device__ __forceinline__ float2 get(int) const {
-        return make_float2(__uint_as_float(w << 16), __uint_as_float(w & 0xffff0000u));
-    }
-};
-template <> struct RawA<float, uint32_t, 4> {
-    uint4 w;
-    __device__ __forceinline__ float2 get(int q) const {
-        const uint32_t v = q == 0 ? w.x : q == 1 ? w.y : q == 2 ? w.z : w.w;
-        return make_float2(__uint_as_float(v << 16), __uint_as_float(v & 0xffff0000u));
-    }
-};
-
 // Sums of five values over the workgroup, the same in every work-item: over rows of 16
 // lanes by data-parallel moves (each lane ends with the row's sum, added in the same
 // tree in every lane), then over the rows through sh.  One barrier, where a tree in LDS
@@ -1094,17 +1139,8 @@ ccr_step_kernel(CoarseGeom c, CcrSplit sp, const S* __restrict__ A, CcrFields<T>
         dv[u] = (e * sp.rnb) >> 20;
         kv[u] = e - dv[u] * Nb;
     }
-    // lane d < 9: the site's neighbour d
-    auto nbrs = [&](int a) {
-        const int d = min(t & 63, 8), mu = (d - 1) & 3;
-        const int st = mu == 0 ? c.cstride[0] : mu == 1 ? c.cstride[1] : mu == 2 ? c.cstride[2] : c.cstride[3];
-        const int C = mu == 0 ? c.C[0] : mu == 1 ? c.C[1] : mu == 2 ? c.C[2] : c.C[3];
-        const int xm = ((unsigned)a / (unsigned)st) % (unsigned)C;
-        const int up = xm == C - 1 ? a - xm * st : a + st, dn = xm == 0 ? a + (C - 1) * st : a - st;
-        return d == 0 ? a : d <= 4 ? up : dn;
-    };
     auto fetch = [&](int a) {
-        const int nv = nbrs(a);
+        const int nv = lane_nbrs(c, a);
 #pragma unroll
         for (int u = 0; u < VR; ++u) {
             const size_t i = (size_t)__shfl(nv, dv[u]) * Nb + kv[u];
@@ -1194,7 +1230,7 @@ ccr_step_kernel(CoarseGeom c, CcrSplit sp, const S* __restrict__ A, CcrFields<T>
         for (int u = 0; u < VR; ++u)
             if (t + u * CWG < nrow) stage(t + u * CWG, ro[u], aro[u], apo[u]);
         if (nrow > VR * CWG) {
-            const int nv = nbrs(a);
+            const int nv = lane_nbrs(c, a);
             for (int e0 = VR * CWG; e0 < nrow; e0 += CWG) {
                 const int e = min(e0 + t, nrow - 1), d = (e * sp.rnb) >> 20;
                 const size_t i = (size_t)__shfl(nv, d) * Nb + (e - d * Nb);
@@ -1838,118 +1874,13 @@ void launch_prolong_h(const CoarseGeom& c, const uint32_t* basis, const float2* 
                            v, y, psi);
 }
 
-namespace {
-
-// The same for R right-hand sides per work-group (blockIdx.y = group of R):
-// each A entry is read once for all R vectors.  Every output element takes the
-// same products in the same order as site_gemv (over d, then k in steps of kg
-// per thread, then the fixed sum over the kg thread groups), so the results
-// equal the one-vector kernel's bit for bit.
-template <typename T, typename S, int E, int R>
-__global__ void __launch_bounds__(CWG) coarse_apply_multi_kernel(CoarseGeom c, const S* __restrict__ A,
-                                                                 const C2<T>* __restrict__ v, C2<T>* __restrict__ out,
-                                                                 int nrhs) {
-    extern __shared__ unsigned char smem_raw[];
-    const int Nb = c.Nb;
-    C2<T>* vs = reinterpret_cast<C2<T>*>(smem_raw);  // [R][9][Nb]
-    C2<T>* red = vs + R * 9 * Nb;                    // [CWG * E]
-    const int a = blockIdx.x;
-    const int r0 = blockIdx.y * R;
-    const int nr = min(R, nrhs - r0);
-    const size_t nv = (size_t)c.Nc * Nb;
-    for (int e = threadIdx.x; e < R * 9 * Nb; e += CWG) {
-        const int r = e / (9 * Nb), rem = e - r * 9 * Nb;
-        const int d = rem / Nb, k = rem - d * Nb;
-        vs[e] = (r < nr) ? v[(size_t)(r0 + r) * nv + (size_t)coarse_nbr(c, a, d) * Nb + k] : mk<T>(0, 0);
-    }
-    __syncthreads();
-    const int nj = Nb / E;
-    const int kg = CWG / nj;
-    const int t = threadIdx.x;
-    const int jq = t % nj, kk = t / nj;
-    C2<T> acc[R][E];
-#pragma unroll
-    for (int r = 0; r < R; ++r)
-#pragma unroll
-        for (int q = 0; q < E; ++q) acc[r][q] = mk<T>(0, 0);
-    if (kk < kg) {
-        const size_t blk = (size_t)Nb * Nb;
-        const S* Aa = A + (size_t)a * 9 * blk + (size_t)jq * E;
-        for (int d = 0; d < 9; ++d) {
-            const S* Ad = Aa + d * blk;
-#pragma unroll 2
-            for (int k = kk; k < Nb; k += kg) {
-                C2<T> e[E];
-                WideA<T, S, E>::ld(Ad + (size_t)k * Nb, e);
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    const C2<T> x = vs[(r * 9 + d) * Nb + k];
-#pragma unroll
-                    for (int q = 0; q < E; ++q) acc[r][q] = cfma<T>(e[q], x, acc[r][q]);
-                }
-            }
-        }
-    }
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        if (r >= nr) break;  // nr is the same for the whole work-group
-        if (kk < kg) {
-#pragma unroll
-            for (int q = 0; q < E; ++q) red[kk * Nb + jq * E + q] = acc[r][q];
-        }
-        __syncthreads();
-        for (int j = t; j < Nb; j += CWG) {
-            C2<T> sum = red[j];
-            for (int g = 1; g < kg; ++g) sum = cadd<T>(sum, red[g * Nb + j]);
-            out[((size_t)(r0 + r) * c.Nc + a) * Nb + j] = sum;
-        }
-        __syncthreads();
-    }
-}
-
-constexpr size_t MULTI_LDS_MAX = 65536;
-template <typename T, int E, int R> size_t multi_lds(const CoarseGeom& c) {
-    return ((size_t)R * 9 * c.Nb + (size_t)CWG * E) * sizeof(C2<T>);
-}
-
-template <typename T, typename S, int E>
-bool coarse_apply_multi_launch(const CoarseGeom& c, const S* A, const C2<T>* v, C2<T>* out, int nrhs, hipStream_t s) {
-    if (nrhs >= 8 && multi_lds<T, E, 8>(c) <= MULTI_LDS_MAX) {
-        hipLaunchKernelGGL((coarse_apply_multi_kernel<T, S, E, 8>), dim3(c.Nc, (nrhs + 7) / 8), dim3(CWG),
-                           (multi_lds<T, E, 8>(c)), s, c, A, v, out, nrhs);
-        return true;
-    }
-    if (nrhs >= 4 && multi_lds<T, E, 4>(c) <= MULTI_LDS_MAX) {
-        hipLaunchKernelGGL((coarse_apply_multi_kernel<T, S, E, 4>), dim3(c.Nc, (nrhs + 3) / 4), dim3(CWG),
-                           (multi_lds<T, E, 4>(c)), s, c, A, v, out, nrhs);
-        return true;
-    }
-    if (nrhs >= 2 && multi_lds<T, E, 2>(c) <= MULTI_LDS_MAX) {
-        hipLaunchKernelGGL((coarse_apply_multi_kernel<T, S, E, 2>), dim3(c.Nc, (nrhs + 1) / 2), dim3(CWG),
-                           (multi_lds<T, E, 2>(c)), s, c, A, v, out, nrhs);
-        return true;
-    }
-    return false;
-}
-
-}  // namespace
-
 template <typename T, typename S>
 void coarse_apply_launch(const CoarseGeom& c, const S* A, const C2<T>* v, C2<T>* out, int nrhs, hipStream_t s) {
     constexpr int E = wide_entries<S>();
-    if (nrhs > 1) {
-        if (c.Nb % E == 0) {
-            if (coarse_apply_multi_launch<T, S, E>(c, A, v, out, nrhs, s)) return;
-        } else if (coarse_apply_multi_launch<T, S, 1>(c, A, v, out, nrhs, s)) {
-            return;
-        }
-    }
     if (c.Nb % E == 0)
-        hipLaunchKernelGGL((coarse_apply_kernel<T, S, E>), dim3(c.Nc, nrhs), dim3(CWG), (apply_lds<T, E>(c)), s, c,
-                           A, v, out);
+        coarse_apply_pick<T, S, E>(c, A, v, out, nrhs, s);
     else
-        hipLaunchKernelGGL((coarse_apply_kernel<T, S, 1>), dim3(c.Nc, nrhs), dim3(CWG), (apply_lds<T, 1>(c)), s, c,
-                           A, v, out);
+        coarse_apply_pick<T, S, 1>(c, A, v, out, nrhs, s);
 }
 
 template <typename T>

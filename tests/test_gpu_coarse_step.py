@@ -55,3 +55,27 @@ def test_steps_match_oracle(L, Ls, block, nvec):
             x, it, code = hd.coarse_solve(lat, A, dt, bd, maxiter=4, tol=0.0, return_status=True)
             assert code == 0 and it == 4 and ref.iters == 4
             assert max_rel_elem(to_host(x), ref.x) <= tol
+
+
+@pytest.mark.parametrize("L,Ls,block,nvec", [SHAPES[0], SHAPES[2], SHAPES[3], ((4, 6, 2, 2), 4, (2, 2, 2, 2), 24),
+                                             ((2, 4, 2, 2), 4, (1, 2, 2, 1), 5)])
+def test_apply_every_group_size(L, Ls, block, nvec):
+    """Right-hand sides in groups of 1, 2, 3, 4, 6 and 8, full and short, fewer of them where the vectors
+    do not fit LDS (Nb = 128 in FP64): against the oracle, and each against its own single apply bit for
+    bit.  9 Nb <= 1152 products to an entry: 1e-12 and 3e-5 of the largest entry."""
+    torch = torch_dev()
+    lat = hd.Lattice(L, Ls, block=block, nvec=nvec)
+    cdims = tuple(l // b for l, b in zip(L, block))
+    A64 = to_dev(np.ascontiguousarray(_operator(cdims, lat.nb, 5).swapaxes(2, 3)))
+    rng = np.random.default_rng(6)
+    v = rng.standard_normal((17, lat.nc, lat.nb)) + 1j * rng.standard_normal((17, lat.nc, lat.nb))
+    for dt, tol in ((hd.C128, 1e-12), (hd.C64, 3e-5), (hd.BF16C, 3e-5)):
+        log(f"coarse apply L={L} block={block} nvec={nvec} dtype={dt}")
+        A = A64 if dt == hd.C128 else hd.convert_coarse(lat, A64, dt)
+        vd = to_dev(v, torch.complex128 if dt == hd.C128 else torch.complex64)
+        A_log = to_host(hd.export_coarse(lat, A, dt))
+        ref = np.stack([oracle.coarse_apply(A_log, x.astype(np.complex128), cdims) for x in to_host(vd)])
+        one = torch.cat([hd.apply_coarse(lat, A, dt, vd[r:r + 1].contiguous()) for r in range(17)])
+        assert max_rel_elem(to_host(one), ref) <= tol
+        for n in (2, 3, 4, 5, 6, 7, 8, 9, 12, 17):
+            assert torch.equal(hd.apply_coarse(lat, A, dt, vd[:n].contiguous()), one[:n]), (dt, n)
