@@ -14,6 +14,7 @@ Device layouts (see ``include/hdcr.h``):
 from __future__ import annotations
 
 import ctypes
+import math
 from dataclasses import dataclass, replace
 
 import numpy as np
@@ -56,7 +57,7 @@ class Lattice:
 
     @property
     def V4(self):
-        return int(np.prod(self.L))
+        return math.prod(map(int, self.L))  # np.prod takes 4 us, and every call asks several times
 
     @property
     def N5(self):
@@ -72,7 +73,7 @@ class Lattice:
 
     @property
     def nc(self):
-        return int(np.prod(self.cdims))
+        return math.prod(self.cdims)
 
     @property
     def nb(self):
