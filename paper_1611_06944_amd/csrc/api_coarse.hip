@@ -141,20 +141,21 @@ int hdcr_build_coarse(const hdcr_coarse_desc* desc, const void* U, const void* v
     launch_basis_fold(c, static_cast<const double2*>(vecs), b64, stream);
     bool gs = !chq_ok(c);
     if (!gs) {
-        launch_chq_pass(c, b64, chq, 0, flag, stream);
+        launch_chq_round(c, b64, chq, 0, flag, stream);
         int hf[2] = {0, 0};
         HDCR_HIP_CHECK(hipMemcpyAsync(hf, flag + 1, 2 * sizeof(int), hipMemcpyDeviceToHost, stream));
         HDCR_HIP_CHECK(hipStreamSynchronize(stream));
         gs = hf[0] != 0;
         if (!gs) {
-            launch_chq_apply(c, b64, chq, stream);
-            launch_chq_pass(c, b64, chq, 1, flag, stream);
-            launch_chq_apply(c, b64, chq, stream);
+            launch_chq_round(c, b64, chq, 1, flag, stream);
+            launch_chq_finish(c, b64, chq, basis32(c, basis), basis16(c, basis), stream);
         }
     }
-    if (gs) launch_block_orth(c, b64, flag, stream);
-    launch_basis_to_f32(c, b64, basis32(c, basis), stream);
-    launch_basis_to_f16(c, b64, basis16(c, basis), stream);
+    if (gs) {
+        launch_block_orth(c, b64, flag, stream);
+        launch_basis_to_f32(c, b64, basis32(c, basis), stream);
+        launch_basis_to_f16(c, b64, basis16(c, basis), stream);
+    }
     HDCR_HIP_CHECK(hipGetLastError());
     // A = P^dag H P
     launch_coarse_build(c, b64, static_cast<const double2*>(U), Pp,

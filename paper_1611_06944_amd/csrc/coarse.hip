@@ -214,60 +214,180 @@ __global__ void __launch_bounds__(CWG) block_orth_kernel(CoarseGeom c, double2* 
 // chirality the Gram matrix G = V^dag V, its Cholesky factor R (G = R^dag R,
 // R upper triangular with a positive real diagonal, so V = Q R is the thin QR
 // in index order) and Q = V R^-1; the second round repeats this on Q, which
-// restores orthogonality to rounding.  It reads the vectors 6 times instead of
+// restores orthogonality to rounding.  It reads the vectors 3 times instead of
 // about 2 nvec times.  A pivot of the first round at most 1e-8 of its diagonal
 // entry (a vector whose part outside the span of the previous ones is below
 // 1e-4 of its norm) is out of reach of Cholesky QR in FP64; the caller then
 // runs the Gram-Schmidt kernel above, whose rank test stays the reference.
-constexpr int CHQ_MAXV = 32;   // vectors per block and chirality
-constexpr int CHQ_CH = 64;     // indices staged per step of the Gram kernel
-constexpr int CHQ_R = 2;       // Gram entries per work-item in each direction (16 x 16 work-items)
+// entries of the basis's FP32 copy and of its FP16 copy (HBASIS_SCALE * phi, rounded to
+// nearest even)
+__device__ __forceinline__ float2 to_f32(double2 v) { return make_float2((float)v.x, (float)v.y); }
+__device__ __forceinline__ uint32_t to_f16(double2 v) {
+    const _Float16 re = (_Float16)((float)(v.x * (double)HBASIS_SCALE));
+    const _Float16 im = (_Float16)((float)(v.y * (double)HBASIS_SCALE));
+    return (uint32_t)__builtin_bit_cast(unsigned short, re) | ((uint32_t)__builtin_bit_cast(unsigned short, im) << 16);
+}
 
-// partial Gram matrices: grid (2 Nc, parts); part z sums the indices of its
-// contiguous range, Gp[(ah * parts + z)][j][k] = sum_i conj(V_j[i]) V_k[i]
-__global__ void __launch_bounds__(CWG) chq_gram_kernel(CoarseGeom c, const double2* __restrict__ b64,
-                                                       double2* __restrict__ Gp) {
-    __shared__ double2 S[CHQ_MAXV][CHQ_CH + 1];
+constexpr int CHQ_MAXV = 32;   // vectors per block and chirality
+constexpr int CHQ_CH = 64;     // fewest indices of a part
+constexpr int CHQ_WAVES = CWG / 64;
+
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ f64x4 mfma64(double a, double b, f64x4 c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+
+// The passes over the vectors, on the FP64 matrix cores, with no LDS between them: a
+// wavefront takes 16 indices i of all vectors at a time, in parts (grid (2 Nc, parts)).
+// The product W = V Rinv has V as one operand (k = vector, 4 a step; m or n = index) and
+// Rinv, in registers, as the other (upper triangular: the first 16 columns take the first
+// 16 vectors only).  With the indices as rows, a lane ends with vector l % 16 at indices l
+// / 16 + 4 ii, which is both operands of the Gram product over the indices as it stands;
+// with the indices as columns it ends with 16 consecutive indices of a vector, for stores.
+//   CHQ_GRAM   Gp = partial Gram matrices of V
+//   CHQ_NEXT   V <- V Rinv, Gp = those of the new V
+//   CHQ_LAST   V <- V Rinv, and its FP32 and FP16 copies
+// Gp[ah * parts + z][j][k] = sum of part z of conj(V_j[i]) V_k[i], tiles with j <= k.
+// Bound by memory: at 16^4 x 16, nvec = 24, 4^4 blocks (4.8 GB) 1.35, 2.5 and 3.5 ms (3.6,
+// 3.8 and 3.7 TB/s).  Each product through LDS on the vector units took 3.0 ms for a Gram
+// pass, 4.3 for an apply and 2.5 for the copies: 17 ms in all.
+enum { CHQ_GRAM, CHQ_NEXT, CHQ_LAST };
+
+// KS: groups of four vectors
+template <int KS, int MODE>
+__global__ void __launch_bounds__(CWG) __attribute__((amdgpu_waves_per_eu(2)))
+chq_pass_kernel(CoarseGeom c, double2* b64, const double2* __restrict__ Rinv, double2* __restrict__ Gp,
+                float2* __restrict__ b32, uint32_t* __restrict__ b16) {
+    constexpr int NT = (KS + 3) / 4, NP = NT * (NT + 1) / 2;  // vector tiles and tile pairs
+    constexpr int NL = MODE == CHQ_GRAM ? 4 * NT : KS;         // loads per tile of indices
     const int ah = blockIdx.x, n = c.nvec, nh = c.nhalf;
-    const double2* V = b64 + (size_t)ah * n * nh;
-    const int nchunk = (nh + CHQ_CH - 1) / CHQ_CH;
-    const int cb = (int)(((long long)nchunk * blockIdx.y) / gridDim.y);
-    const int ce = (int)(((long long)nchunk * (blockIdx.y + 1)) / gridDim.y);
-    const int ty = threadIdx.x >> 4, tx = threadIdx.x & 15;
-    double2 acc[CHQ_R][CHQ_R];
+    const int lane = threadIdx.x & 63, q = lane >> 4, l = lane & 15, wave = threadIdx.x >> 6;
+    const size_t base = (size_t)ah * n * nh;
+    double2* V = b64 + base;
+    const int ntile = (nh + 15) / 16;
+    const int tb = (int)(((long long)ntile * blockIdx.y) / gridDim.y) + wave;
+    const int te = (int)(((long long)ntile * (blockIdx.y + 1)) / gridDim.y);
+    // nh is a multiple of 4, so a group of four indices is inside or outside as a whole;
+    // loads past the last vector or index repeat it
+    auto load = [&](int t, double2 (&x)[NL]) {
 #pragma unroll
-    for (int r = 0; r < CHQ_R; ++r)
+        for (int s = 0; s < NL; ++s) {
+            const int k = MODE == CHQ_GRAM ? (s / 4) * 16 + l : 4 * s + q;
+            const int i = 16 * t + (MODE == CHQ_GRAM ? 4 * (s % 4) + q : l);
+            x[s] = V[(size_t)min(k, n - 1) * nh + min(i, nh - 1)];
+        }
+    };
+    double2 R[NT][KS];
+    if constexpr (MODE != CHQ_GRAM) {
 #pragma unroll
-        for (int q = 0; q < CHQ_R; ++q) acc[r][q] = make_double2(0, 0);
-    for (int ch = cb; ch < ce; ++ch) {
-        const int i0 = ch * CHQ_CH;
-        __syncthreads();  // the previous chunk has been read
-        for (int e = threadIdx.x; e < CHQ_MAXV * CHQ_CH; e += CWG) {
-            const int j = e / CHQ_CH, ii = e - j * CHQ_CH;
-            S[j][ii] = (j < n && i0 + ii < nh) ? V[(size_t)j * nh + i0 + ii] : make_double2(0, 0);
+        for (int vt = 0; vt < NT; ++vt)
+#pragma unroll
+            for (int s = 0; s < (vt == 0 ? (KS < 4 ? KS : 4) : KS); ++s) {
+                const int k = 4 * s + q, col = 16 * vt + l;
+                const double2 v = Rinv[(size_t)ah * n * n + min(k, n - 1) * n + min(col, n - 1)];
+                R[vt][s] = k < n && col < n ? v : make_double2(0, 0);
+            }
+    }
+    f64x4 gr[NP], gi[NP];
+#pragma unroll
+    for (int p = 0; p < NP; ++p) gr[p] = gi[p] = f64x4{0, 0, 0, 0};
+    auto gram = [&](int i0, const double2 (&x)[NT][4]) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (i0 + 4 * u >= nh) break;
+            int p = 0;
+#pragma unroll
+            for (int jt = 0; jt < NT; ++jt)
+#pragma unroll
+                for (int kt = jt; kt < NT; ++kt, ++p) {
+                    const double2 a = x[jt][u], b = x[kt][u];
+                    gr[p] = mfma64(a.x, b.x, gr[p]);
+                    gi[p] = mfma64(a.x, b.y, gi[p]);
+                    gr[p] = mfma64(a.y, b.y, gr[p]);
+                    gi[p] = mfma64(-a.y, b.x, gi[p]);
+                }
+        }
+    };
+    double2 v[NL];
+    if (tb < te) load(tb, v);
+    for (int t = tb; t < te; t += CHQ_WAVES) {
+        double2 nx[NL];
+        load(t + CHQ_WAVES < te ? t + CHQ_WAVES : t, nx);
+        const int i0 = 16 * t;
+        double2 x[NT][4];
+        if constexpr (MODE == CHQ_GRAM) {
+#pragma unroll
+            for (int s = 0; s < NL; ++s) x[s / 4][s % 4] = v[s];
+        } else {
+#pragma unroll
+            for (int vt = 0; vt < NT; ++vt) {
+                f64x4 re = {0, 0, 0, 0}, im = {0, 0, 0, 0};
+#pragma unroll
+                for (int s = 0; s < (vt == 0 ? (KS < 4 ? KS : 4) : KS); ++s) {
+                    const double2 a = v[s], b = R[vt][s];
+                    if constexpr (MODE == CHQ_NEXT) {
+                        re = mfma64(a.x, b.x, re);
+                        im = mfma64(a.x, b.y, im);
+                        re = mfma64(-a.y, b.y, re);
+                        im = mfma64(a.y, b.x, im);
+                    } else {
+                        re = mfma64(b.x, a.x, re);
+                        im = mfma64(b.y, a.x, im);
+                        re = mfma64(-b.y, a.y, re);
+                        im = mfma64(b.x, a.y, im);
+                    }
+                }
+#pragma unroll
+                for (int ii = 0; ii < 4; ++ii) {
+                    x[vt][ii] = make_double2(re[ii], im[ii]);
+                    const int k = 16 * vt + (MODE == CHQ_NEXT ? l : q + 4 * ii);
+                    const int i = i0 + (MODE == CHQ_NEXT ? q + 4 * ii : l);
+                    if (k < n && i < nh) {
+                        const size_t o = (size_t)k * nh + i;
+                        V[o] = x[vt][ii];
+                        if constexpr (MODE == CHQ_LAST) {
+                            b32[base + o] = to_f32(x[vt][ii]);
+                            b16[base + o] = to_f16(x[vt][ii]);
+                        }
+                    }
+                }
+            }
+        }
+        if constexpr (MODE != CHQ_LAST) gram(i0, x);
+#pragma unroll
+        for (int s = 0; s < NL; ++s) v[s] = nx[s];
+    }
+    if constexpr (MODE != CHQ_LAST) {
+        // the wavefronts' sums, in their order
+        __shared__ double sh[CHQ_WAVES - 1][NP][8][64];
+        if (wave > 0) {
+#pragma unroll
+            for (int p = 0; p < NP; ++p)
+#pragma unroll
+                for (int ii = 0; ii < 4; ++ii) {
+                    sh[wave - 1][p][ii][lane] = gr[p][ii];
+                    sh[wave - 1][p][4 + ii][lane] = gi[p][ii];
+                }
         }
         __syncthreads();
-        for (int ii = 0; ii < CHQ_CH; ++ii) {
-            double2 a[CHQ_R], b[CHQ_R];
+        if (wave == 0) {
+            double2* G = Gp + ((size_t)ah * gridDim.y + blockIdx.y) * n * n;
+            int p = 0;
 #pragma unroll
-            for (int r = 0; r < CHQ_R; ++r) {
-                a[r] = S[ty * CHQ_R + r][ii];
-                b[r] = S[tx * CHQ_R + r][ii];
-            }
+            for (int jt = 0; jt < NT; ++jt)
 #pragma unroll
-            for (int r = 0; r < CHQ_R; ++r)
+                for (int kt = jt; kt < NT; ++kt, ++p)
 #pragma unroll
-                for (int q = 0; q < CHQ_R; ++q) acc[r][q] = cjfma<double>(a[r], b[q], acc[r][q]);
+                    for (int ii = 0; ii < 4; ++ii) {
+                        double2 g = make_double2(gr[p][ii], gi[p][ii]);
+                        for (int w = 0; w < CHQ_WAVES - 1; ++w)
+                            g = cadd<double>(g, make_double2(sh[w][p][ii][lane], sh[w][p][4 + ii][lane]));
+                        const int j = 16 * jt + q + 4 * ii, k = 16 * kt + l;
+                        if (j < n && k < n) G[j * n + k] = g;
+                    }
         }
     }
-    double2* G = Gp + ((size_t)ah * gridDim.y + blockIdx.y) * n * n;
-#pragma unroll
-    for (int r = 0; r < CHQ_R; ++r)
-#pragma unroll
-        for (int q = 0; q < CHQ_R; ++q) {
-            const int j = ty * CHQ_R + r, k = tx * CHQ_R + q;
-            if (j < n && k < n) G[j * n + k] = acc[r][q];
-        }
 }
 
 // one wavefront per block and chirality: G = sum of the partials in part
@@ -284,7 +404,8 @@ __global__ void __launch_bounds__(64) chq_chol_kernel(CoarseGeom c, const double
     const int ah = blockIdx.x, n = c.nvec, l = threadIdx.x;
     for (int e = l; e < n * n; e += 64) {
         double2 g = make_double2(0, 0);
-        for (int z = 0; z < parts; ++z) g = cadd<double>(g, Gp[((size_t)ah * parts + z) * n * n + e]);
+        if (e / n <= e % n)
+            for (int z = 0; z < parts; ++z) g = cadd<double>(g, Gp[((size_t)ah * parts + z) * n * n + e]);
         G[e / n][e % n] = g;
     }
     __syncthreads();
@@ -325,74 +446,31 @@ __global__ void __launch_bounds__(64) chq_chol_kernel(CoarseGeom c, const double
     }
 }
 
-// V <- V Rinv in place: grid (2 Nc, parts); a workgroup stages 64 indices of
-// all nvec vectors in LDS, then work-item (i, g) forms columns 8 g .. 8 g + 7 of
-// index i (column q sums rows k <= q) and writes them back
-constexpr int CHQ_TI = 64;
-__global__ void __launch_bounds__(CWG) chq_apply_kernel(CoarseGeom c, double2* __restrict__ b64,
-                                                        const double2* __restrict__ Rinv) {
-    __shared__ double2 Ri[CHQ_MAXV * CHQ_MAXV];
-    __shared__ double2 S[CHQ_MAXV][CHQ_TI + 1];
-    const int ah = blockIdx.x, n = c.nvec, nh = c.nhalf;
-    for (int e = threadIdx.x; e < n * n; e += CWG) Ri[e] = Rinv[(size_t)ah * n * n + e];
-    double2* V = b64 + (size_t)ah * n * nh;
-    const int ii = threadIdx.x % CHQ_TI, g = threadIdx.x / CHQ_TI;  // 4 groups of 8 columns
-    const int ntile = (nh + CHQ_TI - 1) / CHQ_TI;
-    for (int t = blockIdx.y; t < ntile; t += gridDim.y) {
-        const int i0 = t * CHQ_TI;
-        __syncthreads();  // Ri staged; the previous tile has been read
-        for (int e = threadIdx.x; e < n * CHQ_TI; e += CWG) {
-            const int k = e / CHQ_TI, x = e - k * CHQ_TI;
-            S[k][x] = (i0 + x < nh) ? V[(size_t)k * nh + i0 + x] : make_double2(0, 0);
-        }
-        __syncthreads();
-        double2 w[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) w[q] = make_double2(0, 0);
-        const int q0 = 8 * g;
-        const int kmax = min(n, q0 + 8);
-        for (int k = 0; k < kmax; ++k) {
-            const double2 v = S[k][ii];
-#pragma unroll
-            for (int q = 0; q < 8; ++q)
-                if (k <= q0 + q) w[q] = cfma<double>(v, Ri[k * n + min(q0 + q, n - 1)], w[q]);
-        }
-        if (i0 + ii < nh) {
-#pragma unroll
-            for (int q = 0; q < 8; ++q)
-                if (q0 + q < n) V[(size_t)(q0 + q) * nh + i0 + ii] = w[q];
-        }
-    }
-}
-
 __global__ void __launch_bounds__(CWG) basis_to_f32_kernel(size_t n, const double2* __restrict__ a,
                                                            float2* __restrict__ b) {
     for (size_t e = (size_t)blockIdx.x * CWG + threadIdx.x; e < n; e += (size_t)gridDim.x * CWG)
-        b[e] = make_float2((float)a[e].x, (float)a[e].y);
+        b[e] = to_f32(a[e]);
 }
 
-// FP16 copy of the basis: HBASIS_SCALE * phi, rounded to nearest even
 __global__ void __launch_bounds__(CWG) basis_to_f16_kernel(size_t n, const double2* __restrict__ a,
                                                            uint32_t* __restrict__ b) {
     for (size_t e = (size_t)blockIdx.x * CWG + threadIdx.x; e < n; e += (size_t)gridDim.x * CWG) {
-        const _Float16 re = (_Float16)((float)(a[e].x * (double)HBASIS_SCALE));
-        const _Float16 im = (_Float16)((float)(a[e].y * (double)HBASIS_SCALE));
-        b[e] = (uint32_t)__builtin_bit_cast(unsigned short, re) | ((uint32_t)__builtin_bit_cast(unsigned short, im) << 16);
+        b[e] = to_f16(a[e]);
     }
 }
 
 // fields[kk][comp][site][s] = basis vector k0+kk as a full fine field
 __global__ void __launch_bounds__(CWG) basis_expand_kernel(CoarseGeom c, const double2* __restrict__ b64, int k0,
-                                                           int nk, double2* __restrict__ fields) {
-    const size_t per = (size_t)12 * c.f.N5;
-    const size_t total = per * nk;
-    for (size_t e = (size_t)blockIdx.x * CWG + threadIdx.x; e < total; e += (size_t)gridDim.x * CWG) {
-        const int kk = (int)(e / per);
-        size_t r = e % per;
-        const int s = (int)(r % c.f.Ls);
-        r /= c.f.Ls;
-        const int site = (int)(r % c.f.V4);
-        const int comp = (int)(r / c.f.V4);
+                                                           double2* __restrict__ fields) {
+    // one field per blockIdx.y, 32-bit indices (12 N5 < 2^32 / 16); a stored entry is read
+    // once and gives the slices s and Ls-1-s (2.7 ms for 48 fields of 16^4 x 16, 5.3 TB/s;
+    // one entry a slice with 64-bit divisions 4.0)
+    const unsigned Lh = (unsigned)c.Lh, per = 12u * (unsigned)c.f.V4 * Lh, kk = blockIdx.y;
+    for (unsigned e = blockIdx.x * CWG + threadIdx.x; e < per; e += gridDim.x * CWG) {
+        const unsigned r = e / Lh;
+        const int s = (int)(e - r * Lh);
+        const int comp = (int)(r / (unsigned)c.f.V4);
+        const int site = (int)(r - (unsigned)comp * (unsigned)c.f.V4);
         // coordinates -> block and block-local site
         int x[4], t = site;
         x[0] = t % c.f.L[0];
@@ -407,16 +485,15 @@ __global__ void __launch_bounds__(CWG) basis_expand_kernel(CoarseGeom c, const d
             a = a * c.C[mu] + x[mu] / c.B[mu];
             sl = sl * c.B[mu] + x[mu] % c.B[mu];
         }
-        const int k = k0 + kk;
+        const int k = k0 + (int)kk;
         const int h = (k < c.nvec) ? 0 : 1;
         const int kh = k - h * c.nvec;
-        const bool upper_s = s < c.Lh;
-        const int sc = upper_s ? s : c.f.Ls - 1 - s;
-        const int i = (comp * c.bvol + sl) * c.Lh + sc;
-        double2 v = b64[(((size_t)a * 2 + h) * c.nvec + kh) * c.nhalf + i];
-        double f = RSQRT2;
-        if (!upper_s) f *= (h == 0 ? 1.0 : -1.0) * (comp < 6 ? 1.0 : -1.0);
-        fields[e] = make_double2(v.x * f, v.y * f);
+        const int i = (comp * c.bvol + sl) * c.Lh + s;
+        const double2 v = b64[(((size_t)a * 2 + h) * c.nvec + kh) * c.nhalf + i];
+        const double f = RSQRT2, g = f * (h == 0 ? 1.0 : -1.0) * (comp < 6 ? 1.0 : -1.0);
+        double2* o = fields + ((size_t)kk * 12 * c.f.V4 + r) * c.f.Ls;
+        o[s] = make_double2(v.x * f, v.y * f);
+        o[c.f.Ls - 1 - s] = make_double2(v.x * g, v.y * g);
     }
 }
 
@@ -1351,12 +1428,6 @@ void ccr_step_launch(const CoarseGeom& c, const S* A, C2<T>* x, const CoarseCRWo
 // Images of all basis vectors in memory and two dot-product kernels took 62 ms; the
 // whole H on the matrix cores 24; both row chiralities in one wavefront, two per SIMD,
 // the same.
-typedef double f64x4 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ f64x4 mfma64(double a, double b, f64x4 c) {
-    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-}
-
 // v += x (i^P y), x real
 template <int P> __device__ __forceinline__ void axpy_phase(double x, double2 y, double2& v) {
     if constexpr (P == 0) {
@@ -1756,18 +1827,35 @@ int chq_parts(const CoarseGeom& c) {
 size_t chq_scratch_elems(const CoarseGeom& c) {
     return chq_ok(c) ? (size_t)2 * c.Nc * (chq_parts(c) + 1) * c.nvec * c.nvec : 0;
 }
-void launch_chq_pass(const CoarseGeom& c, double2* b64, double2* scratch, int pass, int* flag, hipStream_t s) {
+namespace {
+template <int MODE>
+void chq_go(const CoarseGeom& c, double2* b64, const double2* Rinv, double2* Gp, float2* b32, uint32_t* b16,
+            hipStream_t s) {
+    const dim3 grid(c.Nc * 2, chq_parts(c)), wg(CWG);
+    if (c.nvec <= 8)
+        hipLaunchKernelGGL((chq_pass_kernel<2, MODE>), grid, wg, 0, s, c, b64, Rinv, Gp, b32, b16);
+    else if (c.nvec <= 16)
+        hipLaunchKernelGGL((chq_pass_kernel<4, MODE>), grid, wg, 0, s, c, b64, Rinv, Gp, b32, b16);
+    else if (c.nvec <= 24)
+        hipLaunchKernelGGL((chq_pass_kernel<6, MODE>), grid, wg, 0, s, c, b64, Rinv, Gp, b32, b16);
+    else
+        hipLaunchKernelGGL((chq_pass_kernel<8, MODE>), grid, wg, 0, s, c, b64, Rinv, Gp, b32, b16);
+}
+}  // namespace
+void launch_chq_round(const CoarseGeom& c, double2* b64, double2* scratch, int pass, int* flag, hipStream_t s) {
     const int parts = chq_parts(c);
     double2* Gp = scratch;
     double2* Rinv = scratch + (size_t)2 * c.Nc * parts * c.nvec * c.nvec;
-    hipLaunchKernelGGL(chq_gram_kernel, dim3(c.Nc * 2, parts), dim3(CWG), 0, s, c, b64, Gp);
+    if (pass == 0)
+        chq_go<CHQ_GRAM>(c, b64, nullptr, Gp, nullptr, nullptr, s);
+    else
+        chq_go<CHQ_NEXT>(c, b64, Rinv, Gp, nullptr, nullptr, s);
     hipLaunchKernelGGL(chq_chol_kernel, dim3(c.Nc * 2), dim3(64), 0, s, c, Gp, parts, pass, Rinv, flag);
 }
-void launch_chq_apply(const CoarseGeom& c, double2* b64, const double2* scratch, hipStream_t s) {
-    const int parts = chq_parts(c);
-    const double2* Rinv = scratch + (size_t)2 * c.Nc * parts * c.nvec * c.nvec;
-    const int ap = std::max(1, std::min(16, (c.nhalf + CHQ_TI - 1) / CHQ_TI));
-    hipLaunchKernelGGL(chq_apply_kernel, dim3(c.Nc * 2, ap), dim3(CWG), 0, s, c, b64, Rinv);
+void launch_chq_finish(const CoarseGeom& c, double2* b64, const double2* scratch, float2* b32, uint32_t* b16,
+                       hipStream_t s) {
+    const double2* Rinv = scratch + (size_t)2 * c.Nc * chq_parts(c) * c.nvec * c.nvec;
+    chq_go<CHQ_LAST>(c, b64, Rinv, nullptr, b32, b16, s);
 }
 
 void launch_basis_to_f32(const CoarseGeom& c, const double2* b64, float2* b32, hipStream_t s) {
@@ -1781,8 +1869,8 @@ void launch_basis_to_f16(const CoarseGeom& c, const double2* b64, uint32_t* b16,
 }
 
 void launch_basis_expand(const CoarseGeom& c, const double2* b64, int k0, int nk, double2* fields, hipStream_t s) {
-    const size_t n = (size_t)12 * c.f.N5 * nk;
-    hipLaunchKernelGGL(basis_expand_kernel, dim3(grid_for(n)), dim3(CWG), 0, s, c, b64, k0, nk, fields);
+    if (nk <= 0) return;
+    hipLaunchKernelGGL(basis_expand_kernel, dim3(grid_for((size_t)6 * c.f.N5), nk), dim3(CWG), 0, s, c, b64, k0, fields);
 }
 
 template <typename T, typename B, int W, int RKG>
