@@ -117,18 +117,20 @@ template <int NS> __device__ __forceinline__ void wg_sums2(Sum2 (&v)[NS]) {
         for (int w = 1; w < WAVES; ++w) v[q] = v[q] + sh[q][w];
     }
 }
-// v += row 0, q[k] += rows 1 + 2 k (hi) and 2 + 2 k (lo) of the partials
+// v += row 0, q[k] += rows 1 + 2 k (hi) and 2 + 2 k (lo) of the partials; o: the first
+// chunk, loaded before
 template <int NS>
-__device__ __forceinline__ void add_rows(const double* __restrict__ part, int np, double& v, Sum2* q) {
-    for (int i = threadIdx.x; i < np; i += 4 * REDUCE_THREADS) {
-        double o[1 + 2 * NS][4];
-        load_partials<1 + 2 * NS>(part, np, i, o);
+__device__ __forceinline__ void add_rows(const double* __restrict__ part, int np, double (&o)[1 + 2 * NS][4], double& v,
+                                         Sum2* q) {
+    for (int i = threadIdx.x;;) {
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             v += o[0][u];
 #pragma unroll
             for (int k = 0; k < NS; ++k) q[k] = q[k] + Sum2{o[1 + 2 * k][u], o[2 + 2 * k][u]};
         }
+        if ((i += 4 * REDUCE_THREADS) >= np) break;
+        load_partials<1 + 2 * NS>(part, np, i, o);
     }
 }
 
@@ -144,8 +146,9 @@ __device__ __forceinline__ int cr_stop(double rr, double tol2) {
 // and |Ap|^2 (hi, lo) of the previous and of this step.  slot: place of the previous
 // step's |r|^2 in the batch's history, or -1.
 // Bound by the 8 or 10 vectors it streams, and on small lattices by the start:
-// 512 workgroups with three elements in flight per work-item take 39.6 us a step at
-// 8^4 x 16 with the apply, 1024 with two 43.2, 256 with four 39.1.
+// with the apply a step takes 37.4 us at 8^4 x 16, 39.6 with the first elements loaded
+// after the scalars (then 1024 workgroups with two elements in flight 43.2, 256 with four
+// 39.1, against these 512 with three).
 template <bool FIRST, bool XUP>
 __global__ void __launch_bounds__(REDUCE_THREADS) cr_step_kernel(int64_t n, double2* __restrict__ x,
                                                                  double2* __restrict__ r, double2* __restrict__ p,
@@ -153,12 +156,37 @@ __global__ void __launch_bounds__(REDUCE_THREADS) cr_step_kernel(int64_t n, doub
                                                                  double2* __restrict__ Ap, const double* dpart, int ndot,
                                                                  const double* uin, double* uout, CrState* st, int step,
                                                                  int slot, double tol) {
+    // the partials and the first elements are on their way before the scalars are known;
+    // indices past the end repeat the last element, which is then not stored
+    constexpr int U = 3;
+    struct Batch {
+        double2 r[U], ar[U], p[U], ap[U], x[U];
+    };
+    const int64_t stride = (int64_t)gridDim.x * REDUCE_THREADS;
+    auto load = [&](int64_t i, Batch& b) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t k = min(i + u * stride, n - 1);
+            b.r[u] = r[k];
+            b.ar[u] = Ar[k];
+            b.p[u] = FIRST ? make_double2(0, 0) : p[k];
+            b.ap[u] = FIRST ? make_double2(0, 0) : Ap[k];
+            b.x[u] = XUP ? x[k] : make_double2(0, 0);
+        }
+    };
+    double od[DOT_ROWS][4], ou[3][4];
+    load_partials<DOT_ROWS>(dpart, ndot, (int)threadIdx.x, od);
+    if constexpr (!FIRST) load_partials<3>(uin, (int)gridDim.x, (int)threadIdx.x, ou);
+    int64_t i = (int64_t)blockIdx.x * REDUCE_THREADS + threadIdx.x;
+    Batch cur;
+    load(i, cur);
+    __builtin_amdgcn_sched_barrier(0);
     if (st->reason != CR_RUN) return;
     const bool lead = blockIdx.x == 0 && threadIdx.x == 0;
     double t[2] = {0.0, 0.0};                     // <r,Ar>, |r|^2
     Sum2 q[3] = {{0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}};  // |Ar|^2, Re<Ap,Ar>, |Ap|^2 of the old Ap
-    add_rows<2>(dpart, ndot, t[0], q);
-    if constexpr (!FIRST) add_rows<1>(uin, (int)gridDim.x, t[1], q + 2);
+    add_rows<2>(dpart, ndot, od, t[0], q);
+    if constexpr (!FIRST) add_rows<1>(uin, (int)gridDim.x, ou, t[1], q + 2);
     wg_sums<2>(t);
     wg_sums2<3>(q);
     const double rr = FIRST ? st->S[S_RR0] : t[1], arar = q[0].hi + q[0].lo;
@@ -182,7 +210,6 @@ __global__ void __launch_bounds__(REDUCE_THREADS) cr_step_kernel(int64_t n, doub
     const double alpha = rar / apap, aold = XUP ? st->S[S_ALPHA + ((step - 1) & 1)] : 0.0;
     double v[1] = {0.0};
     Sum2 an[1] = {{0.0, 0.0}};
-    const int64_t stride = (int64_t)gridDim.x * REDUCE_THREADS;
     auto element = [&](int64_t i, double2 ri, double2 ari, double2 po, double2 apo, double2 xi) {
         double2 pi = ri, api = ari;
         if constexpr (!FIRST) {
@@ -205,24 +232,15 @@ __global__ void __launch_bounds__(REDUCE_THREADS) cr_step_kernel(int64_t n, doub
         add_product(an[0], api.x, api.x);
         add_product(an[0], api.y, api.y);
     };
-    constexpr int U = 3;
-    int64_t i = (int64_t)blockIdx.x * REDUCE_THREADS + threadIdx.x;
-    for (; i + (U - 1) * stride < n; i += U * stride) {
-        double2 a[U], b[U], c[U], d[U], e[U];
+    while (i < n) {
+        Batch next;
+        load(i + U * stride, next);
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            a[u] = r[i + u * stride];
-            b[u] = Ar[i + u * stride];
-            c[u] = FIRST ? make_double2(0, 0) : p[i + u * stride];
-            d[u] = FIRST ? make_double2(0, 0) : Ap[i + u * stride];
-            e[u] = XUP ? x[i + u * stride] : make_double2(0, 0);
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) element(i + u * stride, a[u], b[u], c[u], d[u], e[u]);
+        for (int u = 0; u < U; ++u)
+            if (i + u * stride < n) element(i + u * stride, cur.r[u], cur.ar[u], cur.p[u], cur.ap[u], cur.x[u]);
+        cur = next;
+        i += U * stride;
     }
-    for (; i < n; i += stride)
-        element(i, r[i], Ar[i], FIRST ? make_double2(0, 0) : p[i], FIRST ? make_double2(0, 0) : Ap[i],
-                XUP ? x[i] : make_double2(0, 0));
     wg_sums<1>(v);
     wg_sums2<1>(an);
     if (threadIdx.x == 0) {
