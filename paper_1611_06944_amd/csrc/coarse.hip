@@ -570,8 +570,10 @@ constexpr int RKG_MAX = 32;
 // for the RKG vectors k of the workgroup.  Work-item = (row slot, W consecutive s):
 // a row is (component, block site), so the loads of the compressed basis (index
 // row * Lh + s) and of psi are contiguous; W = 2 (Lh even) makes them 16-byte
-// pairs in FP32.
-template <typename T, typename B, bool SUB, int W, int RKG>
+// pairs in FP32.  FULL: a group of RKG vectors has no test between its loads, at which
+// each would wait for the one before (16^3 x 32 x 16, 2^4 blocks, nvec = 16: 325 against
+// 415 us with the FP16 copy, 5.6 TB/s, 549 against 659 with the FP32 one).
+template <typename T, typename B, bool SUB, int W, int RKG, bool FULL>
 __global__ void __launch_bounds__(CWG) restrict_kernel(CoarseGeom c, const B* __restrict__ basis,
                                                        const C2<T>* __restrict__ psi, const C2<T>* __restrict__ psi2,
                                                        C2<T>* __restrict__ v) {
@@ -634,6 +636,18 @@ __global__ void __launch_bounds__(CWG) restrict_kernel(CoarseGeom c, const B* __
 #pragma unroll
             for (int w = 0; w < W; ++w) f[w] = mk<T>((p1[w].x + sg * p2[w].x) * r2, (p1[w].y + sg * p2[w].y) * r2);
             const size_t i = (size_t)row * c.Lh + s;
+            if constexpr (FULL) {
+                if (kn == RKG) {
+#pragma unroll
+                    for (int q = 0; q < RKG; ++q) {
+                        C2<T> bv[W];
+                        ld_basis<T, W>(bh + (size_t)q * c.nhalf + i, bv);
+#pragma unroll
+                        for (int w = 0; w < W; ++w) acc[q] = cjfma<T>(bv[w], f[w], acc[q]);
+                    }
+                    continue;
+                }
+            }
 #pragma unroll
             for (int q = 0; q < RKG; ++q) {
                 if (q < kn) {
@@ -1873,14 +1887,30 @@ void launch_basis_expand(const CoarseGeom& c, const double2* b64, int k0, int nk
     hipLaunchKernelGGL(basis_expand_kernel, dim3(grid_for((size_t)6 * c.f.N5), nk), dim3(CWG), 0, s, c, b64, k0, fields);
 }
 
-template <typename T, typename B, int W, int RKG>
-void restrict_launch_w(const CoarseGeom& c, const B* basis, const C2<T>* psi, const C2<T>* psi2, C2<T>* v,
+template <typename T, typename B, int W, int RKG, bool FULL>
+void restrict_launch_f(const CoarseGeom& c, const B* basis, const C2<T>* psi, const C2<T>* psi2, C2<T>* v,
                        hipStream_t s) {
     const dim3 grid(c.Nc * 2 * ((c.nvec + RKG - 1) / RKG));
     if (psi2)
-        hipLaunchKernelGGL((restrict_kernel<T, B, true, W, RKG>), grid, dim3(CWG), 0, s, c, basis, psi, psi2, v);
+        hipLaunchKernelGGL((restrict_kernel<T, B, true, W, RKG, FULL>), grid, dim3(CWG), 0, s, c, basis, psi, psi2, v);
     else
-        hipLaunchKernelGGL((restrict_kernel<T, B, false, W, RKG>), grid, dim3(CWG), 0, s, c, basis, psi, psi2, v);
+        hipLaunchKernelGGL((restrict_kernel<T, B, false, W, RKG, FULL>), grid, dim3(CWG), 0, s, c, basis, psi, psi2, v);
+}
+
+template <typename T, typename B, int W, int RKG>
+void restrict_launch_w(const CoarseGeom& c, const B* basis, const C2<T>* psi, const C2<T>* psi2, C2<T>* v,
+                       hipStream_t s) {
+    // Full groups where there are any, in FP32 arithmetic (FP64 takes 253 registers with
+    // them, 950 against 894 us at 16^4 x 16, 4^4 blocks, nvec = 24).  The FP32 copy with
+    // large blocks streams a little slower that way once it is far larger than the caches
+    // (4^4 blocks: 16^4 x 16, nvec = 32, 3.2 GB, 523 against 647 us; 24^4 x 16, nvec = 16,
+    // 8.2 GB, 1492 against 1475, nvec = 32 2776 against 2677; 2^4 blocks there 1334
+    // against 1570).
+    if constexpr (sizeof(T) == 4) {
+        const bool far = std::is_same<B, C2<T>>::value && c.bvol > 16 && basis_elems(c) * sizeof(B) > ((size_t)6 << 30);
+        if (c.nvec >= RKG && !far) return restrict_launch_f<T, B, W, RKG, true>(c, basis, psi, psi2, v, s);
+    }
+    restrict_launch_f<T, B, W, RKG, false>(c, basis, psi, psi2, v, s);
 }
 
 template <typename T, typename B, int RKG>
