@@ -740,7 +740,17 @@ __global__ void __launch_bounds__(PAR2_WG) __attribute__((amdgpu_waves_per_eu(2)
     // slice s0 goes to Ls-1-s0, slice s0+1 to Ls-2-s0: one pair at Ls-2-s0,
     // lower spins negated (H = gamma5 R5 D)
     const uint32_t oo = (uint32_t)(st.site * LS + (LS - 2 - s0)) * CB;
-    store_pair<NY, H16>(f, oo, ep, a0, a1);
+    if constexpr (NY == 0) {
+        // in place: scheduled through store_pair the plain apply is 0.6% slower
+#pragma unroll
+        for (int c = 0; c < 12; ++c) {
+            const C2<T> lo = (c < 6) ? a1[c] : cneg<T>(a1[c]);
+            const C2<T> hi = (c < 6) ? a0[c] : cneg<T>(a0[c]);
+            st_pair_s_nt<H16>(make_float4(lo.x, lo.y, hi.x, hi.y), f.out, oo, (uint32_t)c * f.cstride);
+        }
+    } else {
+        store_pair<NY, H16>(f, oo, ep, a0, a1);
+    }
 }
 
 // Parity-tile kernel at Ls = 8 (even extents, FP32 and FP64).  The tile scheme
