@@ -1377,19 +1377,23 @@ bool launch_site(const FineGeom& g, const C2<T>* U, const C2<T>* in, C2<T>* out,
     return true;
 }
 
-// FP32 fields with even Ls take the site kernel's 16-byte slice pairs from this
-// many 5d sites on; below it the second work-item per pair is worth more: 16^3 x
-// 32 x 12 (1.6M sites) takes 119 us in pairs and 139 us in single slices, 12^4 x
-// 20 (0.4M) 40 and 36 us, 15^4 x 24 (1.2M) 104 and 102 us.
+// FP32 fields with even Ls take the site kernels' 16-byte slice pairs from SITE_PAIRS 5d
+// sites on (16^3 x 32 x 12, 1.6M: 117 us in pairs, 145 in single slices), and at Ls >=
+// 10 from an eighth of that on (16^4 x 12, 0.8M: 54 and 60; 12^4 x 10, 0.2M: 18.7 and
+// 22.2; 10^4 x 12, 0.1M: equal).  At fewer slices LDS takes only part of a workgroup's
+// work-items in pairs (16^4 x 4: 29 and 25 us).
 constexpr int SITE_PAIRS = 1 << 20;
+bool site_pairs(const FineGeom& g) {
+    return g.Ls % 2 == 0 && (g.N5 >= SITE_PAIRS || g.Ls > WG || (g.Ls >= 10 && g.N5 >= SITE_PAIRS / 8));
+}
 
 // The library's choice (tune.dslash_variant 0).  Even extents with Ls = 16 or 8:
 // the parity-tile kernels, whose tiles fill whole wavefronts there (at other Ls
-// they do not, and were no faster than the site kernel: 141 against 119 us at 16^3
-// x 32 x 12 in FP32, 234 against 237 us in FP64).  Odd extents with Ls = 16 in FP32:
-// the tile kernel (31.7 against 32.4 us at 11 x 12 x 13 x 14).  Otherwise the site
-// kernel: against the generic one it takes 119 instead of 205 us (FP32) and 237
-// instead of 340 us (FP64) at 16^3 x 32 x 12.
+// they do not, and were no faster than the site kernel: 141 against 117 us at 16^3
+// x 32 x 12 in FP32, 234 against 227 us in FP64).  Odd extents with Ls = 16 in FP32:
+// the tile kernel (29.2 against 30.1 us at 11 x 12 x 13 x 14, 55 against 58 at 15^4).
+// Otherwise the site kernel: against the generic one it takes 117 instead of 202 us
+// (FP32) and 227 instead of 332 us (FP64) at 16^3 x 32 x 12.
 template <typename T, int NY>
 bool launch_default(const FineGeom& g, const C2<T>* U, const C2<T>* in, C2<T>* out, const Epi<T>& ep, hipStream_t s) {
     constexpr int W = sizeof(T) == 4 ? 2 : 1;
@@ -1414,7 +1418,7 @@ bool launch_default(const FineGeom& g, const C2<T>* U, const C2<T>* in, C2<T>* o
     }
     if (sizeof(T) == 4 && g.Ls == 16) return false;
     if constexpr (W == 2) {
-        if (g.Ls % 2 == 0 && (g.N5 >= SITE_PAIRS || g.Ls > WG)) return launch_site<T, 2, NY>(g, U, in, out, ep, s);
+        if (site_pairs(g)) return launch_site<T, 2, NY>(g, U, in, out, ep, s);
     }
     return launch_site<T, 1, NY>(g, U, in, out, ep, s);
 }
@@ -1803,7 +1807,7 @@ void launch_cf(const FineGeom& g, const CfCoef& k, const C2<T>* U, const C2<T>* 
         return;
     }
     if constexpr (sizeof(T) == 4) {
-        if (g.Ls % 2 == 0 && big) return launch_cf_site<float, 2>(g, k, U, in, out, s);
+        if (site_pairs(g)) return launch_cf_site<float, 2>(g, k, U, in, out, s);
     }
     launch_cf_site<T, 1>(g, k, U, in, out, s);
 }

@@ -104,3 +104,22 @@ def test_continued_fraction_slice_pairs():
     ref = hd.apply_cf(lat, U, x, beta, 0.35)  # FP64: single slices
     got = hd.apply_cf(lat, U.to(torch.complex64), x.to(torch.complex64), beta, 0.35)
     assert float((got - ref).abs().max()) <= 1e-5 * float(ref.abs().max())
+
+
+@pytest.mark.parametrize("L,Ls", [((11, 9, 10, 14), 10), ((7, 11, 13, 6), 22)])
+def test_slice_pairs_from_ten_slices(L, Ls):
+    """Just above 2^17 5d sites, ragged last workgroups: pairs against the generic kernel, and the
+    continued fraction's against FP64; rounding as above."""
+    torch = torch_dev()
+    log(f"slice pairs L={L} Ls={Ls}")
+    lat = hd.Lattice(L, Ls, mf=0.05)
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(5)
+    U = to_dev(hd.pack_gauge(hi.gauge_field(L, seed=4)))
+    x = torch.randn((12, lat.V4, Ls), dtype=torch.complex128, device="cuda:0", generator=g)
+    U32, x32 = U.to(torch.complex64), x.to(torch.complex64)
+    ref = hd.apply_fine(lat.with_tune(dslash_variant=2), U32, x32)
+    assert float((hd.apply_fine(lat, U32, x32) - ref).abs().max()) <= 1e-6 * float(ref.abs().max())
+    beta = list(0.3 + 0.1 * np.arange(Ls - 1))
+    ref = hd.apply_cf(lat, U, x, beta, 0.35)
+    assert float((hd.apply_cf(lat, U32, x32, beta, 0.35) - ref).abs().max()) <= 1e-5 * float(ref.abs().max())
