@@ -8,10 +8,10 @@
 // of p, Ap, x and r.  The scalars live in device memory: every workgroup of the
 // update reduces the partial sums of the two kernels before it, in the same
 // fixed order, and so takes the same decisions; convergence and breakdown set a
-// flag that ends the later launches of a batch.  The host enqueues a batch of
-// steps and reads the flag and the residual norms back once per batch.  On
-// convergence of the updated residual the true residual b - H x is recomputed;
-// if it does not meet the tolerance the iteration restarts from it.
+// flag that ends the later launches of a batch and is not read in its own.  The
+// host enqueues a batch of steps and reads the flag and the residual norms back
+// once per batch.  On convergence of the updated residual the true residual b - H x
+// is recomputed; if it does not meet the tolerance the iteration restarts from it.
 //
 // The steps' vectors are streamed, so their bytes bound a step: |Ap|^2 comes from
 //   |Ar + beta Ap|^2 = |Ar|^2 + 2 beta Re<Ap,Ar> + beta^2 |Ap|^2,
@@ -43,7 +43,10 @@ constexpr int S_COUNT = S_HIST + CR_BATCH;
 enum { CR_RUN = 0, CR_CONVERGED = 1, CR_BREAKDOWN = 2, CR_NAN = 3 };
 struct CrState {
     double S[S_COUNT];
-    int reason;
+    // of the even / odd steps: step k reads the reason of step k - 1 and writes its own.
+    // If a launch read the one that it writes, a late workgroup could end some of its
+    // wavefronts and not the others, whose sums would then take in what LDS held before
+    int reason[2];
     int steps;
 };
 
@@ -181,8 +184,13 @@ __global__ void __launch_bounds__(REDUCE_THREADS) cr_step_kernel(int64_t n, doub
     Batch cur;
     load(i, cur);
     __builtin_amdgcn_sched_barrier(0);
-    if (st->reason != CR_RUN) return;
     const bool lead = blockIdx.x == 0 && threadIdx.x == 0;
+    const int before = st->reason[(step - 1) & 1];
+    int* const reason = &st->reason[step & 1];
+    if (before != CR_RUN) {
+        if (lead) *reason = before;
+        return;
+    }
     double t[2] = {0.0, 0.0};                     // <r,Ar>, |r|^2
     Sum2 q[3] = {{0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}};  // |Ar|^2, Re<Ap,Ar>, |Ap|^2 of the old Ap
     add_rows<2>(dpart, ndot, od, t[0], q);
@@ -194,14 +202,14 @@ __global__ void __launch_bounds__(REDUCE_THREADS) cr_step_kernel(int64_t n, doub
         const int stop = cr_stop(rr, tol * tol * st->S[S_BB]);
         if (lead && slot >= 0) st->S[S_HIST + slot] = rr;
         if (stop != CR_RUN) {
-            if (lead) st->reason = stop;
+            if (lead) *reason = stop;
             return;
         }
     }
     const double rar = t[0];
     // (near-)breakdown: <r,Ar> at rounding level of |r||Ar|
     if (!(fabs(rar) >= 1e-13 * sqrt(rr) * sqrt(arar))) {
-        if (lead) st->reason = isfinite(rar) ? CR_BREAKDOWN : CR_NAN;
+        if (lead) *reason = isfinite(rar) ? CR_BREAKDOWN : CR_NAN;
         return;
     }
     const double beta = FIRST ? 0.0 : rar / st->S[S_RAR + ((step - 1) & 1)];
@@ -258,13 +266,13 @@ __global__ void __launch_bounds__(REDUCE_THREADS) cr_step_kernel(int64_t n, doub
 // |r|^2 after the last step of a batch, and its stop test
 __global__ void __launch_bounds__(REDUCE_THREADS) cr_check_kernel(const double* uin, int nu, CrState* st, int step,
                                                                   int slot, double tol) {
-    if (st->reason != CR_RUN || st->steps != step) return;
+    if (st->reason[step & 1] != CR_RUN) return;
     double t[1] = {0.0};
     add_partials<1>(uin, nu, t);
     wg_sums<1>(t);
     if (threadIdx.x == 0) {
         st->S[S_HIST + slot] = t[0];
-        st->reason = cr_stop(t[0], tol * tol * st->S[S_BB]);
+        st->reason[step & 1] = cr_stop(t[0], tol * tol * st->S[S_BB]);  // one workgroup: all have read it
     }
 }
 
@@ -296,9 +304,9 @@ __device__ __forceinline__ void store_dots(double* __restrict__ part, double (&v
 // The apply's own partials (nin columns) summed into gridDim.x columns: a large
 // lattice has more of them than every workgroup of the update can add up.
 __global__ void __launch_bounds__(REDUCE_THREADS) cr_compress_kernel(const double* __restrict__ in, int nin,
-                                                                     const CrState* __restrict__ st,
+                                                                     const CrState* __restrict__ st, int step,
                                                                      double* __restrict__ out) {
-    if (st->reason != CR_RUN) return;
+    if (st->reason[(step - 1) & 1] != CR_RUN) return;
     double v[1] = {0.0};
     Sum2 q[2] = {{0.0, 0.0}, {0.0, 0.0}};
     for (int i = blockIdx.x * REDUCE_THREADS + threadIdx.x; i < nin; i += gridDim.x * REDUCE_THREADS) {
@@ -315,9 +323,9 @@ template <bool FIRST>
 __global__ void __launch_bounds__(REDUCE_THREADS) cr_dots_kernel(int64_t n, const double2* __restrict__ r,
                                                                  const double2* __restrict__ Ar,
                                                                  const double2* __restrict__ Ap,
-                                                                 const CrState* __restrict__ st,
+                                                                 const CrState* __restrict__ st, int step,
                                                                  double* __restrict__ dpart) {
-    if (st->reason != CR_RUN) return;
+    if (st->reason[(step - 1) & 1] != CR_RUN) return;
     double v[1] = {0.0};
     Sum2 q[2] = {{0.0, 0.0}, {0.0, 0.0}};
     const int64_t stride = (int64_t)gridDim.x * REDUCE_THREADS;
@@ -372,7 +380,7 @@ __global__ void __launch_bounds__(REDUCE_THREADS) cr_start_kernel(const double* 
     if (threadIdx.x == 0) {
         st->S[S_RR0] = t[0];
         st->S[S_BB] = t[1];
-        st->reason = CR_RUN;
+        st->reason[0] = st->reason[1] = CR_RUN;
         st->steps = 0;
     }
 }
@@ -472,19 +480,20 @@ int cr_solve(const FineGeom& g, const hdcr_solve_params* prm, const double2* U, 
                    (const double*)w.dpart, step == 1 ? nwg : nd, uin, uout, w.st, step, slot, prm->tol)
                 if (step == 1) {
                     launch_dslash<double>(g, U, w.r, w.Ar, s);
-                    hipLaunchKernelGGL(cr_dots_kernel<true>, rg, rt, 0, s, n, w.r, w.Ar, w.Ap, w.st, w.dpart);
+                    hipLaunchKernelGGL(cr_dots_kernel<true>, rg, rt, 0, s, n, w.r, w.Ar, w.Ap, w.st, step, w.dpart);
                     HDCR_CR_STEP(true, false);
                     continue;
                 }
                 if (ndots > REDUCE_BLOCKS) {
                     launch_dslash_dots(g, U, w.r, w.Ar, w.Ap, w.apart, s);
                     hipLaunchKernelGGL(cr_compress_kernel, dim3(CR_COMPRESS), rt, 0, s, (const double*)w.apart, ndots,
-                                       w.st, w.dpart);
+                                       w.st, step, w.dpart);
                 } else if (ndots > 0) {
                     launch_dslash_dots(g, U, w.r, w.Ar, w.Ap, w.dpart, s);
                 } else {
                     launch_dslash<double>(g, U, w.r, w.Ar, s);
-                    hipLaunchKernelGGL(cr_dots_kernel<false>, rg, rt, 0, s, n, w.r, w.Ar, w.Ap, w.st, w.dpart);
+                    hipLaunchKernelGGL(cr_dots_kernel<false>, rg, rt, 0, s, n, w.r, w.Ar, w.Ap, w.st, step,
+                                       w.dpart);
                 }
                 if (step % 2 == 0)
                     HDCR_CR_STEP(false, true);
@@ -495,7 +504,7 @@ int cr_solve(const FineGeom& g, const hdcr_solve_params* prm, const double2* U, 
             hipLaunchKernelGGL(cr_check_kernel, dim3(1), rt, 0, s, (const double*)w.upart[step & 1], nwg, w.st, step,
                                nb - 1, prm->tol);
             HDCR_HIP_CHECK(read());
-            reason = h.reason;
+            reason = h.reason[step & 1];
             step = h.steps;
             const int did = step - done;
             for (int k = 0; k < did; ++k)
