@@ -112,10 +112,9 @@ void launch_coarse_apply_bf16(const CoarseGeom& c, const uint16_t* A, const floa
                               hipStream_t s);
 
 // Coarse conjugate residual (the subspace inverse by a Krylov method, Sec. 4)
-// with device-resident scalars: every kernel reads a done flag and returns at
-// once when it is set, so a batch of iterations can be enqueued without
-// synchronising; reductions finish in the last-arriving workgroup in a fixed
-// order (reproducible).
+// with device-resident scalars: every step reads a done flag and returns when it
+// is set, so a batch of iterations can be enqueued without synchronising; every
+// reduction adds in a fixed order (reproducible).
 template <typename T> struct CoarseCRWork {
     C2<T>* r[2];    // of the even / odd steps, as Ar and Ap
     C2<T>* Ar[2];
@@ -124,9 +123,7 @@ template <typename T> struct CoarseCRWork {
     double* part;   // partial sums: CCR_START_PARTS of the start kernels, then two halves of
                     // [5][ccr_groups<T>(Nc)] of the step kernel (even / odd steps)
     double* cs;     // scalars: 3 |r|^2 of the start, 4 |b|^2, 5 tol^2, 6 / 7 <r,Ar> of the even / odd steps
-    int* flags;     // 0 done, 1 iterations, 2 (unused), 3 maxiter,
-                    // 4 stop reason (0 none, 2 near-breakdown, 3 not finite);
-                    // CCR_COUNTERS.. arrival counters (CCR_FLAGS ints)
+    int* flags;     // CCR_DONE.. and CCR_COUNTERS.. (arrival counters), CCR_FLAGS ints
     double* dpart;  // partial sums of the deflated start: [2 * DEFL_KMAX][DEFL_BLOCKS]
     double* dcoef;  // its coefficients <V_j, b> / theta_j: [2 * DEFL_KMAX] (re, im)
 };
@@ -151,6 +148,11 @@ template <typename T> int ccr_groups(int Nc) {
     const int most = 256 * (sizeof(T) == 8 ? 3 : 4), spw = (Nc + most - 1) / most;
     return (Nc + spw - 1) / spw;
 }
+// flags.  Done after the even (CCR_DONE) / odd (CCR_DONE + 1) steps: step k reads that of
+// step k - 1 and writes its own.  If a launch read the one that it writes, a late workgroup
+// could end some of its wavefronts and not the others, whose sums would then take in what
+// LDS held before.  Stop reason: 0 none, 2 near-breakdown, 3 not finite.
+enum { CCR_DONE = 0, CCR_ITERS = 2, CCR_REASON = 3, CCR_HOST_FLAGS = 4 };
 constexpr int ARRIVE_GROUPS = 16;   // group counters of the last-arrival test
 constexpr int ARRIVE_STRIDE = 64;   // ints between counters (each counter on its own 256-byte line)
 constexpr int CCR_COUNTERS = 64;    // first arrival counter in flags

@@ -1030,10 +1030,9 @@ __global__ void __launch_bounds__(CWG) ccr_init_kernel(int n, const C2<T>* __res
             cs[4] = s[0];
             cs[3] = s[0];
             cs[5] = tol2;
-            flags[3] = maxiter;
-            flags[1] = 0;
-            flags[4] = 0;
-            flags[0] = (s[0] == 0.0 || maxiter <= 0 || !isfinite(s[0])) ? 1 : 0;
+            flags[CCR_ITERS] = 0;
+            flags[CCR_REASON] = 0;
+            flags[CCR_DONE] = flags[CCR_DONE + 1] = (s[0] == 0.0 || maxiter <= 0 || !isfinite(s[0])) ? 1 : 0;
         }
     }
 }
@@ -1117,10 +1116,10 @@ __global__ void __launch_bounds__(CWG) ccr_init_defl_kernel(int n, const C2<T>* 
             cs[4] = s[0];
             cs[3] = s[1];
             cs[5] = tol2;
-            flags[3] = maxiter;
-            flags[1] = 0;
-            flags[4] = 0;
-            flags[0] = (s[0] == 0.0 || maxiter <= 0 || !isfinite(s[0]) || !isfinite(s[1])) ? 1 : 0;
+            flags[CCR_ITERS] = 0;
+            flags[CCR_REASON] = 0;
+            flags[CCR_DONE] = flags[CCR_DONE + 1] =
+                (s[0] == 0.0 || maxiter <= 0 || !isfinite(s[0]) || !isfinite(s[1])) ? 1 : 0;
         }
     }
 }
@@ -1186,7 +1185,8 @@ template <typename T> struct CcrFields {
 // the start of step k (from step 2 on; step 1 runs unconditionally, as the start
 // kernel only stops on a zero or non-finite b), and a converged r_k costs one apply
 // that is not used.  All workgroups reduce the same partials in the same order and so
-// take the same decisions; workgroup 0 records them.
+// take the same decisions; workgroup 0 records them, in places that this launch does
+// not read (the done flag and <r,Ar> are kept for even and odd steps).
 //
 // A work-item covers E consecutive rows j (t % (Nb/E)) and the rows of the site's 9 Nb
 // x Nb matrix (d, k) = kk, kk + kg, ... (kk = t / (Nb/E), kg = CWG / (Nb/E) groups),
@@ -1214,7 +1214,8 @@ ccr_step_kernel(CoarseGeom c, CcrSplit sp, const S* __restrict__ A, CcrFields<T>
     const int w = logical_block(blockIdx.x, G);
     const int a0 = w * sp.spw, a1 = min(a0 + sp.spw, c.Nc);
     const bool first = step == 1, lead = w == 0 && t == 0;
-    const int done = flags[0];
+    const int done = flags[CCR_DONE + ((step - 1) & 1)];
+    int* const set_done = &flags[CCR_DONE + (step & 1)];
     const double rr0 = cs[3], stop = cs[5] * cs[4], rar_old = cs[6 + ((step - 1) & 1)];
     double v[5];  // the work-item's first entry of each row of partials
 #pragma unroll
@@ -1255,7 +1256,10 @@ ccr_step_kernel(CoarseGeom c, CcrSplit sp, const S* __restrict__ A, CcrFields<T>
     for (int u = 0; u < PB; ++u) buf[u] = load(a0, kk + u * kg);
     for (int e = nrow + t; e < nb * kg * PB; e += CWG) vs[e] = mk<T>(0, 0);
     __builtin_amdgcn_sched_barrier(0);
-    if (done) return;
+    if (done) {
+        if (lead) *set_done = 1;
+        return;
+    }
 
     T bt = 0, alpha = 0;
     double rar = 0;
@@ -1270,7 +1274,7 @@ ccr_step_kernel(CoarseGeom c, CcrSplit sp, const S* __restrict__ A, CcrFields<T>
         block_sum5(v, sh[0]);
         const double rr = first ? rr0 : v[3];
         if (!first && (rr <= stop || !isfinite(rr))) {  // r_k converged (or not finite): x_k is the result
-            if (lead) flags[0] = 1;
+            if (lead) *set_done = 1;
             return;
         }
         rar = v[0];
@@ -1279,8 +1283,8 @@ ccr_step_kernel(CoarseGeom c, CcrSplit sp, const S* __restrict__ A, CcrFields<T>
         const double apap = first ? v[1] : v[1] + 2.0 * beta * v[2] + beta * beta * v[4];
         if (bd || !(apap > 0.0)) {  // (near-)breakdown ends the coarse solve
             if (lead) {
-                flags[4] = bd ? bd : 2;
-                flags[0] = 1;
+                flags[CCR_REASON] = bd ? bd : 2;
+                *set_done = 1;
             }
             return;
         }
@@ -1376,7 +1380,7 @@ ccr_step_kernel(CoarseGeom c, CcrSplit sp, const S* __restrict__ A, CcrFields<T>
     }
     if (lead && step > 0) {
         cs[6 + (step & 1)] = rar;
-        flags[1] = step;
+        flags[CCR_ITERS] = step;
     }
 }
 

@@ -432,12 +432,12 @@ int coarse_solve(const CoarseGeom& c, hdcr_dtype dt, const void* A, const hdcr_c
     int it = 0;
     int e = coarse_cr<T>(c, dt, A, b, x, maxiter, tol, w, 0, s, &it, defl ? &dv : nullptr);
     if (e) return e;
-    int hf[5] = {0, 0, 0, 0, 0};
-    HDCR_HIP_CHECK(hipMemcpyAsync(hf, w.flags, 5 * sizeof(int), hipMemcpyDeviceToHost, s));
+    int hf[CCR_HOST_FLAGS] = {};
+    HDCR_HIP_CHECK(hipMemcpyAsync(hf, w.flags, sizeof(hf), hipMemcpyDeviceToHost, s));
     HDCR_HIP_CHECK(hipStreamSynchronize(s));
-    if (iters) *iters = hf[1];
-    if (hf[4] == 2) return HDCR_EBREAKDOWN;
-    if (hf[4] == 3) return HDCR_ENAN;
+    if (iters) *iters = hf[CCR_ITERS];
+    if (hf[CCR_REASON] == 2) return HDCR_EBREAKDOWN;
+    if (hf[CCR_REASON] == 3) return HDCR_ENAN;
     return HDCR_OK;
 }
 

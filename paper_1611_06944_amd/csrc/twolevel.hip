@@ -110,18 +110,18 @@ int coarse_cr(const CoarseGeom& c, hdcr_dtype A_dtype, const void* A, const C2<T
     // blocks, Nb = 24, FP64) took 2.95 ms with 8 steps a batch and takes 2.48.
     int enq = 0;
     int batch = std::max(4, std::min(hint > 0 ? hint + 2 : 16, maxiter));
-    int hf[5] = {0, 0, 0, 0, 0};
+    int hf[CCR_HOST_FLAGS] = {};
     while (enq < maxiter) {
         const int nb = std::min(batch, maxiter - enq);
         for (int i = 1; i <= nb; ++i) launch_ccr_step<T>(c, A_dtype, A, x, w, enq + i, s);
         enq += nb;
-        HDCR_HIP_CHECK(hipMemcpyAsync(hf, w.flags, 5 * sizeof(int), hipMemcpyDeviceToHost, s));
+        HDCR_HIP_CHECK(hipMemcpyAsync(hf, w.flags, sizeof(hf), hipMemcpyDeviceToHost, s));
         HDCR_HIP_CHECK(hipStreamSynchronize(s));
-        if (hf[0]) break;
+        if (hf[CCR_DONE + (enq & 1)]) break;
         batch = std::max(8, std::min(enq / 4, 64));
     }
-    if (iters) *iters = hf[1];
-    if (reason) *reason = hf[4];
+    if (iters) *iters = hf[CCR_ITERS];
+    if (reason) *reason = hf[CCR_REASON];
     HDCR_HIP_CHECK(hipGetLastError());
     return HDCR_OK;
 }

@@ -11,10 +11,10 @@ CLANG = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin", "c
 
 
 @pytest.mark.skipif(not os.path.exists(CLANG), reason="needs ROCm's clang")
-@pytest.mark.parametrize("name", ["cr"])
-def test_solver_on_host(name, tmp_path):
+@pytest.mark.parametrize("name,opt", [("cr", "-O1"), ("coarse_cr", "-O0")])
+def test_solver_on_host(name, opt, tmp_path):
     exe = tmp_path / name
-    cmd = [CLANG, "-x", "c++", "-std=c++17", "-O1", "-Wno-unknown-attributes", "-I" + os.path.join(ROOT, "tests", "simt"),
+    cmd = [CLANG, "-x", "c++", "-std=c++17", opt, "-Wno-unknown-attributes", "-I" + os.path.join(ROOT, "tests", "simt"),
            "-I" + os.path.join(ROOT, "include"), os.path.join(ROOT, "tests", "simt", name + "_main.cpp"), "-o", str(exe),
            "-lpthread"]
     subprocess.run(cmd, check=True, capture_output=True, text=True)
