@@ -215,6 +215,11 @@ __global__ void __launch_bounds__(REDUCE_THREADS) cr_step_kernel(int64_t n, doub
     const double beta = FIRST ? 0.0 : rar / st->S[S_RAR + ((step - 1) & 1)];
     const Sum2 e = add_scaled(add_scaled(q[0], 2.0 * beta, q[1]), beta, add_scaled(Sum2{0.0, 0.0}, beta, q[2]));
     const double apap = FIRST ? arar : e.hi + e.lo;
+    // no step to take along p; r, p, Ap and x stay those of the step before
+    if (!(apap > 0.0 && isfinite(apap))) {
+        if (lead) *reason = isfinite(apap) ? CR_BREAKDOWN : CR_NAN;
+        return;
+    }
     const double alpha = rar / apap, aold = XUP ? st->S[S_ALPHA + ((step - 1) & 1)] : 0.0;
     double v[1] = {0.0};
     Sum2 an[1] = {{0.0, 0.0}};

@@ -8,6 +8,8 @@ namespace hdcr {
 
 static std::vector<double> diag;  // H of the test, one value per complex entry
 static int64_t applies = 0;
+static int64_t odd_apply = 0;     // number of the apply that is scaled
+static double odd_scale = 1.0;
 
 int fail(int code, const std::string& msg) {
     fprintf(stderr, "%s\n", msg.c_str());
@@ -15,8 +17,8 @@ int fail(int code, const std::string& msg) {
 }
 template <typename T>
 void launch_dslash(const FineGeom&, const C2<T>*, const C2<T>* in, C2<T>* out, hipStream_t) {
-    ++applies;
-    for (size_t i = 0; i < diag.size(); ++i) out[i] = make_double2(diag[i] * in[i].x, diag[i] * in[i].y);
+    const double f = ++applies == odd_apply ? odd_scale : 1.0;
+    for (size_t i = 0; i < diag.size(); ++i) out[i] = make_double2(f * diag[i] * in[i].x, f * diag[i] * in[i].y);
 }
 template void launch_dslash<double>(const FineGeom&, const double2*, const double2*, double2*, hipStream_t);
 int dslash_dots_blocks(const FineGeom&) { return 0; }
@@ -87,6 +89,27 @@ int main() {
         check(a.code == HDCR_OK && a.st.outer_iters == k, "the solve stops where it is to", k);
         check(same(a, c), "a late workgroup stops with the others", k);
     }
-    printf(failures ? "cr: %d failed\n" : "cr ok\n", failures);
+    // A second step (the third apply: H x, step 1, step 2) whose |Ap|^2 overflows or vanishes, though
+    // its |Ar|^2 and <r, Ar> do not stop it: it changes nothing, x is the iterate of the first step.
+    const Result one = run(b, 1e-30, 1, simt::IN_TURN);
+    double arar = 0;  // |H r|^2 after the first step
+    for (size_t i = 0; i < n; ++i) {
+        const double rx = b[i].x - diag[i] * one.x[i].x, ry = b[i].y - diag[i] * one.x[i].y;
+        arar += diag[i] * diag[i] * (rx * rx + ry * ry);
+    }
+    odd_apply = 3;
+    odd_scale = sqrt(1.6e308 / arar);
+    const Result big = run(b, 1e-30, 5, simt::IN_TURN);
+    check(big.code == HDCR_ENAN && big.st.outer_iters == 1, "an overflow of |Ap|^2 ends the solve");
+    check(memcmp(big.x.data(), one.x.data(), n * sizeof(double2)) == 0, "with the last good iterate");
+    odd_scale = 1e-170;
+    const Result small = run(b, 1e-30, 5, simt::IN_TURN);
+    check(small.code == HDCR_EBREAKDOWN && small.st.outer_iters == 1, "a vanishing |Ap|^2 ends the solve");
+    check(memcmp(small.x.data(), one.x.data(), n * sizeof(double2)) == 0, "with the last good iterate");
+    odd_apply = 0;
+    if (failures)
+        printf("cr: %d failed\n", failures);
+    else
+        printf("cr ok\n");
     return failures != 0;
 }
