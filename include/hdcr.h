@@ -166,7 +166,8 @@ typedef struct hdcr_solve_stats {
     int32_t status;
     int32_t outer_iters;
     int64_t coarse_iters;       /* total coarse CR iterations */
-    int64_t fine_applies_f64;   /* H applications in FP64 */
+    int64_t fine_applies_f64;   /* H applications in FP64 (plain CR: with those that were enqueued
+                                   behind the stop, which run as well) */
     int64_t fine_applies_inner; /* H applications in the inner precision */
     int64_t coarse_applies;
     double true_rel_residual;

@@ -471,12 +471,12 @@ int cr_solve(const FineGeom& g, const hdcr_solve_params* prm, const double2* U, 
         // steps from the residual in r, in batches
         int step = 0, reason = CR_RUN, batch = 8;
         const int nd = ndots > REDUCE_BLOCKS ? CR_COMPRESS : (ndots > 0 ? ndots : nwg);  // rows of dpart past step 1
-        ++napply;  // the first step's apply
         while (reason == CR_RUN && it < prm->maxiter) {
             const int done = step;
             const int nb = std::min(batch, prm->maxiter - it);
             for (int k = 0; k < nb; ++k) {
                 ++step;
+                ++napply;  // those past the stop run too
                 const double* uin = w.upart[(step - 1) & 1];
                 double* uout = w.upart[step & 1];
                 const int slot = k > 0 ? k - 1 : -1;
@@ -517,7 +517,6 @@ int cr_solve(const FineGeom& g, const hdcr_solve_params* prm, const double2* U, 
             const double before = rr;
             if (did > 0) rr = h.S[S_HIST + did - 1];
             it += did;
-            napply += did;
             // the next batch: half the steps that this batch's rate predicts
             batch = CR_BATCH;
             if (did > 0 && rr < before) {

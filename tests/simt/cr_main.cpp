@@ -88,6 +88,7 @@ int main() {
         const Result a = run(b, tol, 100, simt::IN_TURN), c = run(b, tol, 100, simt::LATE);
         check(a.code == HDCR_OK && a.st.outer_iters == k, "the solve stops where it is to", k);
         check(same(a, c), "a late workgroup stops with the others", k);
+        check(a.st.fine_applies_f64 == a.applies, "every application of H is counted", k);
     }
     // A second step (the third apply: H x, step 1, step 2) whose |Ap|^2 overflows or vanishes, though
     // its |Ar|^2 and <r, Ar> do not stop it: it changes nothing, x is the iterate of the first step.
