@@ -84,8 +84,9 @@ typedef enum {
  *                   kernel with one fifth-dimension slice per work-item (FP32),
  *                   5 paired-slice kernel on FP16 fields, 6 FP16 smoother and filter
  *                   steps as a plain pass plus a separate combination; for
- *                   hdcr_apply_cf: 2 one work-item per 5d site, 4 parity tiles with
- *                   one slice per work-item (else paired slices in FP32 with even Ls)
+ *                   hdcr_apply_cf: 2 site kernel (whole 4d sites per workgroup, links
+ *                   and own spinors in LDS; slice pairs on large FP32 lattices), 4 parity
+ *                   tiles with one slice per work-item (even extents, Ls <= 16)
  *   tslab, ysplit, xsplit  traversal blocking of the stencil's tiles (or sites):
  *                   t slabs of tslab tiles, y and x cut into ysplit and xsplit parts
  *                   (a value that does not divide the extent selects no cut)

@@ -1781,23 +1781,49 @@ void launch_cf_site(const FineGeom& g, const CfCoef& k, const C2<T>* U, const C2
                        ss, k, U, in, out);
 }
 
+// The kernel of hdcr_apply_cf (tune.dslash_variant 2: the site kernel, 4: one-slice tiles
+// where there are tiles).  On large lattices the site kernel, bound by the re-reads of
+// neighbours (24^4 x 9: 268 us, tiles 351, in FP32; 434 and 560 in FP64; 16^4 x 2: 24 and
+// 49), but for the Ls whose tiles are whole wavefronts or near it:
+//   Ls = 16 (24^4 in FP32: 347 and 368 us; 16^4 in FP64: 138 and 148),
+//   FP32 below SITE_PAIRS 5d sites from Ls = 11 on (16^4 x 11: 53 and 57, x 13: 62 and 63),
+//   FP64 from SITE_PAIRS on at Ls = 12 (24^4: 554 and 564).
+// On small lattices the latencies of a workgroup count, and the site kernel's chain is
+// the longer one (links, own spinors, then eight gathers; a tile has half its hops in LDS):
+//   FP32 up to 2^14 sites and 3 2^16 5d sites (4^4 x 3: 6.4 and 9.8 us, 8^4 x 10: 7.0 and
+//   8.5, 8 x 8 x 16 x 16 x 9: 14.9 and 16.5; 12^4 x 9: 20.2 and 17.3),
+//   FP64 up to 2^13 sites (4^4 x 7: 7.3 and 9.5, 8^3 x 16 x 8: 11.7 and 14.8; 10^4 x 8: 17.0
+//   and 15.2), and up to 2^14 from Ls = 12 on (8 x 8 x 16 x 16 x 12: 24.6 and 28.2) or where
+//   the site kernel fills the chip, at two workgroups to a CU, once and little more (10^4 x
+//   14, 556 workgroups: 22.1 and 24.2; 8 x 8 x 16 x 16 x 8, 565: 20.2 and 21.4).
+// FP32 tiles hold slice pairs above that size, where the bytes count (24^4 x 16: 348 us,
+// single slices 365), and single slices below it, with twice the wavefronts (8^4 x 12: 6.9
+// and 9.4 us).
+enum CfTiles { CF_SITES, CF_SINGLE, CF_PAIRS };
+template <typename T> CfTiles cf_tiles(const FineGeom& g) {
+    if (!even_extents(g) || g.Ls > CFT_LS || g.variant == 2) return CF_SITES;
+    const bool big = g.N5 >= SITE_PAIRS, near = g.V4 <= 1 << 14;
+    if (g.variant == 4) return CF_SINGLE;
+    if (sizeof(T) == 4) {
+        if (near && g.N5 <= 3 << 16) return CF_SINGLE;
+        if (g.Ls != 16 && (big || g.Ls < 11)) return CF_SITES;
+        return g.Ls % 2 == 0 ? CF_PAIRS : CF_SINGLE;
+    }
+    SiteSplit ss;
+    int lds;
+    const bool fits = site_split<T, 1>(g, ss, lds, 1);
+    const int nwg = fits ? (g.V4 + ss.sites - 1) / ss.sites : 0;
+    const bool small = g.V4 <= 1 << 13 || (near && (g.Ls >= 12 || (nwg > 512 && nwg <= 640)));
+    return small || g.Ls == 16 || (g.Ls == 12 && big) ? CF_SINGLE : CF_SITES;
+}
+
 template <typename T>
 void launch_cf(const FineGeom& g, const CfCoef& k, const C2<T>* U, const C2<T>* in, C2<T>* out, hipStream_t s) {
-    // Even extents with Ls = 16: parity tiles (paired slices in FP32; 347 against 368 us
-    // at 24^4, 67 against 72 at 16^4; FP64 144 against 147).  Otherwise the site kernel
-    // (24^4 x 9: 268 against 351 us in FP32, 434 against 560 in FP64; 24^4 x 8: 212
-    // against 235; 16^4 x 2: 24 against 49), but for Ls near 16: tiles in FP32 from 12 on
-    // below SITE_PAIRS 5d sites (16^4 x 12: 55 against 58 us; 24^4 x 12: 355 against 312),
-    // and in FP64 at 12 from there on (24^4: 554 against 564 us; 16^4: 111 against 107).
-    // tune.dslash_variant 2 forces the site kernel, 4 the tiles with one slice per
-    // work-item where Ls <= 16.
-    const bool big = g.N5 >= SITE_PAIRS;
-    const bool pick = g.Ls == 16 || (sizeof(T) == 4 ? g.Ls >= 12 && !big : g.Ls == 12 && big);
-    const bool tiles = g.variant != 2 && g.Ls <= CFT_LS && even_extents(g) && (pick || g.variant == 4);
-    if (tiles) {
+    const CfTiles tiles = cf_tiles<T>(g);
+    if (tiles != CF_SITES) {
         const TileGeom tg = tile_geom(g);
         if constexpr (sizeof(T) == 4) {
-            if (g.Ls % 2 == 0 && g.variant != 4) {
+            if (tiles == CF_PAIRS) {
                 hipLaunchKernelGGL((cf_tile_kernel<float, 2>), dim3(tg.t.V4), dim3(16 * g.Ls / 2), 0, s, g, tg, k, U,
                                    in, out);
                 return;

@@ -1,0 +1,46 @@
+"""Kernel choices that depend on the size of the lattice, on both sides of their lines: each call against
+the kernels that a tuning value forces, and FP32 against FP64.  Sums of some 10^2 roundings: 2^-53 each
+stay under 1e-12 of the largest entry, 2^-24 each under 1e-5."""
+import numpy as np
+import pytest
+
+import hdcr_inputs as hi
+import paper_1611_06944_amd as hd
+from tests.gpu_util import log, to_dev, torch_dev
+
+pytestmark = pytest.mark.gpu
+
+
+def _fields(lat, L, seed):
+    torch = torch_dev()
+    U = to_dev(hd.pack_gauge(hi.gauge_field(L, seed=seed)))
+    g = torch.Generator(device="cuda:0").manual_seed(seed)
+    return U, torch.randn((12, lat.V4, lat.Ls), dtype=torch.complex128, device="cuda:0", generator=g)
+
+
+def _err(a, b):
+    return float((a - b).abs().max()) / float(b.abs().max())
+
+
+@pytest.mark.parametrize("L,Ls", [
+    ((8, 8, 8, 16), 8),      # 2^13 sites: FP64 on tiles
+    ((8, 8, 8, 18), 8),      # above: site kernel
+    ((10, 10, 10, 10), 13),  # site kernel would fill the chip once and little more: tiles
+    ((8, 8, 16, 16), 6),     # 2^14 sites: FP32 on single-slice tiles, FP64 on the site kernel
+    ((8, 8, 16, 16), 12),    # 3 2^16 5d sites
+    ((8, 8, 14, 18), 14),    # above: FP32 tiles of slice pairs
+    ((12, 12, 12, 14), 11),  # odd Ls above 2^14 sites: FP32 on single-slice tiles
+    ((12, 12, 12, 14), 16),
+])
+def test_continued_fraction_choices(L, Ls):
+    torch = torch_dev()
+    log(f"cf choices L={L} Ls={Ls}")
+    lat = hd.Lattice(L, Ls, M5=1.7, bc=(1, -1, 1, -1))
+    U, x = _fields(lat, L, 3)
+    beta, R = list(0.3 + 0.1 * np.arange(Ls - 1)), 0.35
+    ref = hd.apply_cf(lat.with_tune(dslash_variant=2), U, x, beta, R)
+    assert _err(hd.apply_cf(lat.with_tune(dslash_variant=4), U, x, beta, R), ref) <= 1e-12
+    assert _err(hd.apply_cf(lat, U, x, beta, R), ref) <= 1e-12
+    U32, x32 = U.to(torch.complex64), x.to(torch.complex64)
+    for variant in (0, 2, 4):
+        assert _err(hd.apply_cf(lat.with_tune(dslash_variant=variant), U32, x32, beta, R), ref) <= 1e-5, variant
