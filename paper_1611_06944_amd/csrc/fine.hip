@@ -1393,7 +1393,18 @@ bool site_pairs(const FineGeom& g) {
 // x 32 x 12 in FP32, 234 against 227 us in FP64).  Odd extents with Ls = 16 in FP32:
 // the tile kernel (29.2 against 30.1 us at 11 x 12 x 13 x 14, 55 against 58 at 15^4).
 // Otherwise the site kernel: against the generic one it takes 117 instead of 202 us
-// (FP32) and 227 instead of 332 us (FP64) at 16^3 x 32 x 12.
+// (FP32) and 227 instead of 332 us (FP64) at 16^3 x 32 x 12; against the tile kernel at Ls =
+// 32 and 64 48 instead of 55 us (12^4 x 32) and 326 instead of 362 us (16^4 x 64) in FP32,
+// 98 instead of 123 and 681 instead of 786 us in FP64.
+// Ls = 32 and 64 below the sizes where the site kernel's larger workgroups fill the chip:
+// the tile kernel, whose chain of latencies is shorter (FP32: 4^4 x 32 6.6 and 7.5 us, 7^4 x
+// 32 11.6 and 12.7, 8^3 x 16 x 64 40.5 and 42.4, but 46.5 and 45.7 at 10^4 x 64; FP64: 4^3 x 8
+// x 64 9.9 and 10.5, but 11.0 and 10.4 at 6^4 x 32).
+template <typename T> bool tile_ls(const FineGeom& g) {
+    if (sizeof(T) == 8) return (g.Ls == 32 || g.Ls == 64) && g.N5 <= 1 << 15;
+    return (g.Ls == 32 && g.V4 <= 1 << 12) || (g.Ls == 64 && g.V4 <= 1 << 13);
+}
+
 template <typename T, int NY>
 bool launch_default(const FineGeom& g, const C2<T>* U, const C2<T>* in, C2<T>* out, const Epi<T>& ep, hipStream_t s) {
     constexpr int W = sizeof(T) == 4 ? 2 : 1;
@@ -1416,7 +1427,8 @@ bool launch_default(const FineGeom& g, const C2<T>* U, const C2<T>* in, C2<T>* o
                            ep, DotOut{});
         return true;
     }
-    if (sizeof(T) == 4 && g.Ls == 16) return false;
+    if ((sizeof(T) == 4 && g.Ls == 16) || tile_ls<T>(g)) return false;
+    if (g.V4 < 32 && g.Ls < 8) return false;  // the generic kernel: 2^4 x 4 in FP32 5.7 and 7.3 us
     if constexpr (W == 2) {
         if (site_pairs(g)) return launch_site<T, 2, NY>(g, U, in, out, ep, s);
     }

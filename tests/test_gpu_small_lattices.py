@@ -44,3 +44,24 @@ def test_continued_fraction_choices(L, Ls):
     U32, x32 = U.to(torch.complex64), x.to(torch.complex64)
     for variant in (0, 2, 4):
         assert _err(hd.apply_cf(lat.with_tune(dslash_variant=variant), U32, x32, beta, R), ref) <= 1e-5, variant
+
+
+@pytest.mark.parametrize("L,Ls", [
+    ((2, 2, 2, 2), 5),       # generic kernel below 32 sites
+    ((4, 2, 2, 2), 5),       # site kernel from there
+    ((4, 4, 4, 8), 64),      # FP64 on the tile kernel (2^15 5d sites)
+    ((4, 4, 4, 9), 64),      # on the site kernel
+    ((8, 8, 8, 8), 32),      # FP32 on the tile kernel (2^12 sites; 2^13 at Ls = 64)
+    ((8, 8, 8, 9), 32),
+    ((8, 8, 8, 16), 64),
+    ((8, 8, 9, 15), 64),
+])
+def test_fine_apply_choices(L, Ls):
+    torch = torch_dev()
+    log(f"apply choices L={L} Ls={Ls}")
+    lat = hd.Lattice(L, Ls, mf=0.05, bc=(1, -1, 1, -1))
+    U, x = _fields(lat, L, 5)
+    ref = hd.apply_fine(lat.with_tune(dslash_variant=2), U, x)
+    assert _err(hd.apply_fine(lat, U, x), ref) <= 1e-12
+    U32, x32 = U.to(torch.complex64), x.to(torch.complex64)
+    assert _err(hd.apply_fine(lat, U32, x32), ref) <= 1e-5
