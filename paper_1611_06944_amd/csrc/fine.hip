@@ -1290,8 +1290,15 @@ void launch_tile(const FineGeom& g, const C2<T>* U, const C2<T>* in, C2<T>* out,
     hipLaunchKernelGGL((dslash_tile_kernel<T, LS, NT, NY>), dim3(blocks), dim3(WG), 0, s, g, U, in, out, ep);
 }
 
+// Sweep: one t slab per XCD or the whole extent, y parts of eight rows or more.  A workgroup
+// holds some hundred sites at the Ls it runs at, so thin slabs and parts only scatter its
+// rows (16^4 x 2 in FP64 45 us, 56 in the site kernel's slabs of four; 10^4 x 2 13.5 and 14.5).
 template <typename T, int NY>
-void launch_generic(const FineGeom& g, const C2<T>* U, const C2<T>* in, C2<T>* out, const Epi<T>& ep, hipStream_t s) {
+void launch_generic(const FineGeom& g0, const C2<T>* U, const C2<T>* in, C2<T>* out, const Epi<T>& ep, hipStream_t s) {
+    FineGeom g = g0;
+    int ysplit = g.L[1] >= 16 ? g.L[1] / 8 : 1;
+    while (g.L[1] % ysplit != 0) --ysplit;
+    choose_traversal(g, g.L[3] % NUM_XCD == 0 ? g.L[3] / NUM_XCD : g.L[3], ysplit);
     const int blocks = (g.N5 + WG - 1) / WG;
     hipLaunchKernelGGL((dslash_dwf_kernel<T, NY>), dim3(blocks), dim3(WG), 0, s, g, U, in, out, ep);
 }
