@@ -466,11 +466,18 @@ int cr_solve(const FineGeom& g, const hdcr_solve_params* prm, const double2* U, 
     } else if (rr <= tol2) {
         status = HDCR_OK;
     }
+    // Steps behind the stop cost an application of H each, and a read-back some 25 us with
+    // the GPU idle.  Where a step is longer than ten of those, a batch is two steps at first,
+    // a quarter of the steps so far later, and ends by the rate of all of them, which a few
+    // steps do not give (24^4 x 16, to 0.9 |b|, two steps: 7.6 ms, eight in the first batch 12.9;
+    // to 0.01 |b|: 114.4 ms, by the last batch's rate 120.7).
+    const bool long_steps = g.N5 >= 1 << 19;
     bool fresh = true;  // r is the true residual of x
     while (status == HDCR_ENOTCONV && it < prm->maxiter) {
         // steps from the residual in r, in batches
-        int step = 0, reason = CR_RUN, batch = 8;
+        int step = 0, reason = CR_RUN, batch = long_steps ? 2 : 8;
         const int nd = ndots > REDUCE_BLOCKS ? CR_COMPRESS : (ndots > 0 ? ndots : nwg);  // rows of dpart past step 1
+        const double rr0 = rr;
         while (reason == CR_RUN && it < prm->maxiter) {
             const int done = step;
             const int nb = std::min(batch, prm->maxiter - it);
@@ -517,12 +524,14 @@ int cr_solve(const FineGeom& g, const hdcr_solve_params* prm, const double2* U, 
             const double before = rr;
             if (did > 0) rr = h.S[S_HIST + did - 1];
             it += did;
-            // the next batch: half the steps that this batch's rate predicts
+            // the next batch: half the steps that the rate predicts
             batch = CR_BATCH;
-            if (did > 0 && rr < before) {
-                const double left = std::log(rr / tol2) / std::log(before / rr) * did;
-                if (left < 2.0 * CR_BATCH) batch = std::max(4, (int)(0.5 * left));
+            const double from = long_steps ? rr0 : before;
+            if (did > 0 && rr < from) {
+                const double left = std::log(rr / tol2) / std::log(from / rr) * (long_steps ? step : did);
+                if (left < 2.0 * CR_BATCH) batch = std::max(long_steps ? 1 : 4, (int)(0.5 * left));
             }
+            if (long_steps) batch = std::min(batch, std::max(2, step / 4));
         }
         if (step % 2 == 1) hipLaunchKernelGGL(cr_flush_kernel, rg, rt, 0, s, n, x, (const double2*)w.p, w.st);
         fresh = false;
