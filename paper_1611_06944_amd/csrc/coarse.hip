@@ -980,23 +980,6 @@ __device__ __forceinline__ void reduce_partials(const double* part, int np, doub
     for (int q = 0; q < NQ; ++q) out[q] = v[q];
 }
 
-// fixed-order sum of nq rows of np partials written by an earlier kernel; every
-// workgroup that calls it gets the same values (no cross-workgroup traffic)
-template <int NQ>
-__device__ __forceinline__ void sum_partials(const double* part, int np, double (&out)[NQ]) {
-    double v[NQ];
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) v[q] = 0.0;
-#pragma unroll 4
-    for (int i = threadIdx.x; i < np; i += blockDim.x) {
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) v[q] += part[(size_t)q * np + i];
-    }
-    block_reduce<NQ>(v);
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) out[q] = v[q];
-}
-
 // Near-breakdown test of the coarse CR: <r, Ar> is the numerator of alpha and the
 // denominator of the next beta; once |<r, Ar>| < eps |r| |Ar| the recurrence makes
 // no progress (alpha ~ 0) or loses its conjugacy (beta unbounded), so the solve

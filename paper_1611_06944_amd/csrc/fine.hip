@@ -1159,13 +1159,11 @@ __global__ void __launch_bounds__(256) dslash_site_kernel(FineGeom g, SiteSplit 
     const int Ls = g.Ls, NK = ss.NK, row = ss.sites * NK;
     Word* spin = reinterpret_cast<Word*>(smem_raw);          // [c][j][kk]
     C2<T>* lds = reinterpret_cast<C2<T>*>(spin + 12 * row);  // [j][matrix][entry]
-    // Work-items past the last site repeat another's loads and LDS stores (same
-    // values, same places) and store nothing: a guarded load would end in a wait
-    // at the branch's join.
-    const int t = (int)threadIdx.x / NK, kk = (int)threadIdx.x - t * NK;
-    const int j = min(t, ss.sites - 1);
+    // sites * NK work-items.  Sites past the lattice's last one repeat it in LDS of their
+    // own and store nothing: a guarded load would end in a wait at the branch's join.
+    const int j = (int)threadIdx.x / NK, kk = (int)threadIdx.x - j * NK;
     const int lsite = logical_block(blockIdx.x, gridDim.x) * ss.sites + j;
-    const bool active = t < ss.sites && lsite < g.V4;
+    const bool active = lsite < g.V4;
     const Site st = traverse(g, min(lsite, g.V4 - 1));
     const Nbrs<T> n = neighbours<T>(g, st);
     FieldRefs f;
@@ -1563,10 +1561,9 @@ __global__ void __launch_bounds__(256) cf_site_kernel(FineGeom g, SiteSplit ss, 
     const int Ls = g.Ls, m = Ls - 1, NK = ss.NK, row = ss.sites * NK;
     Word* spin = reinterpret_cast<Word*>(smem_raw);          // [c][j][kk]
     C2<T>* lds = reinterpret_cast<C2<T>*>(spin + 12 * row);  // [j][matrix][entry]
-    const int t = (int)threadIdx.x / NK, kk = (int)threadIdx.x - t * NK;
-    const int j = min(t, ss.sites - 1);  // work-items past the last site: as in dslash_site_kernel
+    const int j = (int)threadIdx.x / NK, kk = (int)threadIdx.x - j * NK;
     const int lsite = logical_block(blockIdx.x, gridDim.x) * ss.sites + j;
-    const bool active = t < ss.sites && lsite < g.V4;
+    const bool active = lsite < g.V4;  // sites past the lattice's last one: as in dslash_site_kernel
     const Site st = traverse(g, min(lsite, g.V4 - 1));
     const Nbrs<T> n = neighbours<T>(g, st);
     FieldRefs f;
@@ -1653,29 +1650,11 @@ __global__ void __launch_bounds__(256) cf_site_kernel(FineGeom g, SiteSplit ss, 
 // the staged tile.  The output lands at its own slice.
 constexpr int CFT_LS = 16;
 
-template <typename T, int W> struct CfWord;
-template <typename T> struct CfWord<T, 1> {
-    typedef C2<T> type;
-    static __device__ __forceinline__ type ld(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
-        return Buf<T>::ld(r, voff, soff);
-    }
-    static __device__ __forceinline__ C2<T> slice(type w, int) { return w; }
-};
-template <> struct CfWord<float, 2> {
-    typedef float4 type;
-    static __device__ __forceinline__ type ld(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
-        return ld_pair(r, voff, soff);
-    }
-    static __device__ __forceinline__ C2<float> slice(type w, int i) {
-        return i == 0 ? mk<float>(w.x, w.y) : mk<float>(w.z, w.w);
-    }
-};
-
 template <typename T, int W>
 __global__ void __launch_bounds__(16 * CFT_LS / W) __attribute__((amdgpu_waves_per_eu(2))) cf_tile_kernel(FineGeom g, TileGeom tg, CfCoef k,
                                                                   const C2<T>* U, const C2<T>* in, C2<T>* out) {
     static_assert(W == 1 || sizeof(T) == 4, "paired slices are FP32 only");
-    typedef CfWord<T, W> Wd;
+    typedef SliceWord<T, W> Wd;
     typedef typename Wd::type Word;
     constexpr int NKMAX = CFT_LS / W;
     constexpr uint32_t CB = sizeof(C2<T>);
