@@ -805,9 +805,10 @@ __device__ __forceinline__ int lane_nbrs(const CoarseGeom& c, int a) {
 // PB 16-byte loads in flight, the first of them before the vectors are staged; the kg
 // partial sums are added in a fixed order.  One R or another, an output takes the same
 // products in the same order, so the results agree bit for bit.
-// Bound by A for one right-hand side (8192 sites, Nb = 32: 101 us in C64, 50 in BF16),
-// by the FMAs and their LDS reads for many (256 sites, Nb = 48, 12 right-hand sides: 15.0
-// us in C64, 25 in C128; 1296 sites, Nb = 64, 24: 160 us).  Loads two at a time behind the staged vectors took 107, 58, 32.7, 62 and 323 us.
+// Bound by A for one right-hand side (8192 sites, Nb = 32: 102 us in C64, 51 in BF16),
+// by the FMAs and their LDS reads for many (256 sites, Nb = 48, 12 right-hand sides: 15.3
+// us in C64, 24 in C128; 1296 sites, Nb = 64, 24: 164 us).  Loads two at a time behind the
+// staged vectors took 107, 58, 32.7, 62 and 323 us.
 struct ApplySplit {
     int kg;        // row groups
     int ng;        // groups of R right-hand sides
@@ -899,8 +900,10 @@ void coarse_apply_go(const CoarseGeom& c, const S* A, const C2<T>* v, C2<T>* out
                        (apply_lds<T, S, E, R>(c)), s, c, sp, A, v, out, nrhs);
 }
 // the R of least work: right-hand sides taken, idle ones included, and two for the reads
-// of A (in us, C64: 256 sites, Nb = 48, 12 right-hand sides R = 4, 6, 8: 14.2, 14.8, 17.9;
-// 8192 sites, Nb = 32, 8: 147, 165, 134; 1296 sites, Nb = 64, 24: 168, 153, 157; one: 393)
+// of A (in us, C64, R = 4, 6, 8: 4096 sites, Nb = 24, 12 right-hand sides 58, 51, 67; 8192
+// sites, Nb = 32, 8: 150, 170, 138; 1296 sites, Nb = 64, 24: 173, 161, 164; where six leave
+// fewer workgroups than the chip holds, four are up to 6% faster: 256 sites, Nb = 48, 12:
+// 14.4, 15.3, 18.9)
 template <typename T, typename S, int E>
 void coarse_apply_pick(const CoarseGeom& c, const S* A, const C2<T>* v, C2<T>* out, int nrhs, hipStream_t s) {
     int best = 1, cost = nrhs * 3;

@@ -243,8 +243,7 @@ bool launch_dslash_h16_epi(const FineGeom& g, const float2* U, const void* in, v
 // Continued-fraction form of the overlap operator (Sec. 3) on Ls = m + 1 slices:
 //   out_s = sigma_s H_W psi_s + [s = m] R gamma5 psi_s + cdn_s psi_(s-1) + cup_s psi_(s+1),
 // H_W = gamma5 D_W(-M5) with D_W's diagonal wdiag = 4 - M5 and the 4d hops of
-// FineGeom (coefficient g.hop = -1/2, boundary factors bc).  sites: 4d sites per
-// workgroup (sites * Ls <= 256 work-items).
+// FineGeom (coefficient g.hop = -1/2, boundary factors bc).
 constexpr int CF_MAX_LS = 64;
 struct CfCoef {
     double sigma[CF_MAX_LS];
@@ -302,8 +301,9 @@ __device__ __forceinline__ void block_reduce(double (&v)[NQ]) {
 
 // Sums carried as hi + lo, for inner products whose combination cancels: the
 // error terms of every product and sum are kept (TwoProduct by FMA and Knuth's
-// TwoSum), so a sum of n products is good to about n 2^-106 of the sum of their
-// magnitudes.  Free beside memory traffic: some ten operations per product.
+// TwoSum).  The error terms are added in plain double, so a sum of n products is good to
+// some n^2 2^-106 of the sum of their magnitudes at worst, and to 2^-53 of itself.  Free
+// beside memory traffic: some ten operations per product.
 struct Sum2 {
     double hi, lo;
 };
