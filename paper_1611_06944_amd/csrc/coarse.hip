@@ -1426,9 +1426,10 @@ void ccr_step_launch(const CoarseGeom& c, const S* A, C2<T>* x, const CoarseCRWo
 // component and row tile.  The site is the same for the whole workgroup, so the links
 // come through the scalar unit.
 //
-// Bound by the latency of the hops' loads at three wavefronts per SIMD (waiting 87% of
-// the time; the matrix cores need 4 ms of 17.6 at 16^4 x 16, nvec = 24, 4^4 blocks): a
-// block's columns are 19 MB there, so a site's neighbours come from memory again.
+// Bound by the latency of the hops' loads at three wavefronts per SIMD (a wavefront waits
+// for data 42% of its cycles and to issue 45%; the matrix cores need 4 ms of 17.7 at 16^4 x
+// 16, nvec = 24, 4^4 blocks): a block's columns are 19 MB there, so a site's neighbours
+// come from memory again.
 // Images of all basis vectors in memory and two dot-product kernels took 62 ms; the
 // whole H on the matrix cores 24; both row chiralities in one wavefront, two per SIMD,
 // the same.

@@ -148,10 +148,10 @@ __device__ __forceinline__ int cr_stop(double rr, double tol2) {
 // every second step x += alpha_old p_old + alpha p.  uin / uout: partials of |r|^2
 // and |Ap|^2 (hi, lo) of the previous and of this step.  slot: place of the previous
 // step's |r|^2 in the batch's history, or -1.
-// Bound by the 8 or 10 vectors it streams, and on small lattices by the start:
-// with the apply a step takes 37.4 us at 8^4 x 16, 39.6 with the first elements loaded
-// after the scalars (then 1024 workgroups with two elements in flight 43.2, 256 with four
-// 39.1, against these 512 with three).
+// Bound by the 7 or 9 vectors it streams (24^4 x 16: 1.46 and 1.77 ms, 4.9 and 5.2 TB/s),
+// and on small lattices by the start: with the apply a step takes 37.4 us at 8^4 x 16,
+// 39.6 with the first elements loaded after the scalars (then 1024 workgroups with two
+// elements in flight 43.2, 256 with four 39.1, against these 512 with three).
 template <bool FIRST, bool XUP>
 __global__ void __launch_bounds__(REDUCE_THREADS) cr_step_kernel(int64_t n, double2* __restrict__ x,
                                                                  double2* __restrict__ r, double2* __restrict__ p,
