@@ -65,3 +65,28 @@ def test_fine_apply_choices(L, Ls):
     assert _err(hd.apply_fine(lat, U, x), ref) <= 1e-12
     U32, x32 = U.to(torch.complex64), x.to(torch.complex64)
     assert _err(hd.apply_fine(lat, U32, x32), ref) <= 1e-5
+
+
+@pytest.mark.parametrize("L,Ls", [
+    ((4, 4, 2, 6), 8),       # parity tiles of slice pairs
+    ((4, 6, 4, 4), 16),
+    ((11, 9, 10, 14), 10),   # site kernels with slice pairs
+])
+def test_fields_aligned_to_one_entry(L, Ls):
+    """FP32 fields need the alignment of an entry, 8 bytes; kernels with 16-byte accesses give the same
+    bits for them as for fields on 16 bytes."""
+    torch = torch_dev()
+    log(f"alignment L={L} Ls={Ls}")
+    lat = hd.Lattice(L, Ls, mf=0.05)
+    U, x = _fields(lat, L, 7)
+    U, x = U.to(torch.complex64), x.to(torch.complex64)
+
+    def shifted(t):
+        buf = torch.zeros(t.numel() + 2, dtype=t.dtype, device=t.device)
+        view = buf[1:1 + t.numel()].view(t.shape)
+        assert view.data_ptr() % 16 == 8
+        return view.copy_(t)
+
+    beta = list(0.3 + 0.1 * np.arange(Ls - 1))
+    for f in (lambda u, v, o: hd.apply_fine(lat, u, v, out=o), lambda u, v, o: hd.apply_cf(lat, u, v, beta, 0.35, out=o)):
+        assert torch.equal(f(shifted(U), shifted(x), shifted(torch.zeros_like(x))), f(U, x, torch.zeros_like(x)))
