@@ -1894,9 +1894,9 @@ void restrict_launch_w(const CoarseGeom& c, const B* basis, const C2<T>* psi, co
     // Full groups where there are any, in FP32 arithmetic (FP64 takes 253 registers with
     // them, 950 against 894 us at 16^4 x 16, 4^4 blocks, nvec = 24).  The FP32 copy with
     // large blocks streams a little slower that way once it is far larger than the caches
-    // (4^4 blocks: 16^4 x 16, nvec = 32, 3.2 GB, 523 against 647 us; 24^4 x 16, nvec = 16,
-    // 8.2 GB, 1492 against 1475, nvec = 32 2776 against 2677; 2^4 blocks there 1334
-    // against 1570).
+    // (4^4 blocks: 16^4 x 16, nvec = 32, 3.2 GB, 523 against 647 us; 16^3 x 32 x 16, nvec =
+    // 32, 6.4 GB, 1074 against 1097; 24^4 x 16, nvec = 16, 8.2 GB, 1492 against 1475, nvec = 32
+    // 2776 against 2677; 2^4 blocks there 1334 against 1570).
     if constexpr (sizeof(T) == 4) {
         const bool far = std::is_same<B, C2<T>>::value && c.bvol > 16 && basis_elems(c) * sizeof(B) > ((size_t)6 << 30);
         if (c.nvec >= RKG && !far) return restrict_launch_f<T, B, W, RKG, true>(c, basis, psi, psi2, v, s);
