@@ -32,6 +32,8 @@
 // hop coefficient (-1/2, times bc[mu] across the boundary) is applied in the
 // accumulating FMAs.  The output is written at (x, Ls-1-s) with the lower
 // spins negated: H = gamma5 R5 D.
+#include <type_traits>
+
 #include "internal.h"
 
 namespace hdcr {
@@ -1111,11 +1113,10 @@ struct SiteSplit {
     int sites;  // sites per workgroup
 };
 // the eight link matrices of a site to lds, by its NK work-items (kk)
-template <typename T, int W>
+template <typename T, int W, int LB>
 __device__ __forceinline__ void stage_site_links(const FieldRefs& f, const Site& st, const Nbrs<T>& n, int kk, int NK,
                                                  C2<T>* lds) {
     constexpr uint32_t CB = sizeof(C2<T>);
-    constexpr int LB = (W == 2) ? 18 : 9;
     for (int i0 = 0; i0 * NK < 72; i0 += LB) {
         C2<T> lk[LB];
 #pragma unroll
@@ -1149,7 +1150,7 @@ __device__ __forceinline__ void stage_site_links(const FieldRefs& f, const Site&
             hop_core<T, MU, FWD>(w, u, FWD ? n.cf[MU] : n.cb[MU], a[i]);                                      \
         }                                                                                                     \
     }
-template <typename T, int W, int NY>
+template <typename T, int W, int NY, int LB>
 __global__ void __launch_bounds__(256) dslash_site_kernel(FineGeom g, SiteSplit ss, const C2<T>* U, const C2<T>* in,
                                                           C2<T>* out, Epi<T> ep) {
     typedef SliceWord<T, W> Wd;
@@ -1171,7 +1172,7 @@ __global__ void __launch_bounds__(256) dslash_site_kernel(FineGeom g, SiteSplit 
     f.in = make_rsrc(in, 12u * f.cstride);
     f.out = make_rsrc(out, 12u * f.cstride);
     f.U = make_rsrc(U, (uint32_t)g.V4 * 36u * CB);
-    stage_site_links<T, W>(f, st, n, kk, NK, lds + j * 8 * LPAD);
+    stage_site_links<T, W, LB>(f, st, n, kk, NK, lds + j * 8 * LPAD);
     const int s0 = W * kk;
     const uint32_t o0 = (uint32_t)(st.site * Ls + s0) * CB;
     C2<T> v[W][12];
@@ -1372,13 +1373,30 @@ template <typename T, int W> bool site_split(const FineGeom& g, SiteSplit& ss, i
     lds = ss.sites * per;
     return ss.sites > 0;
 }
+// The link entries that a work-item loads in one batch, LB: of the 72 of a site its NK
+// work-items take 72 / NK each, entries past the last being loaded again.  One batch of 12
+// instead of two of 9 takes 0.95 of the time at NK = 6 and 7, two instead of three 0.98 at 3,
+// and batches of 5 instead of 9 0.97 from 15 on (4^4 to 24^4, FP32 and FP64, 0.91 at the
+// smallest); 12 at NK = 4 and 5, whose two batches of 9 waste less, 1.06.
+template <int W, typename F> void with_link_batch(const SiteSplit& ss, F&& go) {
+    if constexpr (W == 2)
+        go(std::integral_constant<int, 18>{});
+    else if (ss.NK < 4 || ss.NK == 6 || ss.NK == 7)
+        go(std::integral_constant<int, 12>{});
+    else if (ss.NK < 15)
+        go(std::integral_constant<int, 9>{});
+    else
+        go(std::integral_constant<int, 5>{});
+}
 template <typename T, int W, int NY>
 bool launch_site(const FineGeom& g, const C2<T>* U, const C2<T>* in, C2<T>* out, const Epi<T>& ep, hipStream_t s) {
     SiteSplit ss;
     int lds;
     if (!site_split<T, W>(g, ss, lds)) return false;
-    hipLaunchKernelGGL((dslash_site_kernel<T, W, NY>), dim3((g.V4 + ss.sites - 1) / ss.sites), dim3(ss.sites * ss.NK), lds,
-                       s, g, ss, U, in, out, ep);
+    with_link_batch<W>(ss, [&](auto lb) {
+        hipLaunchKernelGGL((dslash_site_kernel<T, W, NY, decltype(lb)::value>), dim3((g.V4 + ss.sites - 1) / ss.sites),
+                           dim3(ss.sites * ss.NK), lds, s, g, ss, U, in, out, ep);
+    });
     return true;
 }
 
@@ -1551,7 +1569,7 @@ namespace {
 // wall site kernel.  The slice couplings read their partners psi(s -+ 1) from the
 // staged spinors, and each output is written once, at its own slice.  Bound by the
 // neighbours' re-reads: 268 us at 24^4 x 9 in FP32 (2.2 TB/s of the two fields).
-template <typename T, int W>
+template <typename T, int W, int LB>
 __global__ void __launch_bounds__(256) cf_site_kernel(FineGeom g, SiteSplit ss, CfCoef k, const C2<T>* U, const C2<T>* in,
                                                       C2<T>* out) {
     typedef SliceWord<T, W> Wd;
@@ -1571,7 +1589,7 @@ __global__ void __launch_bounds__(256) cf_site_kernel(FineGeom g, SiteSplit ss, 
     f.in = make_rsrc(in, 12u * f.cstride);
     f.out = make_rsrc(out, 12u * f.cstride);
     f.U = make_rsrc(U, (uint32_t)g.V4 * 36u * CB);
-    stage_site_links<T, W>(f, st, n, kk, NK, lds + j * 8 * LPAD);
+    stage_site_links<T, W, LB>(f, st, n, kk, NK, lds + j * 8 * LPAD);
     const int s0 = W * kk;
     const uint32_t o0 = (uint32_t)(st.site * Ls + s0) * CB;
     C2<T> a[W][12];
@@ -1775,8 +1793,10 @@ void launch_cf_site(const FineGeom& g, const CfCoef& k, const C2<T>* U, const C2
     SiteSplit ss;
     int lds;
     if (!site_split<T, W>(g, ss, lds, 1)) return;  // not reachable: Ls <= CF_MAX_LS
-    hipLaunchKernelGGL((cf_site_kernel<T, W>), dim3((g.V4 + ss.sites - 1) / ss.sites), dim3(ss.sites * ss.NK), lds, s, g,
-                       ss, k, U, in, out);
+    with_link_batch<W>(ss, [&](auto lb) {
+        hipLaunchKernelGGL((cf_site_kernel<T, W, decltype(lb)::value>), dim3((g.V4 + ss.sites - 1) / ss.sites),
+                           dim3(ss.sites * ss.NK), lds, s, g, ss, k, U, in, out);
+    });
 }
 
 // The kernel of hdcr_apply_cf (tune.dslash_variant 2: the site kernel, 4: one-slice tiles

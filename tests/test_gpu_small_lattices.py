@@ -5,8 +5,9 @@ import numpy as np
 import pytest
 
 import hdcr_inputs as hi
+import oracle
 import paper_1611_06944_amd as hd
-from tests.gpu_util import log, to_dev, torch_dev
+from tests.gpu_util import log, max_rel_elem, to_dev, to_host, torch_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -90,3 +91,22 @@ def test_fields_aligned_to_one_entry(L, Ls):
     beta = list(0.3 + 0.1 * np.arange(Ls - 1))
     for f in (lambda u, v, o: hd.apply_fine(lat, u, v, out=o), lambda u, v, o: hd.apply_cf(lat, u, v, beta, 0.35, out=o)):
         assert torch.equal(f(shifted(U), shifted(x), shifted(torch.zeros_like(x))), f(U, x, torch.zeros_like(x)))
+
+
+@pytest.mark.parametrize("Ls", [2, 3, 4, 5, 6, 7, 8, 14, 15, 17, 71, 72, 73])
+def test_link_batches(Ls):
+    """Site kernels at the work-items per site where their batches of link loads change, and where there
+    are as many as link entries; odd extents, a short last workgroup."""
+    torch = torch_dev()
+    L, bc = (3, 5, 1, 3), (1, -1, 1, -1)
+    log(f"link batches Ls={Ls}")
+    lat = hd.Lattice(L, Ls, M5=1.8, mf=0.07, bc=bc)
+    U, x = hi.gauge_field(L, seed=1), hi.gaussian_fermion(L, Ls, seed=0)
+    ref = oracle.apply_h(U, x, oracle.Params(L, Ls, M5=1.8, mf=0.07, bc=bc))
+    beta = list(0.2 + np.random.default_rng(Ls).random(Ls - 1))
+    cf = oracle.apply_cf(U, x, 1.8, beta, 0.35, bc) if Ls <= 64 else None
+    for dt, tol in ((torch.complex128, 1e-10), (torch.complex64, 1e-5)):
+        Ud, xd = to_dev(hd.pack_gauge(U), dt), to_dev(hd.pack_fermion(x), dt)
+        assert max_rel_elem(hd.unpack_fermion(to_host(hd.apply_fine(lat, Ud, xd)), L, Ls), ref) <= tol, dt
+        if cf is not None:
+            assert max_rel_elem(hd.unpack_fermion(to_host(hd.apply_cf(lat, Ud, xd, beta, 0.35)), L, Ls), cf) <= tol, dt
